@@ -41,8 +41,9 @@ Layout layout_for(int64_t n) {
   if (!needs_global(n)) return L;
   L.tiles = (n + kGlobalTile - 1) / kGlobalTile;
   // histogram rows: whole blocks of kHistRows rows, never more than kMaxBlocks
+  // (the one-tile-per-workgroup path's rows: at most kTileRows)
   const size_t blocks = (size_t)std::min<int64_t>(
-      (L.tiles + kHistRows - 1) / kHistRows * kHistRows, kMaxBlocks);
+      std::max<int64_t>((L.tiles + kHistRows - 1) / kHistRows * kHistRows, kTileRows), kMaxBlocks);
   size_t off = kHeaderBytes;
   auto take = [&](size_t bytes) {
     const size_t at = off;
@@ -83,6 +84,13 @@ int force_wide() {
 // (the one queues longer than 2^30 requests use), so that layout stays testable.
 int no_compact() {
   const char* e = std::getenv("SEMSCHED_NO_COMPACT");
+  return (e && e[0] == '1') ? 1 : 0;
+}
+
+// SEMSCHED_NO_TILES=1 sends queues of every length above the LDS path through
+// the big-tile path, so that it stays testable on small queues.
+int no_tiles() {
+  const char* e = std::getenv("SEMSCHED_NO_TILES");
   return (e && e[0] == '1') ? 1 : 0;
 }
 
@@ -284,8 +292,15 @@ int enqueue_queue(const uint8_t* p, const int32_t* l, int64_t n, int32_t num_cla
       trace_slots().before[k] = trace_slots().after[k] = nullptr;
     }
   }
-  return launch_global_schedule(g, st, armed ? &ev : nullptr) == hipSuccess ? SEM_OK
-                                                                           : SEM_EDEVICE;
+  // Queues that one tile per workgroup covers take the latency-oriented path;
+  // the knobs that name a layout of the big-tile path keep that path.
+  const bool tiled = n <= kTileMaxItems && !no_tiles() && !g.force_wide && !no_compact() &&
+                     g.d0 == 10;
+  if (tiled) g.chunked = 0;
+  return (tiled ? launch_tile_schedule(g, st, armed ? &ev : nullptr)
+                : launch_global_schedule(g, st, armed ? &ev : nullptr)) == hipSuccess
+             ? SEM_OK
+             : SEM_EDEVICE;
 }
 
 // Workspace of an insertion: the arrivals' own schedule (its workspace first,

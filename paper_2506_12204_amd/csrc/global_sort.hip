@@ -38,6 +38,7 @@
 //                wait come out of the same pass, plus the per-class totals.
 #include "block_common.h"
 #include "kernels.h"
+#include "key_plan.h"
 
 namespace semsched {
 
@@ -150,53 +151,10 @@ __device__ void write_plan(const GArgs& a, int G) {
     pl->ok = 0;
     return;
   }
-  const uint32_t d0 = (uint32_t)a.d0;
-  const uint32_t P = gpmax - gpmin + 1;
-  const uint32_t hmin = glmin >> d0;
-  const uint32_t H = (glmax >> d0) - hmin + 1;
-  const uint32_t wp = bit_width32(P - 1);
-  const uint32_t wh = bit_width32(H - 1);
-  const uint32_t wid = bit_width32((uint32_t)(a.n - 1));
-  const uint32_t kb = wp + wh + d0;  // live key bits
-  pl->pmin = gpmin;
-  pl->P = P;
-  pl->hmin = hmin;
-  pl->H = H;
-  pl->wp = wp;
-  pl->wh = wh;
-  // A key of at most 32 bits sits in the high word above a 32-bit id, so no
-  // shifts across words are needed to take an element apart.
-  pl->W = (!a.force_wide && kb <= 32) ? 32u : wid;
-  pl->packed = (!a.force_wide && kb + pl->W <= 64) ? 1u : 0u;
-  pl->small = glmax < (1u << 26) ? 1u : 0u;
-  const uint64_t R = (uint64_t)P * H;  // <= 2^31 because d0 >= 8
-  pl->shift[0] = 0;
-  pl->nbits[0] = d0;
-  pl->nbins[0] = 1u << d0;
-  uint32_t mids = 0;
-  if (R > (uint64_t)kMaxBins) {
-    const uint32_t b2 = bit_width32((uint32_t)(R - 1));
-    mids = (b2 - 10 + 9) / 10;
-  }
-  for (uint32_t s = 1; s <= mids; ++s) {
-    pl->shift[s] = 10 * (s - 1);
-    pl->nbits[s] = 10;
-    pl->nbins[s] = kMaxBins;
-  }
-  const uint32_t sf = 10 * mids;
-  const uint32_t fb = (uint32_t)((R - 1) >> sf) + 1;
-  pl->shift[1 + mids] = sf;
-  pl->nbins[1 + mids] = fb;
-  pl->nbits[1 + mids] = bit_width32(fb - 1);
-  pl->nscatter = 2 + mids;
-  // compact layout: two passes, at most 256 final digits (the big-tile final
-  // pass), lengths below 2^26, and the sub-bucket starts were counted
-  pl->compact = (a.chunked && !a.force_wide && mids == 0 && fb <= 256 && pl->small) ? 1u : 0u;
+  make_plan(a, gpmin, gpmax, glmin, glmax, pl);
   // carried ranks: above the final digit's bits, if they fit the u32 element
-  pl->pay = 0;
-  pl->pay_shift = 32;
   if (pl->compact && a.payload) {
-    const uint32_t at = kChunkBits + bit_width32(fb - 1);
+    const uint32_t at = kChunkBits + pl->nbits[1];
     if (at + bit_width32(*a.pay_pmax) <= 32) {
       pl->pay = 1;
       pl->pay_shift = at;
@@ -455,37 +413,6 @@ __global__ __launch_bounds__(SCT) void g_scan(GArgs a, int final) {
 
 // ------------------------------------------------------------------------
 // Scatter passes.
-
-struct KeyCodec {
-  uint32_t d0, wh, W, hmin, H, pmin;
-  uint64_t m0, mh, idmask;
-  __device__ __forceinline__ void init(const GArgs& a, const Plan* pl) {
-    d0 = (uint32_t)a.d0;
-    wh = pl->wh;
-    W = pl->W;
-    hmin = pl->hmin;
-    H = pl->H;
-    pmin = pl->pmin;
-    m0 = (1ull << d0) - 1;
-    mh = (1ull << wh) - 1;
-    idmask = (1ull << W) - 1;
-  }
-  __device__ __forceinline__ uint32_t lo(uint64_t key) const { return (uint32_t)(key & m0); }
-  __device__ __forceinline__ uint32_t h(uint64_t key) const {
-    return (uint32_t)((key >> d0) & mh);
-  }
-  __device__ __forceinline__ uint32_t pp(uint64_t key) const {
-    return (uint32_t)(key >> (d0 + wh));
-  }
-  __device__ __forceinline__ uint32_t u2(uint64_t key) const { return pp(key) * H + h(key); }
-  __device__ __forceinline__ uint32_t len(uint64_t key) const {
-    return ((h(key) + hmin) << d0) | lo(key);
-  }
-  __device__ __forceinline__ uint64_t make(uint32_t p, uint32_t l) const {
-    return ((uint64_t)(p - pmin) << (d0 + wh)) | ((uint64_t)((l >> d0) - hmin) << d0) |
-           (l & (uint32_t)m0);
-  }
-};
 
 // Stable rank of the tile's K rounds by digit: on return rk[r] is the position
 // of item (wave, round r, lane) in the tile's digit-sorted order and excl[b]
@@ -1509,50 +1436,6 @@ union MidShared {
   CountMidShared count;
   uint32_t part4[NT / kWave][4];
 };
-
-// Grid barrier of the middle-pass kernel, a normal launch whose grid is the
-// number of workgroups that fit on the device at once. Workgroup leaders add
-// to the arrival count; the last to arrive resets it and publishes the
-// barrier's generation in the release word, which the others poll. The wait
-// is bounded: if the workgroups were not all resident (another program
-// holding CUs), a leader gives up after a.mid_spin polls, records
-// kFlagDevice, clears the plan's ok word (so the kernels after this one do
-// nothing) and every workgroup leaves at its next barrier; the blocking
-// calls then run the schedule again with the middle passes as separate
-// launches per phase, which need no residency.
-__device__ bool grid_barrier(const GArgs& a, uint32_t gen) {
-  __shared__ uint32_t s_ok;
-  __threadfence();  // release this workgroup's writes at agent scope
-  block_sync();
-  if (threadIdx.x == 0) {
-    uint32_t ok = 1;
-    if (atomicAdd(&a.msync->arrive, 1u) == gridDim.x - 1) {
-      __hip_atomic_store(&a.msync->arrive, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      __hip_atomic_store(&a.msync->release, gen, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
-    } else {
-      // relaxed polls: an acquire load would invalidate this XCD's L2 at
-      // every poll, under the workgroups still working there; the fence
-      // after the wait orders what follows
-      for (uint32_t spin = 0; __hip_atomic_load(&a.msync->release, __ATOMIC_RELAXED,
-                                                __HIP_MEMORY_SCOPE_AGENT) < gen;
-           ++spin) {
-        if (spin >= a.mid_spin || ((spin & 63) == 63 && (load_agent(a.flags) & kFlagDevice))) {
-          atomicOr(a.flags, kFlagDevice);
-          // the later kernels of this schedule then return at once
-          __hip_atomic_store(&a.plan->ok, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          ok = 0;
-          break;
-        }
-        __builtin_amdgcn_s_sleep(1);
-      }
-    }
-    if (load_agent(a.flags) & kFlagDevice) ok = 0;
-    s_ok = ok;
-  }
-  block_sync();
-  __threadfence();  // acquire the other workgroups' writes
-  return s_ok != 0;
-}
 
 // The middle passes: per pass, count every block, scan the counts per digit
 // over the blocks, scatter every block, with grid barriers between the phases.
@@ -2830,13 +2713,13 @@ Split make_split(int64_t n, int resident, int mult) {
   return s;
 }
 
-void mark(const StageEvents* ev, int stage, bool after, hipStream_t st) {
+}  // namespace
+
+void mark_stage(const StageEvents* ev, int stage, bool after, hipStream_t st) {
   if (!ev) return;
   hipEvent_t e = after ? ev->after[stage] : ev->before[stage];
   if (e) (void)hipEventRecord(e, st);
 }
-
-}  // namespace
 
 Split global_first_split(int64_t n) {
   static const int r = resident_blocks(reinterpret_cast<const void*>(g_first<10>), NT);
@@ -2857,24 +2740,21 @@ hipError_t launch_global_schedule(const GArgs& a, hipStream_t st, const StageEve
   const int vec_ok = ((uintptr_t)a.priority % 4 == 0) && ((uintptr_t)a.length % 16 == 0);
   const dim3 gm(a.main.blocks);
   const dim3 gmh(a.main.blocks * kHistRows);
-  mark(ev, 0, false, st);
+  mark_stage(ev, 0, false, st);
   hipLaunchKernelGGL(g_hist0, gmh, dim3(HT), 0, st, a, vec_ok);
-  mark(ev, 0, true, st);
+  mark_stage(ev, 0, true, st);
   hipLaunchKernelGGL(g_scan, dim3((1u << a.d0) + 1), dim3(SCT), 0, st, a, 0);
-  mark(ev, 1, false, st);
+  mark_stage(ev, 1, false, st);
   if (a.d0 == 9)
     hipLaunchKernelGGL(g_first<9>, gm, dim3(NT), 0, st, a);
   else if (a.d0 == 10)
     hipLaunchKernelGGL(g_first<10>, gm, dim3(NT), 0, st, a);
   else
     hipLaunchKernelGGL(g_first<8>, gm, dim3(NT), 0, st, a);
-  mark(ev, 1, true, st);
-  mark(ev, 6, false, st);
+  mark_stage(ev, 1, true, st);
+  mark_stage(ev, 6, false, st);
   if (a.split_mid) {
-    // Ranks below 2^8 and lengths below 2^31 make the mixed-radix value
-    // below 2^(39 - d0), so at most (38 - d0) / 10 middle passes of 10 bits.
-    const int max_mids = (38 - a.d0) / 10;
-    for (int s = 1; s <= max_mids && s < kMaxScatter - 1; ++s) {
+    for (int s = 1; s <= max_mid_passes(a.d0); ++s) {
       hipLaunchKernelGGL(g_mid_count, dim3(a.mid.blocks), dim3(NT), 0, st, a, s);
       hipLaunchKernelGGL(g_mid_scan, dim3(kMaxBins / 4), dim3(NT), 0, st, a, s);
       hipLaunchKernelGGL(g_mid_scatter, dim3(a.mid.blocks), dim3(NT), 0, st, a, s);
@@ -2882,11 +2762,11 @@ hipError_t launch_global_schedule(const GArgs& a, hipStream_t st, const StageEve
   } else {
     hipLaunchKernelGGL(g_mid, dim3(a.mid.blocks), dim3(NT), 0, st, a);
   }
-  mark(ev, 6, true, st);
+  mark_stage(ev, 6, true, st);
   const dim3 gf(a.fin.blocks);
   hipLaunchKernelGGL(g_histF, dim3(a.fin.blocks * kHistRows), dim3(HT), 0, st, a);
   hipLaunchKernelGGL(g_scan, dim3(kMaxBins + 1), dim3(SCT), 0, st, a, 1);
-  mark(ev, 2, false, st);
+  mark_stage(ev, 2, false, st);
   // exactly one of the two does the work; the plan on the device decides
   hipLaunchKernelGGL(g_final_big, gf, dim3(NTB), 0, st, a);
   if (a.chunked) hipLaunchKernelGGL(g_final_cglb, gf, dim3(NTB), 0, st, a);
@@ -2895,7 +2775,7 @@ hipError_t launch_global_schedule(const GArgs& a, hipStream_t st, const StageEve
     hipLaunchKernelGGL(g_final_pay_cglb, gf, dim3(NTB), 0, st, a);
   }
   hipLaunchKernelGGL(g_final<>, gf, dim3(NT), 0, st, a);
-  mark(ev, 2, true, st);
+  mark_stage(ev, 2, true, st);
   return hipGetLastError();
 }
 

@@ -247,6 +247,21 @@ Split global_first_split(int64_t n);
 Split global_final_split(int64_t n);
 Split global_mid_split(int64_t n);
 hipError_t launch_global_schedule(const GArgs& a, hipStream_t st, const StageEvents* ev);
+// Most middle passes a key can need: ranks below 2^8 and lengths below 2^31
+// make the mixed-radix value below 2^(39 - d0), of which the final pass takes
+// at most 10 bits.
+inline int max_mid_passes(int d0) {
+  const int m = (38 - d0) / 10;
+  return m < kMaxScatter - 2 ? m : kMaxScatter - 2;
+}
+// Records the stage's event, if one is armed.
+void mark_stage(const StageEvents* ev, int stage, bool after, hipStream_t st);
+
+// The same schedule with one tile per workgroup, for queues of at most
+// kTileMaxItems requests (tile_sort.hip). Packed keys only (force_wide == 0).
+constexpr int kTileRows = 128;  // most tiles of such a queue
+constexpr int64_t kTileMaxItems = (int64_t)kTileRows * 8192;
+hipError_t launch_tile_schedule(const GArgs& a, hipStream_t st, const StageEvents* ev);
 
 // Zeroes `count` 32-bit words (graph-safe replacement for a memset).
 hipError_t launch_fill_zero(uint32_t* p, size_t count, hipStream_t st);

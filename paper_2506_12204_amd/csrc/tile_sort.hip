@@ -1,0 +1,797 @@
+// Schedule of one queue of middling length (more than one workgroup's LDS
+// holds, at most kTileMaxItems), one tile per workgroup.
+//
+// The same LSD radix sort as global_sort.hip (Algorithm 1's drained min-heap:
+// ids ascending by (priority, length, id); the waits of Eq. 1 and the class
+// totals in the last pass), laid out for latency instead of bandwidth: such a
+// queue lies in the caches, so what counts is the number of launches and the
+// length of each kernel's chain, not the bytes. Tiles of 1024 to 8192
+// requests give 17 to 128 workgroups of 16 waves, elements are whole
+// u64 (key above id, nothing to look up by position), and the offsets of a
+// tile are summed by the workgroup that needs them from the other tiles'
+// count rows, so no scan is launched between a count and its scatter:
+//   t_count   ranges and first-digit counts of every tile
+//   t_first   the plan from the ranges, the tile's offsets, first scatter
+//   t_histF   middle passes of wide keys, then final-digit counts and length
+//             sums of every tile
+//   t_final   offsets, order, waits; the last workgroup adds up the totals
+// Measured: a queue of 50,003 requests 156 us in the big-tile path's nine
+// launches (16K-item tiles: 4 workgroups), 28 us here; one of 2^20 76 us (64
+// workgroups), 51 us here.
+#include "block_common.h"
+#include "kernels.h"
+#include "key_plan.h"
+
+namespace semsched {
+
+namespace {
+
+constexpr int TT = 1024;  // threads: one per digit
+constexpr int TWV = TT / kWave;
+static_assert(TT == kMaxBins, "every thread owns one digit");
+constexpr int kCountCopies = 8;  // copies of a count (lane % 8): equal digits in a wave
+                                 // (short lengths, few classes) spread over them
+constexpr int kFinalSlots = 8192;  // u64 slots of the final digit's counts, all copies
+
+__device__ __forceinline__ int wave_no() {
+  return __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
+}
+
+__device__ __forceinline__ void clear_row(uint16_t* cnt) {  // this wave's 1024 counters
+  u64_alias* c64 = reinterpret_cast<u64_alias*>(cnt);
+#pragma unroll
+  for (int i = 0; i < kMaxBins / (kWave * 4); ++i) c64[i * kWave + lane_id()] = 0;
+}
+
+// The count rows of the tile path: first-digit counts (u16, a tile holds at
+// most 8192 requests), then final-digit counts above their length sums (u64:
+// 8192 lengths below 2^31 sum to less than 2^44, so up to eight rows can be
+// added as they are).
+constexpr uint32_t kSumBits = 47;
+__device__ __forceinline__ uint16_t* count_rows(const GArgs& a) {
+  return reinterpret_cast<uint16_t*>(a.block_hist);
+}
+__device__ __forceinline__ uint64_t* final_rows(const GArgs& a) { return a.block_histw; }
+// Per-tile class sums, [tile][P] (lo, hi); unused by this path otherwise.
+__device__ __forceinline__ uint64_t* class_parts(const GArgs& a) {
+  return reinterpret_cast<uint64_t*>(a.chunk_part);
+}
+static_assert(kTileRows * 256 * 16 <= kMaxChunks * kMaxBins * 4, "class sums fit chunk_part");
+
+// Ranges and first-digit counts of one tile; workgroup 0 resets the call's state.
+template <int R>
+__global__ __launch_bounds__(TT) void t_count(GArgs a) {
+  __shared__ uint32_t s_cnt[kMaxBins * kCountCopies];
+  __shared__ uint32_t s_red[4][TWV];
+  const int t = threadIdx.x;
+  const int lane = lane_id();
+  const int64_t first = (int64_t)blockIdx.x * (TT * R);
+  uint32_t pv[R];
+  int32_t lv[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const int64_t i = min(first + r * TT + t, a.n - 1);
+    pv[r] = a.priority[i];
+    lv[r] = a.length[i];
+  }
+  for (int i = t; i < kMaxBins * kCountCopies / 4; i += TT)
+    reinterpret_cast<uint4*>(s_cnt)[i] = make_uint4(0, 0, 0, 0);
+  if (blockIdx.x == 0) {
+    if (t == 0) {
+      a.flags[0] = 0;
+      a.plan->ok = 0;
+      a.plan->pay = 0;
+      a.hist_w[0] = 0;  // workgroups done with the final pass
+      a.msync->arrive = 0;
+      a.msync->release = 0;
+    }
+    for (int i = t; i < 2 * (1 + a.num_classes); i += TT) a.totals[i] = 0;
+  }
+  block_sync();
+  const uint32_t mask = (1u << a.d0) - 1;
+  uint32_t lmin = 0xffffffffu, lmax = 0, pmin = 0xffu, pmax = 0, bad = 0;
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const bool in = first + r * TT + t < a.n;
+    const bool ok = (lv[r] >= 0) & ((int)pv[r] < a.num_classes);
+    bad |= (in & !ok) ? 1u : 0u;
+    lmin = min(lmin, in ? (uint32_t)lv[r] : 0xffffffffu);
+    lmax = max(lmax, in ? (uint32_t)lv[r] : 0u);
+    pmin = min(pmin, in ? pv[r] : 0xffu);
+    pmax = max(pmax, in ? pv[r] : 0u);
+    atomicAdd(&s_cnt[((uint32_t)lv[r] & mask) * kCountCopies + (lane & (kCountCopies - 1))],
+              in ? 1u : 0u);
+  }
+  lmin = wave_min_u32(lmin);
+  lmax = wave_max_u32(lmax);
+  pmin = wave_min_u32(pmin);
+  pmax = wave_max_u32(pmax);
+  bad = wave_or_u32(bad);
+  if (lane == 0) {
+    const int w = wave_no();
+    s_red[0][w] = pmin;
+    s_red[1][w] = pmax | (bad << 31);
+    s_red[2][w] = lmin;
+    s_red[3][w] = lmax;
+  }
+  block_sync();
+  if (t < 4) {
+    uint32_t v = s_red[t][0];
+    for (int i = 1; i < TWV; ++i) {
+      const uint32_t x = s_red[t][i];
+      // (pmax: the error bit is above every rank)
+      v = (t & 1) ? (t == 1 ? (max(v & 0xffu, x & 0xffu) | ((v | x) & 0x80000000u)) : max(v, x))
+                  : min(v, x);
+    }
+    a.block_ranges[4 * (size_t)blockIdx.x + t] = v;
+  }
+  const uint4 c0 = reinterpret_cast<const uint4*>(s_cnt)[2 * t];
+  const uint4 c1 = reinterpret_cast<const uint4*>(s_cnt)[2 * t + 1];
+  static_assert(kCountCopies == 8, "two quads per digit");
+  count_rows(a)[(size_t)blockIdx.x * kMaxBins + t] =
+      (uint16_t)(c0.x + c0.y + c0.z + c0.w + c1.x + c1.y + c1.z + c1.w);
+}
+
+// Turns the waves' counters of a ranked tile into the positions of each
+// wave's first item of a digit in the tile's digit order; the thread's digit
+// starts at the returned position. Holds barriers.
+__device__ __forceinline__ uint32_t tile_positions(uint16_t (*cnt)[kMaxBins], uint32_t* scan32) {
+  const int t = threadIdx.x;
+  uint32_t c[TWV], tot = 0;
+#pragma unroll
+  for (int v = 0; v < TWV; ++v) {
+    c[v] = cnt[v][t];
+    tot += c[v];
+  }
+  uint32_t all;
+  const uint32_t ex = block_excl_scan_u32<TT>(tot, scan32, all);
+  uint32_t run = ex;
+#pragma unroll
+  for (int v = 0; v < TWV; ++v) {
+    cnt[v][t] = (uint16_t)run;
+    run += c[v];
+  }
+  return ex;
+}
+
+// Sums the tiles' count rows: thread t sums digits 4*(t % 256) .. + 3 over every
+// fourth row, rows before this tile's apart from the others (a row is the same
+// for a whole wave, so the split costs scalar branches only). Four partial
+// sums per digit; a barrier must follow.
+__device__ __forceinline__ void fold_rows(const GArgs& a, int me, int rows,
+                                          uint32_t (*s_before)[kMaxBins],
+                                          uint32_t (*s_after)[kMaxBins]) {
+  const int t = threadIdx.x;
+  const int w = wave_no();
+  uint32_t before[4] = {0, 0, 0, 0}, after[4] = {0, 0, 0, 0};
+  {
+    const ushort4* rowv = reinterpret_cast<const ushort4*>(count_rows(a)) + (t & 255);
+    constexpr int U = 16;  // rows in flight per thread
+    for (int g0 = w >> 2; g0 < rows; g0 += 4 * U) {
+      ushort4 x[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        x[u] = rowv[(size_t)min(g0 + 4 * u, rows - 1) * (kMaxBins / 4)];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int g = g0 + 4 * u;
+        if (g < me) {
+          before[0] += x[u].x;
+          before[1] += x[u].y;
+          before[2] += x[u].z;
+          before[3] += x[u].w;
+        } else if (g < rows) {
+          after[0] += x[u].x;
+          after[1] += x[u].y;
+          after[2] += x[u].z;
+          after[3] += x[u].w;
+        }
+      }
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    s_before[t >> 8][4 * (t & 255) + k] = before[k];
+    s_after[t >> 8][4 * (t & 255) + k] = after[k];
+  }
+}
+
+// The output position of this tile's first item of the thread's digit, from
+// the sums of fold_rows. Holds barriers.
+__device__ __forceinline__ uint32_t fold_offset(uint32_t (*s_before)[kMaxBins],
+                                                uint32_t (*s_after)[kMaxBins],
+                                                uint32_t* scan32) {
+  const int t = threadIdx.x;
+  uint32_t mine = 0, total = 0;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    mine += s_before[k][t];
+    total += s_after[k][t];
+  }
+  total += mine;
+  uint32_t sum;
+  return mine + block_excl_scan_u32<TT>(total, scan32, sum);
+}
+
+template <int R>
+struct TileFirstLds {
+  union {
+    uint64_t stage[TT * R];
+    struct {
+      uint32_t before[4][kMaxBins], after[4][kMaxBins];
+    } fold;
+  } u;
+  uint16_t cnt[TWV][kMaxBins];
+  uint32_t base[kMaxBins];
+  uint32_t red[4][TWV];
+  uint32_t scan32[TWV + 1];
+  Plan plan;
+};
+
+// Stages a ranked tile in digit order and writes it out.
+template <int R, typename Codec>
+__device__ __forceinline__ void tile_scatter(const GArgs& a, TileFirstLds<R>& sh, int64_t first,
+                                             int cv, const uint32_t (&pv)[R],
+                                             const uint32_t (&lv)[R], const uint32_t (&dg)[R],
+                                             const uint32_t (&rk)[R]) {
+  const int w = wave_no();
+  const int j0 = w * kWave * R + lane_id();
+  Codec kc;
+  kc.init(a, &sh.plan);
+#pragma unroll
+  for (int r = 0; r < R; ++r)
+    sh.u.stage[rk[r] + sh.cnt[w][dg[r]]] =
+        kc.make(pv[r], lv[r], (uint32_t)(first + j0 + r * kWave));
+  block_sync();
+  uint64_t* out = a.keys[0];
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const int j = j0 + r * kWave;
+    if (j < cv) {
+      const uint64_t e = sh.u.stage[j];
+      const uint32_t pos = sh.base[kc.lo(kc.key(e))] + (uint32_t)j;
+      if (pos < (uint64_t)a.n) out[pos] = e;  // (always, for consistent counts)
+    }
+  }
+}
+
+template <int R>
+__global__ __launch_bounds__(TT) void t_first(GArgs a) {
+  __shared__ TileFirstLds<R> sh;
+  const int t = threadIdx.x;
+  const int lane = lane_id();
+  const int w = wave_no();
+  const int me = (int)blockIdx.x;
+  const int rows = (int)gridDim.x;
+  const int64_t first = (int64_t)me * (TT * R);
+  const int cv = (int)min((int64_t)(TT * R), a.n - first);
+  const int j0 = w * kWave * R + lane;  // the lane's item in round 0
+  uint32_t pv[R], lv[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const int64_t i = first + min(j0 + r * kWave, cv - 1);
+    pv[r] = a.priority[i];
+    lv[r] = (uint32_t)a.length[i];
+  }
+  // ranges of all tiles (rows <= kTileRows <= TT)
+  uint4 rg = make_uint4(0xffu, 0u, 0xffffffffu, 0u);
+  if (t < rows) rg = reinterpret_cast<const uint4*>(a.block_ranges)[t];
+  fold_rows(a, me, rows, sh.u.fold.before, sh.u.fold.after);
+  {
+    const uint32_t pl = wave_min_u32(rg.x), ph = wave_max_u32(rg.y & 0xffu);
+    const uint32_t bad = wave_or_u32(rg.y & 0x80000000u);
+    const uint32_t ll = wave_min_u32(rg.z), lh = wave_max_u32(rg.w);
+    if (lane == 0) {
+      sh.red[0][w] = pl;
+      sh.red[1][w] = ph | bad;
+      sh.red[2][w] = ll;
+      sh.red[3][w] = lh;
+    }
+  }
+  clear_row(sh.cnt[w]);
+  block_sync();
+  if (t == 0) {
+    uint32_t pl = 0xffu, ph = 0, ll = 0xffffffffu, lh = 0, bad = 0;
+    for (int i = 0; i < (rows + kWave - 1) / kWave; ++i) {  // the waves that hold a tile's ranges
+      pl = min(pl, sh.red[0][i]);
+      ph = max(ph, sh.red[1][i] & 0xffu);
+      bad |= sh.red[1][i] & 0x80000000u;
+      ll = min(ll, sh.red[2][i]);
+      lh = max(lh, sh.red[3][i]);
+    }
+    sh.plan.cglb = 0;
+    sh.plan.ok = 0;
+    if (bad) {
+      if (me == 0) atomicOr(a.flags, kFlagRange);
+    } else {
+      make_plan(a, pl, ph, ll, lh, &sh.plan);
+      sh.plan.ok = 1;
+    }
+    if (me == 0 && !bad) *a.plan = sh.plan;
+  }
+  // (holds barriers: the plan is written)
+  const uint32_t mine = fold_offset(sh.u.fold.before, sh.u.fold.after, sh.scan32);
+  if (!sh.plan.ok) return;
+  const uint32_t M0 = (1u << a.d0) - 1;
+
+  uint32_t dg[R], rk[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    // items past the end take the last digit, after every real item of it
+    dg[r] = j0 + r * kWave < cv ? lv[r] & M0 : M0;
+    rk[r] = rank_round_c<10>(dg[r], sh.cnt[w]);
+  }
+  block_sync();
+  const uint32_t ex = tile_positions(sh.cnt, sh.scan32);
+  sh.base[t] = mine - ex;
+  block_sync();
+  if (sh.plan.W == 32) tile_scatter<R, KeyCodec32>(a, sh, first, cv, pv, lv, dg, rk);
+  else tile_scatter<R, KeyCodec64>(a, sh, first, cv, pv, lv, dg, rk);
+}
+
+// ---- middle passes (keys of more than two digits) --------------------------------
+
+struct TileCountLds {
+  uint32_t cnt[kMaxBins * kCountCopies];
+};
+
+// Digit counts of one tile of middle pass s.
+template <int R, typename Codec>
+__device__ void tile_count_mid(const GArgs& a, int s, TileCountLds& sh) {
+  const int t = threadIdx.x;
+  const uint32_t copy = (uint32_t)lane_id() & (kCountCopies - 1);
+  const uint32_t dshift = a.plan->shift[s];
+  Codec kc;
+  kc.init(a, a.plan);
+  const uint64_t* in = a.keys[(s - 1) & 1];
+  const int64_t first = (int64_t)blockIdx.x * (TT * R);
+  uint64_t e[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) e[r] = in[min(first + r * TT + t, a.n - 1)];
+  uint4* quads = reinterpret_cast<uint4*>(sh.cnt);
+  for (int i = t; i < kMaxBins * kCountCopies / 4; i += TT) quads[i] = make_uint4(0, 0, 0, 0);
+  block_sync();
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const uint32_t d = (kc.u2(kc.key(e[r])) >> dshift) & (kMaxBins - 1);
+    atomicAdd(&sh.cnt[d * kCountCopies + copy], first + r * TT + t < a.n ? 1u : 0u);
+  }
+  block_sync();
+  const uint4 c0 = quads[2 * t], c1 = quads[2 * t + 1];
+  count_rows(a)[(size_t)blockIdx.x * kMaxBins + t] =
+      (uint16_t)(c0.x + c0.y + c0.z + c0.w + c1.x + c1.y + c1.z + c1.w);
+}
+
+// Scatter of one tile of middle pass s.
+template <int R, typename Codec>
+__device__ void tile_scatter_mid(const GArgs& a, int s, TileFirstLds<R>& sh) {
+  const int t = threadIdx.x;
+  const int w = wave_no();
+  const int me = (int)blockIdx.x;
+  const uint32_t dshift = a.plan->shift[s];
+  constexpr uint32_t M = kMaxBins - 1;
+  Codec kc;
+  kc.init(a, a.plan);
+  const uint64_t* in = a.keys[(s - 1) & 1];
+  uint64_t* out = a.keys[s & 1];
+  const int64_t first = (int64_t)me * (TT * R);
+  const int cv = (int)min((int64_t)(TT * R), a.n - first);
+  const int j0 = w * kWave * R + lane_id();
+  uint64_t e[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) e[r] = in[first + min(j0 + r * kWave, cv - 1)];
+  fold_rows(a, me, (int)gridDim.x, sh.u.fold.before, sh.u.fold.after);
+  clear_row(sh.cnt[w]);
+  block_sync();
+  const uint32_t mine = fold_offset(sh.u.fold.before, sh.u.fold.after, sh.scan32);
+  uint32_t dg[R], rk[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) {  // items past the end take the last digit
+    dg[r] = j0 + r * kWave < cv ? (kc.u2(kc.key(e[r])) >> dshift) & M : M;
+    rk[r] = rank_round_c<10>(dg[r], sh.cnt[w]);
+  }
+  block_sync();
+  const uint32_t ex = tile_positions(sh.cnt, sh.scan32);
+  sh.base[t] = mine - ex;
+  block_sync();
+#pragma unroll
+  for (int r = 0; r < R; ++r) sh.u.stage[rk[r] + sh.cnt[w][dg[r]]] = e[r];
+  block_sync();
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const int j = j0 + r * kWave;
+    if (j < cv) {
+      const uint64_t x = sh.u.stage[j];
+      const uint32_t pos = sh.base[(kc.u2(kc.key(x)) >> dshift) & M] + (uint32_t)j;
+      if (pos < (uint64_t)a.n) out[pos] = x;  // (always, for consistent counts)
+    }
+  }
+}
+
+template <int R>
+union TileMidLds {
+  TileCountLds count;
+  TileFirstLds<R> scatter;
+};
+
+template <int R>
+__device__ void mid_count(const GArgs& a, int s, TileMidLds<R>& sh) {
+  if (a.plan->W == 32) tile_count_mid<R, KeyCodec32>(a, s, sh.count);
+  else tile_count_mid<R, KeyCodec64>(a, s, sh.count);
+}
+template <int R>
+__device__ void mid_scatter(const GArgs& a, int s, TileMidLds<R>& sh) {
+  if (a.plan->W == 32) tile_scatter_mid<R, KeyCodec32>(a, s, sh.scatter);
+  else tile_scatter_mid<R, KeyCodec64>(a, s, sh.scatter);
+}
+
+// The middle passes as separate launches (keys known to be wide, and a schedule
+// run again after the barrier below gave up).
+template <int R>
+__global__ __launch_bounds__(TT) void t_mid_count(GArgs a, int s) {
+  __shared__ TileMidLds<R> sh;
+  if (!a.plan->ok || s >= (int)a.plan->nscatter - 1) return;
+  mid_count<R>(a, s, sh);
+}
+template <int R>
+__global__ __launch_bounds__(TT) void t_mid_scatter(GArgs a, int s) {
+  __shared__ TileMidLds<R> sh;
+  if (!a.plan->ok || s >= (int)a.plan->nscatter - 1) return;
+  mid_scatter<R>(a, s, sh);
+}
+
+// Final-digit counts and length sums of one tile of the last pass's input.
+template <int R, typename Codec>
+__device__ void tile_histF(const GArgs& a, uint64_t* s_bin) {
+  const Plan* pl = a.plan;
+  const int t = threadIdx.x;
+  const int s = (int)pl->nscatter - 1;
+  const int nb = (int)pl->nbins[s];
+  const uint32_t dshift = pl->shift[s];
+  const uint32_t dmask = (1u << pl->nbits[s]) - 1;
+  Codec kc;
+  kc.init(a, pl);
+  // bins rounded up to a power of two, in as many copies as the slots hold (at
+  // most one per lane)
+  const uint32_t cb = min(6u, 13u - bit_width32((uint32_t)nb - 1));
+  const uint64_t* in = a.keys[(s - 1) & 1];
+  const int64_t first = (int64_t)blockIdx.x * (TT * R);
+  uint64_t e[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) e[r] = in[min(first + r * TT + t, a.n - 1)];
+  for (int i = t; i < (nb << cb); i += TT) s_bin[i] = 0;
+  block_sync();
+  const uint32_t copy = (uint32_t)lane_id() & ((1u << cb) - 1);
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const auto key = kc.key(e[r]);
+    const uint32_t d = (kc.u2(key) >> dshift) & dmask;
+    if (first + r * TT + t < a.n)
+      atomicAdd(reinterpret_cast<unsigned long long*>(&s_bin[(d << cb) + copy]),
+                (1ull << kSumBits) | kc.len(key));
+  }
+  block_sync();
+  // 2^cb threads per bin where there are threads enough, else one thread
+  // takes a bin's copies
+  uint64_t* row = final_rows(a) + (size_t)blockIdx.x * kMaxBins;
+  const int per = 8;  // copies added by one thread (cb >= 3: nb <= 1024)
+  for (int i = t; i < (nb << cb) / per; i += TT) {
+    uint64_t v = 0;
+#pragma unroll
+    for (int k = 0; k < per; ++k) v += s_bin[per * i + k];
+    for (uint32_t k = 1; k < (1u << cb) / per; k <<= 1) v += __shfl_xor(v, (int)k, kWave);
+    if ((i & ((1 << cb) / per - 1)) == 0) row[i >> (cb - 3)] = v;
+  }
+}
+
+// The final digit's counts, after any middle passes that were not launched
+// on their own (`mids`): those run here with bounded grid barriers between
+// their phases (at most kTileRows workgroups, all resident on an idle
+// device), as g_mid does for the big tiles. A launch of their own, which
+// returns at once for two-pass keys, would cost every call about 3 us.
+template <int R>
+__global__ __launch_bounds__(TT) void t_histF(GArgs a, int mids) {
+  __shared__ union {
+    TileMidLds<R> mid;
+    uint64_t bin[kFinalSlots];
+  } sh;
+  const Plan* pl = a.plan;
+  if (!pl->ok) return;
+  if (mids && pl->nscatter > 2) {
+    uint32_t gen = 0;
+    for (int s = 1; s < (int)pl->nscatter - 1; ++s) {
+      mid_count<R>(a, s, sh.mid);
+      if (!grid_barrier(a, ++gen)) return;
+      mid_scatter<R>(a, s, sh.mid);
+      if (!grid_barrier(a, ++gen)) return;
+    }
+  }
+  if (pl->W == 32) tile_histF<R, KeyCodec32>(a, sh.bin);
+  else tile_histF<R, KeyCodec64>(a, sh.bin);
+}
+
+template <int R>
+struct TileFinalLds {
+  union {
+    uint64_t stage[TT * R];
+    struct {
+      uint64_t bw[kMaxBins], tw[kMaxBins];
+      uint32_t bc[kMaxBins], tc[kMaxBins];
+    } fold;
+  } u;
+  uint16_t cnt[TWV][kMaxBins];
+  uint64_t wb[kMaxBins];     // wait base of the tile's run of a digit
+  uint32_t base[kMaxBins];   // output position of a digit's run minus its tile position
+  uint32_t start[kMaxBins];  // the run's tile position
+  uint64_t clo[256], chi[256];
+  uint64_t scan64[TWV + 1];
+  uint32_t scan32[TWV + 1];
+  uint32_t last;
+};
+
+template <int R, typename Codec>
+__device__ void tile_final(const GArgs& a, TileFinalLds<R>& sh) {
+  const Plan* pl = a.plan;
+  const int t = threadIdx.x;
+  const int lane = lane_id();
+  const int w = wave_no();
+  const int me = (int)blockIdx.x;
+  const int rows = (int)gridDim.x;
+  const int s = (int)pl->nscatter - 1;
+  const int nb = (int)pl->nbins[s];
+  const uint32_t dshift = pl->shift[s];
+  const uint32_t dmask = (1u << pl->nbits[s]) - 1;
+  const uint32_t P = pl->P;
+  const bool small = pl->small != 0;
+  Codec kc;
+  kc.init(a, pl);
+  const int64_t first = (int64_t)me * (TT * R);
+  const int cv = (int)min((int64_t)(TT * R), a.n - first);
+  const int j0 = w * kWave * R + lane;
+  const uint64_t* in = a.keys[(s - 1) & 1];
+  uint64_t e[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) e[r] = in[first + min(j0 + r * kWave, cv - 1)];
+
+  // counts and length sums of the digits: this tile's offsets and the totals.
+  // 2^rb >= nb threads (whole waves) take a row, so 1024 >> rb rows are read
+  // at a time.
+  const uint32_t fb = bit_width32((uint32_t)nb - 1);
+  const uint32_t rb = max(fb, 6u);
+  sh.u.fold.bw[t] = 0;
+  sh.u.fold.tw[t] = 0;
+  sh.u.fold.bc[t] = 0;
+  sh.u.fold.tc[t] = 0;
+  for (uint32_t c = t; c < P; c += TT) {
+    sh.clo[c] = 0;
+    sh.chi[c] = 0;
+  }
+  clear_row(sh.cnt[w]);
+  block_sync();
+  {
+    const int d = t & ((1 << rb) - 1);
+    const int step = TT >> rb;
+    uint64_t bw = 0, aw = 0;
+    uint32_t bc = 0, ac = 0;
+    constexpr int U = 8;
+    constexpr uint64_t kSumMask = (1ull << kSumBits) - 1;
+    const uint64_t* col = final_rows(a) + min(d, nb - 1);
+    for (int g0 = __builtin_amdgcn_readfirstlane(t >> rb); g0 < rows; g0 += step * U) {
+      uint64_t x[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) x[u] = col[(size_t)min(g0 + step * u, rows - 1) * kMaxBins];
+      uint64_t b = 0, c = 0;
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int g = g0 + step * u;
+        if (g < me) b += x[u];
+        else if (g < rows) c += x[u];
+      }
+      bc += (uint32_t)(b >> kSumBits);
+      bw += b & kSumMask;
+      ac += (uint32_t)(c >> kSumBits);
+      aw += c & kSumMask;
+    }
+    if (d < nb) {
+      if (ac + bc) {
+        atomicAdd(&sh.u.fold.tc[d], ac + bc);
+        atomicAdd(reinterpret_cast<unsigned long long*>(&sh.u.fold.tw[d]), aw + bw);
+      }
+      if (bc) {
+        atomicAdd(&sh.u.fold.bc[d], bc);
+        atomicAdd(reinterpret_cast<unsigned long long*>(&sh.u.fold.bw[d]), bw);
+      }
+    }
+  }
+  block_sync();
+  uint32_t pos0 = sh.u.fold.bc[t];
+  uint64_t wait0 = sh.u.fold.bw[t];
+  {
+    uint32_t all32;
+    uint64_t all64;
+    const uint32_t tc = sh.u.fold.tc[t];
+    const uint64_t tw = sh.u.fold.tw[t];
+    pos0 += block_excl_scan_u32<TT>(tc, sh.scan32, all32);
+    wait0 += block_excl_scan_u64<TT>(tw, sh.scan64, all64);
+  }
+
+  uint32_t dg[R], rk[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r)  // items past the end take the last digit
+    dg[r] = j0 + r * kWave < cv ? (kc.u2(kc.key(e[r])) >> dshift) & dmask : dmask;
+  if (fb <= 6) {
+#pragma unroll
+    for (int r = 0; r < R; ++r) rk[r] = rank_round_c<6>(dg[r], sh.cnt[w]);
+  } else if (fb <= 8) {
+#pragma unroll
+    for (int r = 0; r < R; ++r) rk[r] = rank_round_c<8>(dg[r], sh.cnt[w]);
+  } else {
+#pragma unroll
+    for (int r = 0; r < R; ++r) rk[r] = rank_round_c<10>(dg[r], sh.cnt[w]);
+  }
+  block_sync();
+  const uint32_t ex = tile_positions(sh.cnt, sh.scan32);
+  sh.base[t] = pos0 - ex;
+  sh.start[t] = ex;
+  sh.wb[t] = wait0;
+  block_sync();
+#pragma unroll
+  for (int r = 0; r < R; ++r) sh.u.stage[rk[r] + sh.cnt[w][dg[r]]] = e[r];
+  block_sync();
+
+  // lengths in the tile's digit order, scanned; the first item of a run turns
+  // its digit's wait base into the base of the whole run
+  uint64_t lp[R];
+  uint64_t run = 0;
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const int j = j0 + r * kWave;
+    e[r] = sh.u.stage[j];
+    const uint32_t l = j < cv ? kc.len(kc.key(e[r])) : 0u;
+    const uint64_t inc = small ? (uint64_t)wave_incl_scan_u32(l) : wave_incl_scan_len(l);
+    lp[r] = run + inc - l;
+    run += last_lane_u64(inc);
+  }
+  if (lane == 0) sh.scan64[w] = run;
+  block_sync();
+  uint64_t wave0 = 0;
+  for (int v = 0; v < w; ++v) wave0 += sh.scan64[v];  // (w is uniform)
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const int j = j0 + r * kWave;
+    lp[r] += wave0;
+    dg[r] = j < cv ? (kc.u2(kc.key(e[r])) >> dshift) & dmask : dmask;
+    if (j < cv && (uint32_t)j == sh.start[dg[r]]) sh.wb[dg[r]] -= lp[r];
+  }
+  block_sync();
+  // order and waits; the tile is class-major, so a lane's classes do not
+  // decrease over its rounds. A lane sums at most 8 waits below 2^51 (the
+  // queue has at most 2^20 requests).
+  uint32_t cur = 0xffffffffu;
+  uint64_t acc = 0;
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const int j = j0 + r * kWave;
+    if (j < cv) {
+      const uint32_t pos = sh.base[dg[r]] + (uint32_t)j;
+      const uint64_t wt = sh.wb[dg[r]] + lp[r];
+      if (pos < (uint64_t)a.n) {  // (always, for consistent counts)
+        a.order[pos] = (int32_t)kc.id(e[r]);
+        a.wait[pos] = (int64_t)wt;
+      }
+      const uint32_t c = kc.pp(kc.key(e[r]));
+      if (c != cur) {
+        if (cur != 0xffffffffu) {
+          const U128 v = {acc, 0};
+          atomic_add128(&sh.clo[cur], &sh.chi[cur], v);
+        }
+        cur = c;
+        acc = 0;
+      }
+      acc += wt;
+    }
+  }
+  // lanes that end in one class (nearly all waves) add up first
+  const uint32_t c0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)cur);
+  if (__builtin_amdgcn_ballot_w64(cur != c0) == 0) {
+    if (c0 != 0xffffffffu) {
+      const uint64_t sum = last_lane_u64(wave_incl_scan_u64(acc));  // below 2^60
+      const U128 v = {sum, 0};
+      if (lane == 0) atomic_add128(&sh.clo[c0], &sh.chi[c0], v);
+    }
+  } else if (cur != 0xffffffffu) {
+    const U128 v = {acc, 0};
+    atomic_add128(&sh.clo[cur], &sh.chi[cur], v);
+  }
+  block_sync();
+
+  // Class totals: every tile publishes its sums, the last workgroup to finish
+  // adds them up (atomics of all tiles on the totals' few lines would queue at
+  // about 11 ns each). The sums go through agent-scope stores, complete
+  // before the counter is advanced, and are read the same way, so no cache
+  // has to be written back for them.
+  uint64_t* part = class_parts(a);
+  for (uint32_t c = t; c < P; c += TT) {
+    uint64_t* o = part + 2 * ((size_t)me * P + c);
+    __hip_atomic_store(o, sh.clo[c], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(o + 1, sh.chi[c], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): the stores above are complete
+  block_sync();
+  if (t == 0)
+    sh.last = atomicAdd(reinterpret_cast<unsigned long long*>(a.hist_w), 1ull) ==
+              (unsigned long long)(rows - 1);
+  for (uint32_t c = t; c < P; c += TT) {
+    sh.clo[c] = 0;
+    sh.chi[c] = 0;
+  }
+  block_sync();
+  if (!sh.last) return;
+  for (uint32_t i = t; i < (uint32_t)rows * P; i += TT) {
+    const U128 v = {load_agent(part + 2 * (size_t)i), load_agent(part + 2 * (size_t)i + 1)};
+    const uint32_t c = i % P;
+    if (v.lo | v.hi) atomic_add128(&sh.clo[c], &sh.chi[c], v);
+  }
+  block_sync();
+  for (uint32_t c = t; c < P; c += TT) {
+    uint64_t* o = a.totals + 2 * (1 + (size_t)pl->pmin + c);
+    o[0] = sh.clo[c];
+    o[1] = sh.chi[c];
+  }
+  if (t == 0) {
+    U128 sum = {0, 0};
+    for (uint32_t c = 0; c < P; ++c) {
+      const U128 v = {sh.clo[c], sh.chi[c]};
+      add128(sum, v);
+    }
+    a.totals[0] = sum.lo;
+    a.totals[1] = sum.hi;
+  }
+}
+
+template <int R>
+__global__ __launch_bounds__(TT) void t_final(GArgs a) {
+  __shared__ TileFinalLds<R> sh;
+  if (!a.plan->ok) return;
+  if (a.plan->W == 32) tile_final<R, KeyCodec32>(a, sh);
+  else tile_final<R, KeyCodec64>(a, sh);
+}
+
+template <int R>
+hipError_t launch_tiles(const GArgs& a, hipStream_t st, const StageEvents* ev) {
+  const dim3 g((unsigned)((a.n + TT * R - 1) / (TT * R)));
+  mark_stage(ev, 0, false, st);
+  hipLaunchKernelGGL(t_count<R>, g, dim3(TT), 0, st, a);
+  mark_stage(ev, 0, true, st);
+  mark_stage(ev, 1, false, st);
+  hipLaunchKernelGGL(t_first<R>, g, dim3(TT), 0, st, a);
+  mark_stage(ev, 1, true, st);
+  mark_stage(ev, 6, false, st);
+  if (a.split_mid) {
+    for (int s = 1; s <= max_mid_passes(a.d0); ++s) {
+      hipLaunchKernelGGL(t_mid_count<R>, g, dim3(TT), 0, st, a, s);
+      hipLaunchKernelGGL(t_mid_scatter<R>, g, dim3(TT), 0, st, a, s);
+    }
+  }
+  hipLaunchKernelGGL(t_histF<R>, g, dim3(TT), 0, st, a, a.split_mid ? 0 : 1);
+  mark_stage(ev, 6, true, st);
+  mark_stage(ev, 2, false, st);
+  hipLaunchKernelGGL(t_final<R>, g, dim3(TT), 0, st, a);
+  mark_stage(ev, 2, true, st);
+  return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_tile_schedule(const GArgs& a, hipStream_t st, const StageEvents* ev) {
+  // Small tiles make more workgroups and shorter chains in each, but every
+  // workgroup reads every tile's count rows: 64 tiles are best up to 2^18
+  // requests (262,144: 36.8 us in 64 tiles, 37.9 in 128, 44.7 in 256), 128
+  // above (524,288: 45.0 us in 64, 42.8 in 128, 48.0 in 256).
+  if (a.n <= 64ll * TT) return launch_tiles<1>(a, st, ev);
+  if (a.n <= 64ll * TT * 2) return launch_tiles<2>(a, st, ev);
+  if (a.n <= (int64_t)kTileRows * TT * 4) return launch_tiles<4>(a, st, ev);
+  return launch_tiles<8>(a, st, ev);
+}
+
+}  // namespace semsched
