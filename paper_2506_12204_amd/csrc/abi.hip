@@ -587,8 +587,9 @@ int check_batched_args(const uint8_t* p, const int32_t* l, const int64_t* offset
 // lists, then the segmented sort's arrays for up to `long_cap` requests in
 // queues longer than kSegLargeCap.
 struct BLayout {
-  size_t ctl = 64, grab = 0, lists = 0, keys0 = 0, keys1 = 0, ids0 = 0, ids1 = 0, hist = 0, tsum = 0,
-         lbase = 0, tstart = 0, istart = 0, qtot = 0, tdesc = 0, imap = 0, total = 0;
+  size_t ctl = 64, grab = 0, lists = 0, keys0 = 0, keys1 = 0, lbase = 0, tstart = 0, istart = 0,
+         imap = 0, tdesc = 0, plan = 0, lranges = 0, lcount = 0, hist = 0, lfinal = 0, lwait = 0,
+         total = 0;
   uint32_t max_tiles = 0;
 };
 
@@ -608,18 +609,20 @@ BLayout batched_layout(int64_t S, uint64_t long_cap) {
   if (long_cap > 0) {
     const uint64_t queues = std::min<uint64_t>((uint64_t)S, long_cap / (kSegLargeCap + 1));
     L.max_tiles = long_max_tiles(long_cap, S);
+    const size_t rows = (size_t)kMaxBins * (size_t)L.max_tiles;
     L.keys0 = take(8 * long_cap);
     L.keys1 = take(8 * long_cap);
-    L.ids0 = take(4 * long_cap);
-    L.ids1 = take(4 * long_cap);
-    L.hist = take(4 * ((size_t)1 << kLongDigitBits) * (size_t)L.max_tiles);
-    L.tsum = take(8 * (size_t)L.max_tiles);
     L.lbase = take(8 * (size_t)(queues + 1));
     L.tstart = take(4 * (size_t)(queues + 1));
     L.istart = take(4 * (size_t)(queues + 1));
-    L.qtot = take(4 * (size_t)kLongColDigits * (size_t)long_items_max(long_cap, (int64_t)queues));
-    L.tdesc = take(sizeof(LongTileDesc) * (size_t)L.max_tiles);
     L.imap = take(4 * (size_t)long_items_max(long_cap, (int64_t)queues));
+    L.tdesc = take(sizeof(LongTileDesc) * (size_t)L.max_tiles);
+    L.plan = take(sizeof(Plan));
+    L.lranges = take(16 * (size_t)L.max_tiles);
+    L.lcount = take(2 * rows);
+    L.hist = take(4 * rows);
+    L.lfinal = take(8 * rows);
+    L.lwait = take(8 * rows);
   }
   L.total = off;
   return L;
@@ -629,7 +632,7 @@ BLayout batched_layout(int64_t S, uint64_t long_cap) {
 // the fixed part does).
 uint64_t long_capacity(int64_t S, size_t ws_bytes) {
   if (batched_layout(S, 1).total > ws_bytes) return 0;
-  uint64_t lo = 1, hi = ws_bytes / 24 + 1;  // more than 24 bytes per request
+  uint64_t lo = 1, hi = ws_bytes / 16 + 1;  // more than 16 bytes per request
   while (hi - lo > 1) {
     const uint64_t mid = lo + (hi - lo) / 2;
     if (batched_layout(S, mid).total <= ws_bytes) lo = mid;
@@ -669,16 +672,17 @@ int enqueue_batched(const uint8_t* p, const int32_t* l, const int64_t* offsets,
   if (cap > 0) {
     a.keys[0] = reinterpret_cast<uint64_t*>(base + L.keys0);
     a.keys[1] = reinterpret_cast<uint64_t*>(base + L.keys1);
-    a.ids[0] = reinterpret_cast<uint32_t*>(base + L.ids0);
-    a.ids[1] = reinterpret_cast<uint32_t*>(base + L.ids1);
-    a.hist = reinterpret_cast<uint32_t*>(base + L.hist);
-    a.tsum = reinterpret_cast<uint64_t*>(base + L.tsum);
     a.lbase = reinterpret_cast<uint64_t*>(base + L.lbase);
     a.tstart = reinterpret_cast<uint32_t*>(base + L.tstart);
     a.istart = reinterpret_cast<uint32_t*>(base + L.istart);
-    a.qtot = reinterpret_cast<uint32_t*>(base + L.qtot);
-    a.tdesc = reinterpret_cast<LongTileDesc*>(base + L.tdesc);
     a.imap = reinterpret_cast<uint32_t*>(base + L.imap);
+    a.tdesc = reinterpret_cast<LongTileDesc*>(base + L.tdesc);
+    a.plan = reinterpret_cast<Plan*>(base + L.plan);
+    a.lranges = reinterpret_cast<uint32_t*>(base + L.lranges);
+    a.lcount = reinterpret_cast<uint16_t*>(base + L.lcount);
+    a.hist = reinterpret_cast<uint32_t*>(base + L.hist);
+    a.lfinal = reinterpret_cast<uint64_t*>(base + L.lfinal);
+    a.lwait = reinterpret_cast<uint64_t*>(base + L.lwait);
   }
   return launch_batched(a, st) == hipSuccess ? SEM_OK : SEM_EDEVICE;
 }

@@ -15,8 +15,8 @@
 //   b_wide    queues of 4097 .. 16384 requests, plus every shorter queue whose
 //             key does not fit a 32-bit element (the two kernels above hand
 //             those on), one 1024-thread workgroup each on 64-bit elements
-//   b_long    queues of more than 16384 requests: one segmented LSD radix
-//             sort over all of them, in a cooperative launch
+//   l_*       queues of more than 16384 requests: one segmented LSD radix
+//             sort over all of them (long_sort.hip)
 // The medium and wide work lists are split into kSubLists segments, each
 // with an entry counter and a grab counter in a line of its own: the
 // planner files a chunk's queues into the segment of the chunk's index
@@ -37,8 +37,6 @@
 // sorted queue gives the waits, the sorted order is class-major, so per-lane
 // runs of one class give the class totals. 5 bytes are read and 12 written
 // per request: the queue never leaves LDS.
-#include <hip/hip_cooperative_groups.h>
-
 #include <type_traits>
 
 #include "block_common.h"
@@ -47,8 +45,6 @@
 namespace semsched {
 
 namespace {
-
-namespace cg = cooperative_groups;
 
 __device__ __forceinline__ int wave_index() {
   return __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
@@ -672,6 +668,7 @@ __global__ __launch_bounds__(kPlanThreads, 8) void b_plan(BArgs a, int chunk) {
 // 20 and 8-bit ones 16; keys of 15 .. 20 bits take three passes (21 bits, one
 // more than two 10-bit passes).
 using MediumLds = GroupLds<4, 16, 7, uint32_t>;
+constexpr int kMediumThreads = 256;
 
 // Queues of up to 16384 requests with any key: one 1024-thread workgroup each,
 // 64-bit elements. Also the single-queue call for n <= 16384.
@@ -712,10 +709,54 @@ __device__ void block_list_loop(const BArgs& a, int L, GroupLds<NW, R, D, ET>& s
   }
 }
 
+// Where the long queues' elements, tiles and scan items start (one workgroup:
+// the first of b_medium, which saves a launch; the long list is complete since
+// the planner).
+template <typename Lds>
+__device__ __forceinline__ void long_layout(const BArgs& a, Lds& sh) {
+  constexpr int NT = kMediumThreads;
+  const uint32_t K = a.ctl->count[kListLong];
+  if (K == 0 || a.ctl->long_elems > a.long_cap) {  // (uniform)
+    if (K != 0 && threadIdx.x == 0) atomicOr(a.flags, kFlagInval);  // workspace too small
+    return;
+  }
+  uint64_t elems = 0;
+  uint32_t tiles = 0, items = 0;
+  for (uint32_t k0 = 0; k0 < K; k0 += NT) {
+    const uint32_t k = k0 + threadIdx.x;
+    uint64_t m = 0;
+    if (k < K) {
+      const int64_t s = a.lists[list_base(a, kListLong, 0) + k];
+      m = (uint64_t)(a.offsets[s + 1] - a.offsets[s]);
+    }
+    const uint32_t mt = (uint32_t)((m + kLongTile - 1) / kLongTile);
+    const uint32_t mi = k < K ? (mt <= kLongRowsFew ? 1u : (uint32_t)kLongScanParts) : 0u;
+    uint64_t all_m;
+    uint32_t all_t, all_i;
+    const uint64_t em = block_excl_scan_u64<NT>(m, sh.wtot, all_m);
+    const uint32_t et = block_excl_scan_u32<NT>(mt, sh.scan, all_t);
+    const uint32_t ei = block_excl_scan_u32<NT>(mi, sh.scan, all_i);
+    if (k < K) {
+      a.lbase[k] = elems + em;
+      a.tstart[k] = tiles + et;
+      a.istart[k] = items + ei;
+    }
+    elems += all_m;
+    tiles += all_t;
+    items += all_i;
+  }
+  if (threadIdx.x == 0) {
+    a.tstart[K] = tiles;
+    a.ctl->long_tiles = tiles;
+    a.ctl->long_items = items;
+  }
+}
+
 // Five waves per SIMD (at most 96 registers): 6 % faster on 16,384 ragged
 // queues than the four that 113 registers allowed (six spill).
-__global__ __launch_bounds__(256, 5) void b_medium(BArgs a) {
+__global__ __launch_bounds__(kMediumThreads, 5) void b_medium(BArgs a) {
   __shared__ MediumLds sh;
+  if (blockIdx.x == 0 && a.long_cap > 0) long_layout(a, sh);
   block_list_loop<4, 16, 12, 7, uint32_t>(a, kListMedium, sh);
 }
 
@@ -731,660 +772,6 @@ __global__ __launch_bounds__(kWideThreads) void b_wide(BArgs a) {
   }
   block_list_loop<16, 16, 14, 8, uint64_t>(a, kListWide, sh);
 }
-
-// ---- segmented sort of the long queues --------------------------------------------
-// All queues of more than 16384 requests at once. They are cut into tiles of
-// kLongTile requests (a tile never spans two queues); the key of a request is
-// (priority - pmin) << wl | (length - lmin) with the ranges of all long
-// queues together, and the queue a tile belongs to is not part of the key:
-// digit offsets are scanned per queue over its own tiles. The key's live
-// bits are split evenly over passes of at most 10 bits; when the key and the
-// request's index in its queue fit 64 bits, the index rides below the key in
-// one element. Per pass: count every tile's digits, scan the counts per
-// queue and digit over the queue's tiles (plus the queue's digit bases),
-// scatter every tile stably. Then the waits: every tile's length sum, the exclusive scan of
-// those per queue, and every tile's own scan, with exact 128-bit class
-// totals. Grid-wide phases are separated by grid syncs; the launch is
-// cooperative, so every workgroup is resident.
-constexpr int kLT = 512;
-constexpr int kLW = kLT / kWave;
-constexpr int kLR = kLongTile / kLT;  // rounds per thread
-constexpr int kLB = 1 << kLongDigitBits;  // digits of a pass
-constexpr int kLO = kLB / kLT;            // digits per thread (consecutive)
-constexpr int kCD = kLongColDigits;       // digits of a column item
-constexpr int kCR = 512;                  // rows of a column item's block
-constexpr int kCS = kLT / kCD;            // row segments of a block (a thread each per digit)
-constexpr int kCSR = kCR / kCS;           // rows of a segment
-
-struct LongLds {
-  uint16_t cnt[kLW][kLB];
-  uint32_t hrow[kLB];
-  uint32_t dstart[kLB];  // start of each digit's run in the staged tile
-  union {
-    struct {  // the scatter's tile, staged in digit order
-      uint64_t key[kLongTile];
-      uint32_t id[kLongTile];
-    } st;
-    uint32_t acnt[kLW][kLB];  // the counting phase's per-wave counts
-    struct {  // a column item's block of rows (padded rows), its segments' sums
-      uint32_t v[kCR][kCD + 1];
-      uint32_t seg[kCS][kCD];
-    } col;
-  } u;
-  uint64_t clo[256], chi[256];
-  uint64_t part[kLW + 1];
-  uint32_t part32[kLW + 1];
-  uint32_t red[4][kLW];
-};
-
-// Waits for every outstanding global load and store of the wave (s_waitcnt
-// with vmcnt 0; expcnt and lgkmcnt at their maxima, so not waited for). At
-// the top of a tile loop whose next tile is loaded ahead: loads and stores
-// share that counter, and with the previous tile's stores still pending the
-// compiler's own wait at the first use of a loaded value waits for all of
-// them, the next tile's loads too; after this wait it places none.
-__device__ __forceinline__ void wait_vmem() { __builtin_amdgcn_s_waitcnt(0x0F70); }
-
-// Tile t of the long queues, found by a binary search over the first tiles
-// of the K queues (in long-list order). Its chain of dependent loads is paid
-// once per call: phase R stores the result in a.tdesc for the later phases.
-__device__ LongTileDesc long_tile(const BArgs& a, uint32_t t, uint32_t K) {
-  uint32_t k = 0, hi = K;  // tstart[k] <= t < tstart[hi]
-  while (hi - k > 1) {
-    const uint32_t mid = (k + hi) / 2;
-    if (a.tstart[mid] <= t) k = mid;
-    else hi = mid;
-  }
-  LongTileDesc x;
-  const uint32_t r0 = a.tstart[k];
-  x.s = a.lists[list_base(a, kListLong, 0) + k];
-  const int64_t base = a.offsets[x.s];
-  const int64_t m = a.offsets[x.s + 1] - base;
-  x.lo = (t - r0) * (uint32_t)kLongTile;  // (below m < 2^31)
-  x.cnt = (int32_t)min((int64_t)kLongTile, m - (int64_t)x.lo);
-  x.first = base + x.lo;
-  x.at = a.lbase[k] + x.lo;
-  x.item0 = a.istart[k];
-  x.rows = a.tstart[k + 1] - r0;
-  return x;
-}
-
-// Tile tt's descriptor, or an empty tile past the last one.
-__device__ __forceinline__ LongTileDesc tile_or_empty(const BArgs& a, uint32_t tt,
-                                                      uint32_t ntiles) {
-  LongTileDesc x = {};
-  if (tt < ntiles) x = a.tdesc[tt];
-  return x;
-}
-
-__global__ __launch_bounds__(kLT) void b_long(BArgs a) {
-  __shared__ LongLds sh;
-  cg::grid_group grid = cg::this_grid();
-  const int t = threadIdx.x;
-  const int lane = lane_id();
-  const int w = wave_index();
-  const uint32_t K = a.ctl->count[kListLong];
-  if (K == 0) return;  // (uniform: written by earlier kernels)
-  if (a.ctl->long_elems > a.long_cap) {
-    if (blockIdx.x == 0 && t == 0) atomicOr(a.flags, kFlagInval);  // workspace too small
-    return;
-  }
-  const int64_t C1 = 1 + a.num_classes;
-
-  // ---- phase 0: queue starts and first tiles (workgroup 0); zero the totals --------
-  if (blockIdx.x == 0) {
-    uint64_t carry_e = 0;
-    uint32_t carry_t = 0, carry_i = 0;
-    for (uint32_t k0 = 0; k0 < K; k0 += kLT) {
-      const uint32_t k = k0 + t;
-      uint64_t m = 0;
-      if (k < K) {
-        const int64_t s = a.lists[list_base(a, kListLong, 0) + k];
-        m = (uint64_t)(a.offsets[s + 1] - a.offsets[s]);
-      }
-      const uint32_t tiles = (uint32_t)((m + kLongTile - 1) / kLongTile);
-      const uint32_t items = k < K ? (tiles <= kLongRowsFew ? 1u : (uint32_t)(kLB / kCD)) : 0u;
-      uint64_t tot_e;
-      uint32_t tot_t, tot_i;
-      const uint64_t ex_e = block_excl_scan_u64<kLT>(m, sh.part, tot_e);
-      const uint32_t ex_t = block_excl_scan_u32<kLT>(tiles, sh.part32, tot_t);
-      const uint32_t ex_i = block_excl_scan_u32<kLT>(items, sh.part32, tot_i);
-      if (k < K) {
-        a.lbase[k] = carry_e + ex_e;
-        a.tstart[k] = carry_t + ex_t;
-        a.istart[k] = carry_i + ex_i;
-      }
-      carry_e += tot_e;
-      carry_t += tot_t;
-      carry_i += tot_i;
-    }
-    if (t == 0) {
-      a.lbase[K] = carry_e;
-      a.tstart[K] = carry_t;
-      a.istart[K] = carry_i;
-      if (carry_t > a.max_tiles) atomicOr(a.flags, kFlagInval);  // (cannot happen)
-      a.ctl->ranges[0] = 0xffu;
-      a.ctl->ranges[1] = 0;
-      a.ctl->ranges[2] = 0xffffffffu;
-      a.ctl->ranges[3] = 0;
-      a.ctl->ranges[4] = 0;
-    }
-  }
-  for (int64_t i = (int64_t)blockIdx.x * kLT + t; i < (int64_t)K * 2 * C1;
-       i += (int64_t)gridDim.x * kLT) {
-    const int64_t s = a.lists[list_base(a, kListLong, 0) + i / (2 * C1)];
-    a.totals[2 * s * C1 + i % (2 * C1)] = 0;
-  }
-  grid.sync();
-  const uint32_t ntiles = a.tstart[K];
-  const uint32_t nitems = a.istart[K];
-
-  // ---- phase R: ranges and validation of all long queues --------------------------
-  // Reduced over the workgroup's tiles first, then one atomic per range word
-  // and workgroup, skipped when it would not change the word: atomics on one
-  // line serialise, and one per wave and tile queued thousands on it.
-  {
-    uint32_t lmin = 0xffffffffu, lmax = 0, pmin = 0xffu, pmax = 0, bad = 0, mmax = 0;
-    for (uint32_t tt = blockIdx.x; tt < ntiles; tt += gridDim.x) {
-      const LongTileDesc x = long_tile(a, tt, K);
-      if (t == 0) a.tdesc[tt] = x;
-      mmax = max(mmax, x.lo + (uint32_t)x.cnt);  // (uniform) the queue's size at its last tile
-      if (x.lo == 0) {  // (uniform) the queue's first tile: map its digit-offset items
-        const uint32_t nit = x.rows <= kLongRowsFew ? 1u : (uint32_t)(kLB / kCD);
-        for (uint32_t j = t; j < nit; j += kLT) a.imap[x.item0 + j] = tt;
-      }
-      uint32_t p[kLR];
-      int32_t l[kLR];
-#pragma unroll
-      for (int r = 0; r < kLR; ++r) {  // (every load issued before the first use)
-        const int i = r * kLT + t;
-        p[r] = 0;
-        l[r] = 0;
-        if (i < x.cnt) {
-          p[r] = a.priority[x.first + i];
-          l[r] = a.length[x.first + i];
-        }
-      }
-#pragma unroll
-      for (int r = 0; r < kLR; ++r) {
-        if (r * kLT + t < x.cnt) {
-          bad |= (l[r] < 0) | ((int)p[r] >= a.num_classes);
-          lmin = min(lmin, (uint32_t)l[r]);
-          lmax = max(lmax, (uint32_t)l[r]);
-          pmin = min(pmin, p[r]);
-          pmax = max(pmax, p[r]);
-        }
-      }
-    }
-    lmin = wave_min_u32(lmin);
-    lmax = wave_max_u32(lmax);
-    pmin = wave_min_u32(pmin);
-    pmax = wave_max_u32(pmax);
-    bad = wave_or_u32(bad);
-    if (lane == 0) {
-      if (bad) atomicOr(a.flags, kFlagRange);
-      sh.red[0][w] = pmin;
-      sh.red[1][w] = pmax;
-      sh.red[2][w] = lmin;
-      sh.red[3][w] = lmax;
-    }
-    block_sync();
-    if (t == 0) {
-      for (int v = 1; v < kLW; ++v) {
-        pmin = min(pmin, sh.red[0][v]);
-        pmax = max(pmax, sh.red[1][v]);
-        lmin = min(lmin, sh.red[2][v]);
-        lmax = max(lmax, sh.red[3][v]);
-      }
-      uint32_t* rg = a.ctl->ranges;
-      if (pmin < load_agent(rg + 0)) atomicMin(rg + 0, pmin);
-      if (pmax > load_agent(rg + 1)) atomicMax(rg + 1, pmax);
-      if (lmin < load_agent(rg + 2)) atomicMin(rg + 2, lmin);
-      if (lmax > load_agent(rg + 3)) atomicMax(rg + 3, lmax);
-      if (mmax > load_agent(rg + 4)) atomicMax(rg + 4, mmax);  // (mmax: the same in every thread)
-    }
-  }
-  grid.sync();
-  // Every workgroup decides the same: nothing writes the flags from here on
-  // (the earlier kernels and phases R and 0 are done), so no workgroup can
-  // leave while others wait at a later grid sync.
-  if (__hip_atomic_load(a.flags, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) return;
-  auto range = [&](int i) {
-    return __hip_atomic_load(&a.ctl->ranges[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  };
-  const uint32_t pmin = range(0), pmax = range(1);
-  const uint32_t lmin = range(2), lmax = range(3);
-  const uint32_t wl = bit_width32(lmax - lmin);
-  const uint32_t kb = wl + bit_width32(pmax - pmin);
-  const int npass = kb ? (int)((kb + kLongDigitBits - 1) / kLongDigitBits) : 1;
-  // the key's bits split evenly over the passes: longer runs per digit in
-  // the scatter than a full first digit and a short last one
-  const uint32_t dbits = (kb + npass - 1) / npass;
-  const uint32_t dmask = (1u << dbits) - 1;
-  const uint64_t lmask = wl ? ((1ull << wl) - 1) : 0;
-  // When the key and the request's index in its queue fit 64 bits together,
-  // the index rides in the element's low ib bits (8 bytes per element
-  // between the passes instead of a key and a separate id); else ib = 0.
-  const uint32_t idb = bit_width32(range(4) - 1);
-  const bool packed = kb + idb <= 64;
-  const uint32_t ib = packed ? idb : 0u;
-  const uint64_t idmask = (1ull << ib) - 1;
-
-  // element r of this thread in tile x: request x.lo + w*64*kLR + r*64 + lane
-  // (with_ids false: the ids are not read, for the counting phase)
-  auto load_elems = [&](const LongTileDesc& x, int q, uint64_t (&key)[kLR],
-                        uint32_t (&id)[kLR], bool with_ids) {
-#pragma unroll
-    for (int r = 0; r < kLR; ++r) {
-      const int i = w * kWave * kLR + r * kWave + lane;
-      key[r] = ~0ull;
-      id[r] = 0;
-      if (i < x.cnt) {
-        if (q == 0) {
-          const uint32_t p = a.priority[x.first + i];
-          const uint32_t l = (uint32_t)a.length[x.first + i];
-          id[r] = x.lo + (uint32_t)i;
-          key[r] = ((((uint64_t)(p - pmin) << wl) | (uint64_t)(l - lmin)) << ib) |
-                   (packed ? id[r] : 0u);
-        } else {
-          key[r] = a.keys[(q - 1) & 1][x.at + i];
-          if (with_ids && !packed) id[r] = a.ids[(q - 1) & 1][x.at + i];
-        }
-      }
-    }
-  };
-
-  for (int q = 0; q < npass; ++q) {
-    const uint32_t shift = ib + dbits * q;
-    // ---- phase A: digit counts of every tile ----------------------------------------
-    // (the workgroup's next tile is loaded while this one is counted)
-    {
-    LongTileDesc x = tile_or_empty(a, blockIdx.x, ntiles);
-    uint64_t key[kLR];
-    uint32_t id[kLR];
-    load_elems(x, q, key, id, false);
-    for (uint32_t tt = blockIdx.x; tt < ntiles; tt += gridDim.x) {
-      wait_vmem();
-      const LongTileDesc xn = tile_or_empty(a, tt + gridDim.x, ntiles);
-      uint64_t nkey[kLR];
-      uint32_t nid[kLR];
-      load_elems(xn, q, nkey, nid, false);
-      // (counts only: one LDS add per request into the wave's own table)
-      uint32_t* mine = sh.u.acnt[w];
-      for (int b = lane; b < kLB; b += kWave) mine[b] = 0;
-#pragma unroll
-      for (int r = 0; r < kLR; ++r) {
-        const int i = w * kWave * kLR + r * kWave + lane;
-        if (i < x.cnt) atomicAdd(&mine[(uint32_t)(key[r] >> shift) & dmask], 1u);
-      }
-      block_sync();
-#pragma unroll
-      for (int o = 0; o < kLO; ++o) {
-        const int d = kLO * t + o;
-        uint32_t c = 0;
-#pragma unroll
-        for (int v = 0; v < kLW; ++v) c += sh.u.acnt[v][d];
-        a.hist[(size_t)tt * kLB + d] = c;
-      }
-      block_sync();
-      x = xn;
-#pragma unroll
-      for (int r = 0; r < kLR; ++r) key[r] = nkey[r];
-    }
-    }
-    grid.sync();
-    // ---- phase B: per queue and digit, offsets over the queue's tiles ----------------
-    // A queue of few tiles is one work item: each thread runs down the
-    // columns of its kLO digits and the digit bases are added at once. A
-    // queue of many tiles is kLB / kCD items of kCD digits each, whose
-    // columns are scanned together down the queue's tiles; its digit totals
-    // go to qtot and the digit bases are added by the scatter (phase C).
-    for (uint32_t it = blockIdx.x; it < nitems; it += gridDim.x) {
-      const uint32_t r0 = a.imap[it];  // the queue's first tile
-      const LongTileDesc y = a.tdesc[r0];
-      const uint32_t r1 = r0 + y.rows;
-      if (y.rows <= kLongRowsFew) {
-        uint32_t tot[kLO], sum = 0;
-#pragma unroll
-        for (int o = 0; o < kLO; ++o) {
-          tot[o] = 0;
-          for (uint32_t row = r0; row < r1; ++row)
-            tot[o] += a.hist[(size_t)row * kLB + kLO * t + o];
-          sum += tot[o];
-        }
-        uint32_t total;
-        uint32_t run = block_excl_scan_u32<kLT>(sum, sh.part32, total);
-#pragma unroll
-        for (int o = 0; o < kLO; ++o) {
-          uint32_t r = run;
-          for (uint32_t row = r0; row < r1; ++row) {
-            uint32_t* h = a.hist + (size_t)row * kLB + kLO * t + o;
-            const uint32_t c = *h;
-            *h = r;
-            r += c;
-          }
-          run += tot[o];
-        }
-      } else {
-        // kCD digits from d0: blocks of kCR rows are loaded coalesced into
-        // LDS, each thread scans kCSR rows of one digit, a thread per digit
-        // scans the segments' sums (carrying the earlier blocks' totals), and
-        // the offsets go back coalesced
-        const uint32_t d0 = (it - y.item0) * kCD;
-        uint32_t carry = 0;  // (threads t < kCD: digit d0 + t)
-        for (uint32_t row0 = r0; row0 < r1; row0 += kCR) {
-          uint32_t* hb = a.hist + (size_t)row0 * kLB + d0;  // (uniform)
-          const uint32_t nr = min(r1 - row0, (uint32_t)kCR);
-          // the thread index through an empty asm: the offsets below are
-          // formed here, not hoisted out of every loop around this one (they
-          // would hold registers through the other phases)
-          int tv = t;
-          asm volatile("" : "+v"(tv));
-#pragma unroll
-          for (int j = 0; j < kCR * kCD / kLT; ++j) {
-            const int v = j * kLT + tv;
-            sh.u.col.v[v / kCD][v % kCD] =
-                (uint32_t)(v / kCD) < nr ? hb[(v / kCD) * kLB + v % kCD] : 0u;
-          }
-          block_sync();
-          {
-            const int dd = tv % kCD, sg = tv / kCD;
-            uint32_t run = 0;
-#pragma unroll
-            for (int k = 0; k < kCSR; ++k) {
-              const uint32_t c = sh.u.col.v[sg * kCSR + k][dd];
-              sh.u.col.v[sg * kCSR + k][dd] = run;
-              run += c;
-            }
-            sh.u.col.seg[sg][dd] = run;
-          }
-          block_sync();
-          if (t < kCD) {
-#pragma unroll 8
-            for (int g = 0; g < kCS; ++g) {
-              const uint32_t c = sh.u.col.seg[g][t];
-              sh.u.col.seg[g][t] = carry;
-              carry += c;
-            }
-          }
-          block_sync();
-#pragma unroll
-          for (int j = 0; j < kCR * kCD / kLT; ++j) {
-            const int v = j * kLT + tv;
-            if ((uint32_t)(v / kCD) < nr)
-              hb[(v / kCD) * kLB + v % kCD] =
-                  sh.u.col.v[v / kCD][v % kCD] + sh.u.col.seg[(v / kCD) / kCSR][v % kCD];
-          }
-          block_sync();
-        }
-        if (t < kCD) a.qtot[(size_t)it * kCD + t] = carry;
-      }
-    }
-    grid.sync();
-    // ---- phase C: stable scatter of every tile ----------------------------------------
-    // (the workgroup's next tile, its digit offsets and its queue's digit
-    // totals are loaded while this one is placed and written)
-    {
-    LongTileDesc x = tile_or_empty(a, blockIdx.x, ntiles);
-    uint64_t key[kLR];
-    uint32_t id[kLR], hv[kLO], qv[kLO];
-    auto load_offsets = [&](const LongTileDesc& y, uint32_t ty, uint32_t (&h)[kLO],
-                            uint32_t (&c)[kLO]) {
-#pragma unroll
-      for (int o = 0; o < kLO; ++o) {
-        h[o] = y.cnt > 0 ? a.hist[(size_t)ty * kLB + kLO * t + o] : 0u;
-        c[o] = y.rows > kLongRowsFew ? a.qtot[(size_t)y.item0 * kCD + kLO * t + o] : 0u;
-      }
-    };
-    load_elems(x, q, key, id, true);
-    load_offsets(x, blockIdx.x, hv, qv);
-    for (uint32_t tt = blockIdx.x; tt < ntiles; tt += gridDim.x) {
-      wait_vmem();
-      uint32_t dg[kLR], rk[kLR];
-      uint32_t dbase[kLO] = {};  // queues of many tiles: the digits' bases in the queue
-      if (x.rows > kLongRowsFew) {  // (uniform)
-        uint32_t sum = 0;
-#pragma unroll
-        for (int o = 0; o < kLO; ++o) sum += qv[o];
-        uint32_t total;
-        uint32_t run = block_excl_scan_u32<kLT>(sum, sh.part32, total);
-#pragma unroll
-        for (int o = 0; o < kLO; ++o) {
-          dbase[o] = run;
-          run += qv[o];
-        }
-      }
-#pragma unroll
-      for (int o = 0; o < kLO; ++o) sh.hrow[kLO * t + o] = hv[o] + dbase[o];
-      clear_counters<kLB>(sh.cnt[w]);
-#pragma unroll
-      for (int r = 0; r < kLR; ++r) {
-        dg[r] = (uint32_t)(key[r] >> shift) & dmask;
-        rk[r] = rank_round_c<kLongDigitBits>(dg[r], sh.cnt[w]);
-      }
-      const uint32_t tn = tt + gridDim.x;
-      const LongTileDesc xn = tile_or_empty(a, tn, ntiles);
-      uint64_t nkey[kLR];
-      uint32_t nid[kLR];
-      load_elems(xn, q, nkey, nid, true);
-      load_offsets(xn, tn, hv, qv);
-      block_sync();
-      // owners: the waves' offsets within each digit, then the digits'
-      // starts in the tile (elements past the end count in the last digit
-      // and rank after its real ones, so they shift no real position)
-      uint32_t tot[kLO], sum = 0;
-#pragma unroll
-      for (int o = 0; o < kLO; ++o) {
-        const int d = kLO * t + o;
-        uint32_t run = 0;
-#pragma unroll
-        for (int v = 0; v < kLW; ++v) {
-          const uint32_t c = sh.cnt[v][d];
-          sh.cnt[v][d] = (uint16_t)run;
-          run += c;
-        }
-        tot[o] = run;
-        sum += run;
-      }
-      {
-        uint32_t total;
-        uint32_t st = block_excl_scan_u32<kLT>(sum, sh.part32, total);  // (barriers)
-#pragma unroll
-        for (int o = 0; o < kLO; ++o) {
-          sh.dstart[kLO * t + o] = st;
-          st += tot[o];
-        }
-      }
-      block_sync();
-      // stage the tile in digit order, then write it out in runs per digit
-#pragma unroll
-      for (int r = 0; r < kLR; ++r) {
-        const int i = w * kWave * kLR + r * kWave + lane;
-        if (i < x.cnt) {
-          const uint32_t j = sh.dstart[dg[r]] + sh.cnt[w][dg[r]] + rk[r];
-          sh.u.st.key[j] = key[r];
-          if (!packed) sh.u.st.id[j] = id[r];
-        }
-      }
-      block_sync();
-      uint64_t* kout = a.keys[q & 1] + (x.at - x.lo);  // the queue's first element
-      uint32_t* iout = a.ids[q & 1] + (x.at - x.lo);
-      for (int j = t; j < x.cnt; j += kLT) {
-        const uint64_t k = sh.u.st.key[j];
-        const uint32_t d = (uint32_t)(k >> shift) & dmask;
-        const uint32_t at = sh.hrow[d] + (uint32_t)(j - (int)sh.dstart[d]);
-        kout[at] = k;
-        if (!packed) iout[at] = sh.u.st.id[j];
-      }
-      block_sync();
-      x = xn;
-#pragma unroll
-      for (int r = 0; r < kLR; ++r) {
-        key[r] = nkey[r];
-        id[r] = nid[r];
-      }
-    }
-    }
-    grid.sync();
-  }
-
-  // ---- waits and totals of the sorted queues ----------------------------------------
-  const uint64_t* skey = a.keys[(npass - 1) & 1];
-  const uint32_t* sid = a.ids[(npass - 1) & 1];
-  // phase D1: length sum of every tile
-  // (the workgroup's next tile is loaded while this one is summed)
-  {
-  auto load_keys = [&](const LongTileDesc& y, uint64_t (&v)[kLR]) {
-#pragma unroll
-    for (int r = 0; r < kLR; ++r) {
-      const int i = r * kLT + t;
-      v[r] = i < y.cnt ? skey[y.at + i] : 0;
-    }
-  };
-  LongTileDesc x = tile_or_empty(a, blockIdx.x, ntiles);
-  uint64_t v[kLR];
-  load_keys(x, v);
-  for (uint32_t tt = blockIdx.x; tt < ntiles; tt += gridDim.x) {
-    wait_vmem();
-    const LongTileDesc xn = tile_or_empty(a, tt + gridDim.x, ntiles);
-    uint64_t nv[kLR];
-    load_keys(xn, nv);
-    uint64_t s = 0;
-#pragma unroll
-    for (int r = 0; r < kLR; ++r) s += r * kLT + t < x.cnt ? ((v[r] >> ib) & lmask) + lmin : 0;
-    s = wave_sum_u64(s);
-    if (lane == 0) sh.part[w] = s;
-    block_sync();
-    if (t == 0) {
-      uint64_t sum = 0;
-      for (int u = 0; u < kLW; ++u) sum += sh.part[u];
-      a.tsum[tt] = sum;
-    }
-    block_sync();
-    x = xn;
-#pragma unroll
-    for (int r = 0; r < kLR; ++r) v[r] = nv[r];
-  }
-  }
-  grid.sync();
-  // phase D2: per queue, exclusive scan of its tiles' sums
-  for (uint32_t k = blockIdx.x; k < K; k += gridDim.x) {
-    const uint32_t r0 = a.tstart[k], r1 = a.tstart[k + 1];
-    uint64_t carry = 0;
-    for (uint32_t row0 = r0; row0 < r1; row0 += kLT) {
-      const uint32_t row = row0 + t;
-      const uint64_t v = row < r1 ? a.tsum[row] : 0ull;
-      uint64_t total;
-      const uint64_t ex = block_excl_scan_u64<kLT>(v, sh.part, total);
-      if (row < r1) a.tsum[row] = carry + ex;
-      carry += total;
-    }
-  }
-  grid.sync();
-  // phase D3: order, waits and class totals of every tile. The class sums
-  // of the workgroup's consecutive tiles of one queue add up in LDS and go
-  // to the queue's totals when the queue changes and at the end (one atomic
-  // per class and one for the total at each such flush).
-  const uint32_t P = pmax - pmin + 1;
-  int64_t cur_s = -1;  // (uniform) the queue whose sums the LDS totals hold
-  auto flush = [&]() {
-    block_sync();  // every lane's sums are in
-    uint64_t* tot = a.totals + 2 * cur_s * C1;
-    for (uint32_t c = t; c < P; c += kLT) {
-      const U128 v = {sh.clo[c], sh.chi[c]};
-      if (v.lo | v.hi) atomic_add128(tot + 2 * (1 + pmin + c), tot + 2 * (1 + pmin + c) + 1, v);
-    }
-    if (t == 0) {
-      U128 g = {0, 0};
-      for (uint32_t c = 0; c < P; ++c) add128(g, U128{sh.clo[c], sh.chi[c]});
-      if (g.lo | g.hi) atomic_add128(tot, tot + 1, g);
-    }
-    block_sync();  // the sums are read
-    for (uint32_t c = t; c < P; c += kLT) sh.clo[c] = sh.chi[c] = 0;
-  };
-  for (uint32_t c = t; c < P; c += kLT) sh.clo[c] = sh.chi[c] = 0;
-  // (the workgroup's next tile and its wait base are loaded while this one
-  // is written)
-  auto load_sorted = [&](const LongTileDesc& y, uint32_t ty, uint64_t (&key)[kLR],
-                         uint32_t (&id)[kLR], uint64_t& wbase) {
-    // (packed: the ids are taken from the keys where they are stored, so
-    // that no load waits for the one before it)
-#pragma unroll
-    for (int r = 0; r < kLR; ++r) {
-      const int i = w * kWave * kLR + r * kWave + lane;
-      key[r] = i < y.cnt ? skey[y.at + i] : 0ull;
-    }
-#pragma unroll
-    for (int r = 0; r < kLR; ++r) {
-      const int i = w * kWave * kLR + r * kWave + lane;
-      id[r] = !packed && i < y.cnt ? sid[y.at + i] : 0u;
-    }
-    wbase = y.cnt > 0 ? a.tsum[ty] : 0;
-  };
-  LongTileDesc x = tile_or_empty(a, blockIdx.x, ntiles);
-  uint64_t key[kLR], wbase;
-  uint32_t id[kLR];
-  load_sorted(x, blockIdx.x, key, id, wbase);
-  for (uint32_t tt = blockIdx.x; tt < ntiles; tt += gridDim.x) {
-    wait_vmem();
-    if (x.s != cur_s) {  // (uniform)
-      if (cur_s >= 0) flush();
-      cur_s = x.s;
-    }
-    block_sync();  // the totals are cleared
-    uint32_t len[kLR];
-    uint64_t mine = 0;
-#pragma unroll
-    for (int r = 0; r < kLR; ++r) {
-      const int i = w * kWave * kLR + r * kWave + lane;
-      len[r] = i < x.cnt ? (uint32_t)(((key[r] >> ib) & lmask) + lmin) : 0u;
-      mine += len[r];
-    }
-    const uint32_t tn = tt + gridDim.x;
-    const LongTileDesc xn = tile_or_empty(a, tn, ntiles);
-    uint64_t nkey[kLR], nwbase;
-    uint32_t nid[kLR];
-    load_sorted(xn, tn, nkey, nid, nwbase);
-    const uint64_t wsum = wave_sum_u64(mine);
-    if (lane == 0) sh.part[w] = wsum;
-    block_sync();
-    uint64_t run = wbase;
-    for (int v = 0; v < w; ++v) run += sh.part[v];  // (w is uniform)
-    int cur = -1;
-    U128 acc = {0, 0};
-    const int64_t out0 = x.first;
-#pragma unroll
-    for (int r = 0; r < kLR; ++r) {
-      const int i = w * kWave * kLR + r * kWave + lane;
-      const uint64_t incl = wave_incl_scan_len(len[r]);
-      const uint64_t wt = run + incl - len[r];
-      run += last_lane_u64(incl);
-      if (i < x.cnt) {
-        a.order[out0 + i] = (int32_t)(packed ? (uint32_t)(key[r] & idmask) : id[r]);
-        a.wait[out0 + i] = (int64_t)wt;
-        const int cls = (int)(key[r] >> (ib + wl));
-        if (cls != cur) {
-          if (cur >= 0) atomic_add128(&sh.clo[cur], &sh.chi[cur], acc);
-          cur = cls;
-          acc = U128{0, 0};
-        }
-        add128(acc, wt);
-      }
-    }
-    if (cur >= 0) atomic_add128(&sh.clo[cur], &sh.chi[cur], acc);
-    block_sync();  // (sh.part is read; the next tile writes it)
-    x = xn;
-    wbase = nwbase;
-#pragma unroll
-    for (int r = 0; r < kLR; ++r) {
-      key[r] = nkey[r];
-      id[r] = nid[r];
-    }
-  }
-  if (cur_s >= 0) flush();  // (uniform)
-}
-
-// ---- host side -------------------------------------------------------------------
 
 template <typename K>
 int resident(K kernel, int threads) {
@@ -1422,7 +809,6 @@ hipError_t launch_batched(const BArgs& a, hipStream_t st) {
   static const int r_plan = resident(b_plan, kPlanThreads);
   static const int r_medium = resident(b_medium, 256);
   static const int r_wide = resident(b_wide, kWideThreads);
-  static const int r_long = resident(b_long, kLT);
   const int64_t S = a.num_segments;
   // chunks of about S / (resident planner workgroups) queues, at most
   // kPlanChunk; a grid of one workgroup per chunk, or else a multiple of
@@ -1433,13 +819,8 @@ hipError_t launch_batched(const BArgs& a, hipStream_t st) {
                      st, a, (int)chunk);
   hipLaunchKernelGGL(b_medium, dim3(grid_for(r_medium, S)), dim3(256), 0, st, a);
   hipLaunchKernelGGL(b_wide, dim3(grid_for(r_wide, S)), dim3(kWideThreads), 0, st, a);
-  if (hipGetLastError() != hipSuccess) return hipErrorLaunchFailure;
   if (a.long_cap > 0) {
-    const int g = grid_for(r_long, (int64_t)long_max_tiles(a.long_cap, S));
-    BArgs copy = a;
-    void* args[] = {&copy};
-    const hipError_t e = hipLaunchCooperativeKernel(reinterpret_cast<const void*>(b_long),
-                                                    dim3(g), dim3(kLT), args, 0, st);
+    const hipError_t e = launch_long_queues(a, st);
     if (e != hipSuccess) return e;
   }
   return hipGetLastError();

@@ -151,7 +151,8 @@ __device__ void write_plan(const GArgs& a, int G) {
     pl->ok = 0;
     return;
   }
-  make_plan(a, gpmin, gpmax, glmin, glmax, pl);
+  make_plan((uint32_t)a.d0, (uint32_t)(a.n - 1), a.force_wide != 0, a.chunked != 0, gpmin,
+            gpmax, glmin, glmax, pl);
   // carried ranks: above the final digit's bits, if they fit the u32 element
   if (pl->compact && a.payload) {
     const uint32_t at = kChunkBits + pl->nbits[1];
@@ -512,7 +513,7 @@ __device__ void scatter_block(const GArgs& a, int s, int g, Split sp, ScatterSha
   const uint32_t dshift = pl->shift[s];
   const uint32_t dmask = (1u << nbits) - 1;
   KeyCodec kc;
-  kc.init(a, pl);
+  kc.init(a.d0, pl);
   const bool packed = pl->packed != 0;
   const uint64_t* keys_in = FIRST ? nullptr : a.keys[(s - 1) & 1];
   const uint32_t* ids_in = FIRST ? nullptr : a.ids[(s - 1) & 1];
@@ -865,7 +866,7 @@ __device__ void count_block(const GArgs& a, int s, int g, Split sp, int rows, bo
   const uint32_t dshift = pl->shift[s];
   const uint32_t dmask = (1u << pl->nbits[s]) - 1;
   KeyCodec kc;
-  kc.init(a, pl);
+  kc.init(a.d0, pl);
   const bool packed = pl->packed != 0;
   const uint64_t* keys_in = a.keys[(s - 1) & 1];
   for (int b = t; b < nb; b += threads) {
@@ -1202,7 +1203,7 @@ __device__ void mid_fast(const GArgs& a, int s, int g, MidFastShared& sh) {
   const int wb = w * kWave * R1;
   const Plan* pl = a.plan;
   KeyCodec kc;
-  kc.init(a, pl);
+  kc.init(a.d0, pl);
   const uint32_t dshift = pl->shift[s];
   const uint64_t* in = a.keys[(s - 1) & 1];
   uint64_t* out = a.keys[s & 1];
@@ -1339,7 +1340,7 @@ __device__ void count_mid(const GArgs& a, int s, int g, CountMidShared& sh) {
   const uint32_t dshift = pl->shift[s];
   constexpr uint32_t M = kMaxBins - 1;  // middle passes have 1024 digits
   KeyCodec kc;
-  kc.init(a, pl);
+  kc.init(a.d0, pl);
   const bool packed = pl->packed != 0;
   const uint64_t* keys_in = a.keys[(s - 1) & 1];
   uint32_t* flat = &sh.cnt[0][0];
@@ -1511,7 +1512,7 @@ __device__ void final_generic(const GArgs& a, int g, FinalShared& sh) {
   const uint32_t dshift = pl->shift[s];
   const uint32_t dmask = (1u << nbits) - 1;
   KeyCodec kc;
-  kc.init(a, pl);
+  kc.init(a.d0, pl);
   const bool packed = pl->packed != 0;
   const uint64_t* keys_in = a.keys[(s - 1) & 1];
   const uint32_t* ids_in = a.ids[(s - 1) & 1];

@@ -44,7 +44,7 @@ struct BCtl {
   uint32_t count[kLists];             // entries of the long list (count[kListLong])
   uint32_t empty[kLists][kSubLists];  // 1 once a segment was found exhausted (a hint)
   uint64_t long_elems;                // requests in the long list's queues
-  uint32_t ranges[5];                 // long queues: pmin, pmax, lmin, lmax, longest
+  uint32_t long_tiles, long_items;    // their tiles and scan items
 };
 // One segment of a list, alone in its 128-byte line: its entry count (the
 // planner's filing atomics) and the next batch to grab (the kernels'
@@ -65,7 +65,7 @@ struct LongTileDesc {
   int64_t s;       // the queue
   uint32_t lo;     // the tile's first request within the queue
   int32_t cnt;     // requests in the tile
-  uint32_t item0;  // the queue's first digit-offset work item
+  uint32_t item0;  // the queue's first tile
   uint32_t rows;   // tiles of the queue
 };
 
@@ -86,19 +86,21 @@ struct BArgs {
   // the wide list's, then the long list's num_segments entries
   uint32_t* lists;
   int64_t seg_cap;          // list_segment_cap(num_segments)
-  // segmented sort of the long queues (capacity: requests in long queues)
+  // sort of the long queues (capacity: requests in long queues)
   uint64_t long_cap;
   uint32_t max_tiles;
   uint64_t* keys[2];        // [long_cap]
-  uint32_t* ids[2];         // [long_cap]
-  uint32_t* hist;           // [max_tiles][2^kLongDigitBits] digit counts, then offsets
-  uint64_t* tsum;           // [max_tiles] length sums, then wait bases
-  uint64_t* lbase;          // [long list + 1] start of every long queue in keys/ids
-  uint32_t* tstart;         // [long list + 1] first tile of every long queue
-  uint32_t* istart;         // [long list + 1] first digit-offset work item of every long queue
-  uint32_t* qtot;           // [kLongColDigits * long_items_max] digit totals of the queues of many tiles
+  uint64_t* lbase;          // [long queues + 1] start of every long queue in keys
+  uint32_t* tstart;         // [long queues + 1] first tile of every long queue
+  uint32_t* istart;         // [long queues] first scan item of every long queue
+  uint32_t* imap;           // [long_items_max] queue * kLongScanParts + part of each scan item
   LongTileDesc* tdesc;      // [max_tiles] every tile's place, written once per call
-  uint32_t* imap;           // [long_items_max] first tile of each digit-offset item's queue
+  struct Plan* plan;
+  uint32_t* lranges;        // [max_tiles][4] ranges of every tile
+  uint16_t* lcount;         // [max_tiles][1024] digit counts of a scatter pass
+  uint32_t* hist;           // [max_tiles][1024] their prefixes over the queue's tiles
+  uint64_t* lfinal;         // [max_tiles][1024] final-digit counts and length sums
+  uint64_t* lwait;          // [max_tiles][1024] prefixes of the length sums
 };
 
 // Single queue of a.n_single <= kSegLargeCap requests (a.offsets null), one
@@ -107,20 +109,19 @@ hipError_t launch_single_lds(const BArgs& a, hipStream_t st);
 // The whole batched schedule: planner, the LDS kernels of every size class,
 // the segmented sort of long queues. a.flags and a.ctl zeroed by the caller.
 hipError_t launch_batched(const BArgs& a, hipStream_t st);
+// The long queues (long_sort.hip).
+hipError_t launch_long_queues(const BArgs& a, hipStream_t st);
 // Workspace parts of the segmented sort for `long_cap` requests in long
 // queues out of num_segments queues.
 uint32_t long_max_tiles(uint64_t long_cap, int64_t num_segments);
-// Digits of a pass of the segmented sort of the long queues.
-constexpr int kLongDigitBits = 10;
-// A long queue of at most kLongRowsFew tiles takes its digit offsets in one
-// work item; a longer one in one per kLongColDigits digits.
+// A long queue of at most kLongRowsFew tiles is scanned as one work item; a
+// longer one as kLongScanParts.
 constexpr uint32_t kLongRowsFew = 32;
-// Digits of one work item of a longer queue (its columns are scanned together).
-constexpr int kLongColDigits = 16;
-// Most digit-offset work items of the long queues.
+constexpr int kLongScanParts = 64;
+// Most scan items of the long queues.
 inline uint64_t long_items_max(uint64_t long_cap, int64_t queues) {
-  return (uint64_t)queues + ((1u << kLongDigitBits) / kLongColDigits) *
-                                (long_cap / ((uint64_t)kLongRowsFew * kLongTile) + 1);
+  return (uint64_t)queues +
+         kLongScanParts * (long_cap / ((uint64_t)kLongRowsFew * kLongTile) + 1);
 }
 
 // ---------------------------------------------------------------------------
@@ -171,6 +172,7 @@ struct Plan {
   uint32_t cglb;      // compact: 1 if some block of the final pass needs the
                       // global-window kernel (sub-bucket starts beyond the LDS
                       // window, or a queue too long for buffer-resource stores)
+  uint32_t sum64;     // batched long queues: a wave's waits add up below 2^64
   uint32_t shift[kMaxScatter];  // digit = (u2 >> shift) & (bins - 1), passes >= 1
   uint32_t nbits[kMaxScatter];
   uint32_t nbins[kMaxScatter];

@@ -9,17 +9,18 @@
 
 namespace semsched {
 
-// Fills every field of the plan but `ok`, `cglb` and the carried ranks' from
-// the ranges of a valid queue (one thread).
-__device__ __forceinline__ void make_plan(const GArgs& a, uint32_t gpmin, uint32_t gpmax,
+// Fills every field of the plan but `ok` and `cglb` from the ranges of valid
+// queues (one thread); no ranks are carried. d0: width of the first digit;
+// max_id: the largest request id; force_wide, chunked: as in GArgs.
+__device__ __forceinline__ void make_plan(uint32_t d0, uint32_t max_id, bool force_wide,
+                                          bool chunked, uint32_t gpmin, uint32_t gpmax,
                                           uint32_t glmin, uint32_t glmax, Plan* pl) {
-  const uint32_t d0 = (uint32_t)a.d0;
   const uint32_t P = gpmax - gpmin + 1;
   const uint32_t hmin = glmin >> d0;
   const uint32_t H = (glmax >> d0) - hmin + 1;
   const uint32_t wp = bit_width32(P - 1);
   const uint32_t wh = bit_width32(H - 1);
-  const uint32_t wid = bit_width32((uint32_t)(a.n - 1));
+  const uint32_t wid = bit_width32(max_id);
   const uint32_t kb = wp + wh + d0;  // live key bits
   pl->pmin = gpmin;
   pl->P = P;
@@ -29,8 +30,8 @@ __device__ __forceinline__ void make_plan(const GArgs& a, uint32_t gpmin, uint32
   pl->wh = wh;
   // A key of at most 32 bits sits in the high word above a 32-bit id, so no
   // shifts across words are needed to take an element apart.
-  pl->W = (!a.force_wide && kb <= 32) ? 32u : wid;
-  pl->packed = (!a.force_wide && kb + pl->W <= 64) ? 1u : 0u;
+  pl->W = (!force_wide && kb <= 32) ? 32u : wid;
+  pl->packed = (!force_wide && kb + pl->W <= 64) ? 1u : 0u;
   pl->small = glmax < (1u << 26) ? 1u : 0u;
   const uint64_t R = (uint64_t)P * H;  // <= 2^31 because d0 >= 8
   pl->shift[0] = 0;
@@ -54,7 +55,7 @@ __device__ __forceinline__ void make_plan(const GArgs& a, uint32_t gpmin, uint32
   pl->nscatter = 2 + mids;
   // compact layout: two passes, at most 256 final digits (the big-tile final
   // pass), lengths below 2^26, and the sub-bucket starts were counted
-  pl->compact = (a.chunked && !a.force_wide && mids == 0 && fb <= 256 && pl->small) ? 1u : 0u;
+  pl->compact = (chunked && !force_wide && mids == 0 && fb <= 256 && pl->small) ? 1u : 0u;
   pl->pay = 0;
   pl->pay_shift = 32;
 }
@@ -112,8 +113,8 @@ static __device__ bool grid_barrier(const GArgs& a, uint32_t gen) {
 struct KeyCodec {
   uint32_t d0, wh, W, hmin, H, pmin;
   uint64_t m0, mh, idmask;
-  __device__ __forceinline__ void init(const GArgs& a, const Plan* pl) {
-    d0 = (uint32_t)a.d0;
+  __device__ __forceinline__ void init(int first_bits, const Plan* pl) {
+    d0 = (uint32_t)first_bits;
     wh = pl->wh;
     W = pl->W;
     hmin = pl->hmin;
@@ -140,13 +141,16 @@ struct KeyCodec {
   }
 };
 
-// The same for keys of at most 32 bits (an element's high word, Plan::W = 32):
-// no 64-bit shifts.
+// Element forms of the one-tile-per-workgroup sorts (tile_common.h): what a
+// packed element holds, each with make / id / lo_of / u2_of / pp_of / len_of.
+//
+// Keys of at most 32 bits in the element's high word (Plan::W = 32): no 64-bit
+// shifts.
 struct KeyCodec32 {
   uint32_t d0, ph, hoff, H, pmin, m0, mh, ml;
-  __device__ __forceinline__ void init(const GArgs& a, const Plan* pl) {
-    d0 = (uint32_t)a.d0;
-    ph = d0 + pl->wh;  // (32 when a 32-bit key holds lengths only: one rank)
+  __device__ __forceinline__ void init(int first_bits, const Plan* pl) {
+    d0 = (uint32_t)first_bits;
+    ph = d0 + pl->wh;  // at most 31: lengths are below 2^31
     hoff = pl->hmin << d0;
     H = pl->H;
     pmin = pl->pmin;
@@ -154,27 +158,62 @@ struct KeyCodec32 {
     mh = pl->wh ? 0xffffffffu >> (32 - pl->wh) : 0u;
     ml = 0xffffffffu >> (32 - ph);
   }
-  __device__ __forceinline__ static uint32_t key(uint64_t e) { return (uint32_t)(e >> 32); }
   __device__ __forceinline__ static uint32_t id(uint64_t e) { return (uint32_t)e; }
-  __device__ __forceinline__ uint32_t lo(uint32_t k) const { return k & m0; }
-  __device__ __forceinline__ uint32_t pp(uint32_t k) const { return ph < 32 ? k >> ph : 0u; }
-  __device__ __forceinline__ uint32_t u2(uint32_t k) const {
-    return pp(k) * H + ((k >> d0) & mh);
+  __device__ __forceinline__ uint32_t lo_of(uint64_t e) const { return (uint32_t)(e >> 32) & m0; }
+  __device__ __forceinline__ uint32_t pp_of(uint64_t e) const { return (uint32_t)(e >> 32) >> ph; }
+  __device__ __forceinline__ uint32_t u2_of(uint64_t e) const {
+    return pp_of(e) * H + (((uint32_t)(e >> 32) >> d0) & mh);
   }
-  __device__ __forceinline__ uint32_t len(uint32_t k) const { return (k & ml) + hoff; }
+  __device__ __forceinline__ uint32_t len_of(uint64_t e) const {
+    return ((uint32_t)(e >> 32) & ml) + hoff;
+  }
   __device__ __forceinline__ uint64_t make(uint32_t p, uint32_t l, uint32_t i) const {
-    const uint32_t hi = (ph < 32 ? (p - pmin) << ph : 0u) + (l - hoff);
-    return ((uint64_t)hi << 32) | i;
+    return ((uint64_t)(((p - pmin) << ph) + (l - hoff)) << 32) | i;
   }
 };
 
-// KeyCodec with the interface of KeyCodec32.
+// Any key above an id of W bits.
 struct KeyCodec64 : KeyCodec {
-  __device__ __forceinline__ uint64_t key(uint64_t e) const { return e >> W; }
   __device__ __forceinline__ uint32_t id(uint64_t e) const { return (uint32_t)(e & idmask); }
+  __device__ __forceinline__ uint32_t lo_of(uint64_t e) const { return lo(e >> W); }
+  __device__ __forceinline__ uint32_t pp_of(uint64_t e) const { return pp(e >> W); }
+  __device__ __forceinline__ uint32_t u2_of(uint64_t e) const { return u2(e >> W); }
+  __device__ __forceinline__ uint32_t len_of(uint64_t e) const { return len(e >> W); }
   using KeyCodec::make;
   __device__ __forceinline__ uint64_t make(uint32_t p, uint32_t l, uint32_t i) const {
     return (make(p, l) << W) | i;
+  }
+};
+
+// Key and id beyond 64 bits together (39-bit keys in queues of more than 2^25
+// requests): the element leaves the first digit out, which no pass after the
+// first orders by, and lengths are read through the id.
+struct KeyCodecGather {
+  uint32_t d0, wh, W, hmin, H, pmin;
+  uint64_t mh, idmask;
+  const int32_t* lengths;  // the queue's
+  __device__ __forceinline__ void init(int first_bits, const Plan* pl) {
+    d0 = (uint32_t)first_bits;
+    wh = pl->wh;
+    W = pl->W;
+    hmin = pl->hmin;
+    H = pl->H;
+    pmin = pl->pmin;
+    mh = (1ull << wh) - 1;
+    idmask = (1ull << W) - 1;
+    lengths = nullptr;
+  }
+  __device__ __forceinline__ uint32_t id(uint64_t e) const { return (uint32_t)(e & idmask); }
+  __device__ __forceinline__ uint32_t len_of(uint64_t e) const { return (uint32_t)lengths[id(e)]; }
+  __device__ __forceinline__ uint32_t lo_of(uint64_t e) const {
+    return len_of(e) & ((1u << d0) - 1);
+  }
+  __device__ __forceinline__ uint32_t pp_of(uint64_t e) const { return (uint32_t)(e >> (W + wh)); }
+  __device__ __forceinline__ uint32_t u2_of(uint64_t e) const {
+    return pp_of(e) * H + (uint32_t)((e >> W) & mh);
+  }
+  __device__ __forceinline__ uint64_t make(uint32_t p, uint32_t l, uint32_t i) const {
+    return ((((uint64_t)(p - pmin) << wh) | ((l >> d0) - hmin)) << W) | i;
   }
 };
 

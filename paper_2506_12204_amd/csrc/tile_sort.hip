@@ -18,36 +18,14 @@
 // Measured: a queue of 50,003 requests 156 us in the big-tile path's nine
 // launches (16K-item tiles: 4 workgroups), 28 us here; one of 2^20 76 us (64
 // workgroups), 51 us here.
-#include "block_common.h"
-#include "kernels.h"
-#include "key_plan.h"
+#include "tile_common.h"
 
 namespace semsched {
 
 namespace {
 
-constexpr int TT = 1024;  // threads: one per digit
-constexpr int TWV = TT / kWave;
-static_assert(TT == kMaxBins, "every thread owns one digit");
-constexpr int kCountCopies = 8;  // copies of a count (lane % 8): equal digits in a wave
-                                 // (short lengths, few classes) spread over them
-constexpr int kFinalSlots = 8192;  // u64 slots of the final digit's counts, all copies
-
-__device__ __forceinline__ int wave_no() {
-  return __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
-}
-
-__device__ __forceinline__ void clear_row(uint16_t* cnt) {  // this wave's 1024 counters
-  u64_alias* c64 = reinterpret_cast<u64_alias*>(cnt);
-#pragma unroll
-  for (int i = 0; i < kMaxBins / (kWave * 4); ++i) c64[i * kWave + lane_id()] = 0;
-}
-
-// The count rows of the tile path: first-digit counts (u16, a tile holds at
-// most 8192 requests), then final-digit counts above their length sums (u64:
-// 8192 lengths below 2^31 sum to less than 2^44, so up to eight rows can be
-// added as they are).
-constexpr uint32_t kSumBits = 47;
+// The count rows of this path: first-digit (or middle-digit) counts, then
+// final-digit counts and length sums.
 __device__ __forceinline__ uint16_t* count_rows(const GArgs& a) {
   return reinterpret_cast<uint16_t*>(a.block_hist);
 }
@@ -74,8 +52,7 @@ __global__ __launch_bounds__(TT) void t_count(GArgs a) {
     pv[r] = a.priority[i];
     lv[r] = a.length[i];
   }
-  for (int i = t; i < kMaxBins * kCountCopies / 4; i += TT)
-    reinterpret_cast<uint4*>(s_cnt)[i] = make_uint4(0, 0, 0, 0);
+  clear_counts(s_cnt);
   if (blockIdx.x == 0) {
     if (t == 0) {
       a.flags[0] = 0;
@@ -89,69 +66,16 @@ __global__ __launch_bounds__(TT) void t_count(GArgs a) {
   }
   block_sync();
   const uint32_t mask = (1u << a.d0) - 1;
-  uint32_t lmin = 0xffffffffu, lmax = 0, pmin = 0xffu, pmax = 0, bad = 0;
+  TileRanges rg;
 #pragma unroll
   for (int r = 0; r < R; ++r) {
     const bool in = first + r * TT + t < a.n;
-    const bool ok = (lv[r] >= 0) & ((int)pv[r] < a.num_classes);
-    bad |= (in & !ok) ? 1u : 0u;
-    lmin = min(lmin, in ? (uint32_t)lv[r] : 0xffffffffu);
-    lmax = max(lmax, in ? (uint32_t)lv[r] : 0u);
-    pmin = min(pmin, in ? pv[r] : 0xffu);
-    pmax = max(pmax, in ? pv[r] : 0u);
+    rg.add(in, pv[r], lv[r], a.num_classes);
     atomicAdd(&s_cnt[((uint32_t)lv[r] & mask) * kCountCopies + (lane & (kCountCopies - 1))],
               in ? 1u : 0u);
   }
-  lmin = wave_min_u32(lmin);
-  lmax = wave_max_u32(lmax);
-  pmin = wave_min_u32(pmin);
-  pmax = wave_max_u32(pmax);
-  bad = wave_or_u32(bad);
-  if (lane == 0) {
-    const int w = wave_no();
-    s_red[0][w] = pmin;
-    s_red[1][w] = pmax | (bad << 31);
-    s_red[2][w] = lmin;
-    s_red[3][w] = lmax;
-  }
-  block_sync();
-  if (t < 4) {
-    uint32_t v = s_red[t][0];
-    for (int i = 1; i < TWV; ++i) {
-      const uint32_t x = s_red[t][i];
-      // (pmax: the error bit is above every rank)
-      v = (t & 1) ? (t == 1 ? (max(v & 0xffu, x & 0xffu) | ((v | x) & 0x80000000u)) : max(v, x))
-                  : min(v, x);
-    }
-    a.block_ranges[4 * (size_t)blockIdx.x + t] = v;
-  }
-  const uint4 c0 = reinterpret_cast<const uint4*>(s_cnt)[2 * t];
-  const uint4 c1 = reinterpret_cast<const uint4*>(s_cnt)[2 * t + 1];
-  static_assert(kCountCopies == 8, "two quads per digit");
-  count_rows(a)[(size_t)blockIdx.x * kMaxBins + t] =
-      (uint16_t)(c0.x + c0.y + c0.z + c0.w + c1.x + c1.y + c1.z + c1.w);
-}
-
-// Turns the waves' counters of a ranked tile into the positions of each
-// wave's first item of a digit in the tile's digit order; the thread's digit
-// starts at the returned position. Holds barriers.
-__device__ __forceinline__ uint32_t tile_positions(uint16_t (*cnt)[kMaxBins], uint32_t* scan32) {
-  const int t = threadIdx.x;
-  uint32_t c[TWV], tot = 0;
-#pragma unroll
-  for (int v = 0; v < TWV; ++v) {
-    c[v] = cnt[v][t];
-    tot += c[v];
-  }
-  uint32_t all;
-  const uint32_t ex = block_excl_scan_u32<TT>(tot, scan32, all);
-  uint32_t run = ex;
-#pragma unroll
-  for (int v = 0; v < TWV; ++v) {
-    cnt[v][t] = (uint16_t)run;
-    run += c[v];
-  }
-  return ex;
+  rg.write(s_red, a.block_ranges + 4 * (size_t)blockIdx.x);  // (holds a barrier)
+  write_counts(s_cnt, count_rows(a) + (size_t)blockIdx.x * kMaxBins);
 }
 
 // Sums the tiles' count rows: thread t sums digits 4*(t % 256) .. + 3 over every
@@ -237,7 +161,7 @@ __device__ __forceinline__ void tile_scatter(const GArgs& a, TileFirstLds<R>& sh
   const int w = wave_no();
   const int j0 = w * kWave * R + lane_id();
   Codec kc;
-  kc.init(a, &sh.plan);
+  kc.init(a.d0, &sh.plan);
 #pragma unroll
   for (int r = 0; r < R; ++r)
     sh.u.stage[rk[r] + sh.cnt[w][dg[r]]] =
@@ -249,7 +173,7 @@ __device__ __forceinline__ void tile_scatter(const GArgs& a, TileFirstLds<R>& sh
     const int j = j0 + r * kWave;
     if (j < cv) {
       const uint64_t e = sh.u.stage[j];
-      const uint32_t pos = sh.base[kc.lo(kc.key(e))] + (uint32_t)j;
+      const uint32_t pos = sh.base[kc.lo_of(e)] + (uint32_t)j;
       if (pos < (uint64_t)a.n) out[pos] = e;  // (always, for consistent counts)
     }
   }
@@ -277,34 +201,19 @@ __global__ __launch_bounds__(TT) void t_first(GArgs a) {
   uint4 rg = make_uint4(0xffu, 0u, 0xffffffffu, 0u);
   if (t < rows) rg = reinterpret_cast<const uint4*>(a.block_ranges)[t];
   fold_rows(a, me, rows, sh.u.fold.before, sh.u.fold.after);
-  {
-    const uint32_t pl = wave_min_u32(rg.x), ph = wave_max_u32(rg.y & 0xffu);
-    const uint32_t bad = wave_or_u32(rg.y & 0x80000000u);
-    const uint32_t ll = wave_min_u32(rg.z), lh = wave_max_u32(rg.w);
-    if (lane == 0) {
-      sh.red[0][w] = pl;
-      sh.red[1][w] = ph | bad;
-      sh.red[2][w] = ll;
-      sh.red[3][w] = lh;
-    }
-  }
+  stage_ranges(rg, sh.red);
   clear_row(sh.cnt[w]);
   block_sync();
   if (t == 0) {
-    uint32_t pl = 0xffu, ph = 0, ll = 0xffffffffu, lh = 0, bad = 0;
-    for (int i = 0; i < (rows + kWave - 1) / kWave; ++i) {  // the waves that hold a tile's ranges
-      pl = min(pl, sh.red[0][i]);
-      ph = max(ph, sh.red[1][i] & 0xffu);
-      bad |= sh.red[1][i] & 0x80000000u;
-      ll = min(ll, sh.red[2][i]);
-      lh = max(lh, sh.red[3][i]);
-    }
+    const uint4 all = collect_ranges(sh.red, (rows + kWave - 1) / kWave);
     sh.plan.cglb = 0;
     sh.plan.ok = 0;
+    const bool bad = (all.y >> 31) != 0;
     if (bad) {
       if (me == 0) atomicOr(a.flags, kFlagRange);
     } else {
-      make_plan(a, pl, ph, ll, lh, &sh.plan);
+      make_plan((uint32_t)a.d0, (uint32_t)(a.n - 1), false, false, all.x, all.y,
+                all.z, all.w, &sh.plan);
       sh.plan.ok = 1;
     }
     if (me == 0 && !bad) *a.plan = sh.plan;
@@ -342,24 +251,21 @@ __device__ void tile_count_mid(const GArgs& a, int s, TileCountLds& sh) {
   const uint32_t copy = (uint32_t)lane_id() & (kCountCopies - 1);
   const uint32_t dshift = a.plan->shift[s];
   Codec kc;
-  kc.init(a, a.plan);
+  kc.init(a.d0, a.plan);
   const uint64_t* in = a.keys[(s - 1) & 1];
   const int64_t first = (int64_t)blockIdx.x * (TT * R);
   uint64_t e[R];
 #pragma unroll
   for (int r = 0; r < R; ++r) e[r] = in[min(first + r * TT + t, a.n - 1)];
-  uint4* quads = reinterpret_cast<uint4*>(sh.cnt);
-  for (int i = t; i < kMaxBins * kCountCopies / 4; i += TT) quads[i] = make_uint4(0, 0, 0, 0);
+  clear_counts(sh.cnt);
   block_sync();
 #pragma unroll
   for (int r = 0; r < R; ++r) {
-    const uint32_t d = (kc.u2(kc.key(e[r])) >> dshift) & (kMaxBins - 1);
+    const uint32_t d = (kc.u2_of(e[r]) >> dshift) & (kMaxBins - 1);
     atomicAdd(&sh.cnt[d * kCountCopies + copy], first + r * TT + t < a.n ? 1u : 0u);
   }
   block_sync();
-  const uint4 c0 = quads[2 * t], c1 = quads[2 * t + 1];
-  count_rows(a)[(size_t)blockIdx.x * kMaxBins + t] =
-      (uint16_t)(c0.x + c0.y + c0.z + c0.w + c1.x + c1.y + c1.z + c1.w);
+  write_counts(sh.cnt, count_rows(a) + (size_t)blockIdx.x * kMaxBins);
 }
 
 // Scatter of one tile of middle pass s.
@@ -371,7 +277,7 @@ __device__ void tile_scatter_mid(const GArgs& a, int s, TileFirstLds<R>& sh) {
   const uint32_t dshift = a.plan->shift[s];
   constexpr uint32_t M = kMaxBins - 1;
   Codec kc;
-  kc.init(a, a.plan);
+  kc.init(a.d0, a.plan);
   const uint64_t* in = a.keys[(s - 1) & 1];
   uint64_t* out = a.keys[s & 1];
   const int64_t first = (int64_t)me * (TT * R);
@@ -387,7 +293,7 @@ __device__ void tile_scatter_mid(const GArgs& a, int s, TileFirstLds<R>& sh) {
   uint32_t dg[R], rk[R];
 #pragma unroll
   for (int r = 0; r < R; ++r) {  // items past the end take the last digit
-    dg[r] = j0 + r * kWave < cv ? (kc.u2(kc.key(e[r])) >> dshift) & M : M;
+    dg[r] = j0 + r * kWave < cv ? (kc.u2_of(e[r]) >> dshift) & M : M;
     rk[r] = rank_round_c<10>(dg[r], sh.cnt[w]);
   }
   block_sync();
@@ -402,7 +308,7 @@ __device__ void tile_scatter_mid(const GArgs& a, int s, TileFirstLds<R>& sh) {
     const int j = j0 + r * kWave;
     if (j < cv) {
       const uint64_t x = sh.u.stage[j];
-      const uint32_t pos = sh.base[(kc.u2(kc.key(x)) >> dshift) & M] + (uint32_t)j;
+      const uint32_t pos = sh.base[(kc.u2_of(x) >> dshift) & M] + (uint32_t)j;
       if (pos < (uint64_t)a.n) out[pos] = x;  // (always, for consistent counts)
     }
   }
@@ -444,44 +350,17 @@ __global__ __launch_bounds__(TT) void t_mid_scatter(GArgs a, int s) {
 template <int R, typename Codec>
 __device__ void tile_histF(const GArgs& a, uint64_t* s_bin) {
   const Plan* pl = a.plan;
-  const int t = threadIdx.x;
   const int s = (int)pl->nscatter - 1;
-  const int nb = (int)pl->nbins[s];
-  const uint32_t dshift = pl->shift[s];
-  const uint32_t dmask = (1u << pl->nbits[s]) - 1;
   Codec kc;
-  kc.init(a, pl);
-  // bins rounded up to a power of two, in as many copies as the slots hold (at
-  // most one per lane)
-  const uint32_t cb = min(6u, 13u - bit_width32((uint32_t)nb - 1));
+  kc.init(a.d0, pl);
   const uint64_t* in = a.keys[(s - 1) & 1];
   const int64_t first = (int64_t)blockIdx.x * (TT * R);
+  const int cv = (int)min((int64_t)(TT * R), a.n - first);
   uint64_t e[R];
 #pragma unroll
-  for (int r = 0; r < R; ++r) e[r] = in[min(first + r * TT + t, a.n - 1)];
-  for (int i = t; i < (nb << cb); i += TT) s_bin[i] = 0;
-  block_sync();
-  const uint32_t copy = (uint32_t)lane_id() & ((1u << cb) - 1);
-#pragma unroll
-  for (int r = 0; r < R; ++r) {
-    const auto key = kc.key(e[r]);
-    const uint32_t d = (kc.u2(key) >> dshift) & dmask;
-    if (first + r * TT + t < a.n)
-      atomicAdd(reinterpret_cast<unsigned long long*>(&s_bin[(d << cb) + copy]),
-                (1ull << kSumBits) | kc.len(key));
-  }
-  block_sync();
-  // 2^cb threads per bin where there are threads enough, else one thread
-  // takes a bin's copies
-  uint64_t* row = final_rows(a) + (size_t)blockIdx.x * kMaxBins;
-  const int per = 8;  // copies added by one thread (cb >= 3: nb <= 1024)
-  for (int i = t; i < (nb << cb) / per; i += TT) {
-    uint64_t v = 0;
-#pragma unroll
-    for (int k = 0; k < per; ++k) v += s_bin[per * i + k];
-    for (uint32_t k = 1; k < (1u << cb) / per; k <<= 1) v += __shfl_xor(v, (int)k, kWave);
-    if ((i & ((1 << cb) / per - 1)) == 0) row[i >> (cb - 3)] = v;
-  }
+  for (int r = 0; r < R; ++r) e[r] = in[first + min(r * TT + (int)threadIdx.x, cv - 1)];
+  count_final(kc, TileDigit{pl->shift[s], pl->nbits[s]}, (int)pl->nbins[s], e, cv, s_bin,
+              final_rows(a) + (size_t)blockIdx.x * kMaxBins);
 }
 
 // The final digit's counts, after any middle passes that were not launched
@@ -511,7 +390,7 @@ __global__ __launch_bounds__(TT) void t_histF(GArgs a, int mids) {
 }
 
 template <int R>
-struct TileFinalLds {
+struct TileFinalLds : PlaceLds {
   union {
     uint64_t stage[TT * R];
     struct {
@@ -519,13 +398,6 @@ struct TileFinalLds {
       uint32_t bc[kMaxBins], tc[kMaxBins];
     } fold;
   } u;
-  uint16_t cnt[TWV][kMaxBins];
-  uint64_t wb[kMaxBins];     // wait base of the tile's run of a digit
-  uint32_t base[kMaxBins];   // output position of a digit's run minus its tile position
-  uint32_t start[kMaxBins];  // the run's tile position
-  uint64_t clo[256], chi[256];
-  uint64_t scan64[TWV + 1];
-  uint32_t scan32[TWV + 1];
   uint32_t last;
 };
 
@@ -539,12 +411,11 @@ __device__ void tile_final(const GArgs& a, TileFinalLds<R>& sh) {
   const int rows = (int)gridDim.x;
   const int s = (int)pl->nscatter - 1;
   const int nb = (int)pl->nbins[s];
-  const uint32_t dshift = pl->shift[s];
-  const uint32_t dmask = (1u << pl->nbits[s]) - 1;
+  const TileDigit dig = {pl->shift[s], pl->nbits[s]};
   const uint32_t P = pl->P;
   const bool small = pl->small != 0;
   Codec kc;
-  kc.init(a, pl);
+  kc.init(a.d0, pl);
   const int64_t first = (int64_t)me * (TT * R);
   const int cv = (int)min((int64_t)(TT * R), a.n - first);
   const int j0 = w * kWave * R + lane;
@@ -556,8 +427,7 @@ __device__ void tile_final(const GArgs& a, TileFinalLds<R>& sh) {
   // counts and length sums of the digits: this tile's offsets and the totals.
   // 2^rb >= nb threads (whole waves) take a row, so 1024 >> rb rows are read
   // at a time.
-  const uint32_t fb = bit_width32((uint32_t)nb - 1);
-  const uint32_t rb = max(fb, 6u);
+  const uint32_t rb = max(pl->nbits[s], 6u);
   sh.u.fold.bw[t] = 0;
   sh.u.fold.tw[t] = 0;
   sh.u.fold.bc[t] = 0;
@@ -566,7 +436,6 @@ __device__ void tile_final(const GArgs& a, TileFinalLds<R>& sh) {
     sh.clo[c] = 0;
     sh.chi[c] = 0;
   }
-  clear_row(sh.cnt[w]);
   block_sync();
   {
     const int d = t & ((1 << rb) - 1);
@@ -574,7 +443,6 @@ __device__ void tile_final(const GArgs& a, TileFinalLds<R>& sh) {
     uint64_t bw = 0, aw = 0;
     uint32_t bc = 0, ac = 0;
     constexpr int U = 8;
-    constexpr uint64_t kSumMask = (1ull << kSumBits) - 1;
     const uint64_t* col = final_rows(a) + min(d, nb - 1);
     for (int g0 = __builtin_amdgcn_readfirstlane(t >> rb); g0 < rows; g0 += step * U) {
       uint64_t x[U];
@@ -615,94 +483,8 @@ __device__ void tile_final(const GArgs& a, TileFinalLds<R>& sh) {
     wait0 += block_excl_scan_u64<TT>(tw, sh.scan64, all64);
   }
 
-  uint32_t dg[R], rk[R];
-#pragma unroll
-  for (int r = 0; r < R; ++r)  // items past the end take the last digit
-    dg[r] = j0 + r * kWave < cv ? (kc.u2(kc.key(e[r])) >> dshift) & dmask : dmask;
-  if (fb <= 6) {
-#pragma unroll
-    for (int r = 0; r < R; ++r) rk[r] = rank_round_c<6>(dg[r], sh.cnt[w]);
-  } else if (fb <= 8) {
-#pragma unroll
-    for (int r = 0; r < R; ++r) rk[r] = rank_round_c<8>(dg[r], sh.cnt[w]);
-  } else {
-#pragma unroll
-    for (int r = 0; r < R; ++r) rk[r] = rank_round_c<10>(dg[r], sh.cnt[w]);
-  }
-  block_sync();
-  const uint32_t ex = tile_positions(sh.cnt, sh.scan32);
-  sh.base[t] = pos0 - ex;
-  sh.start[t] = ex;
-  sh.wb[t] = wait0;
-  block_sync();
-#pragma unroll
-  for (int r = 0; r < R; ++r) sh.u.stage[rk[r] + sh.cnt[w][dg[r]]] = e[r];
-  block_sync();
-
-  // lengths in the tile's digit order, scanned; the first item of a run turns
-  // its digit's wait base into the base of the whole run
-  uint64_t lp[R];
-  uint64_t run = 0;
-#pragma unroll
-  for (int r = 0; r < R; ++r) {
-    const int j = j0 + r * kWave;
-    e[r] = sh.u.stage[j];
-    const uint32_t l = j < cv ? kc.len(kc.key(e[r])) : 0u;
-    const uint64_t inc = small ? (uint64_t)wave_incl_scan_u32(l) : wave_incl_scan_len(l);
-    lp[r] = run + inc - l;
-    run += last_lane_u64(inc);
-  }
-  if (lane == 0) sh.scan64[w] = run;
-  block_sync();
-  uint64_t wave0 = 0;
-  for (int v = 0; v < w; ++v) wave0 += sh.scan64[v];  // (w is uniform)
-#pragma unroll
-  for (int r = 0; r < R; ++r) {
-    const int j = j0 + r * kWave;
-    lp[r] += wave0;
-    dg[r] = j < cv ? (kc.u2(kc.key(e[r])) >> dshift) & dmask : dmask;
-    if (j < cv && (uint32_t)j == sh.start[dg[r]]) sh.wb[dg[r]] -= lp[r];
-  }
-  block_sync();
-  // order and waits; the tile is class-major, so a lane's classes do not
-  // decrease over its rounds. A lane sums at most 8 waits below 2^51 (the
-  // queue has at most 2^20 requests).
-  uint32_t cur = 0xffffffffu;
-  uint64_t acc = 0;
-#pragma unroll
-  for (int r = 0; r < R; ++r) {
-    const int j = j0 + r * kWave;
-    if (j < cv) {
-      const uint32_t pos = sh.base[dg[r]] + (uint32_t)j;
-      const uint64_t wt = sh.wb[dg[r]] + lp[r];
-      if (pos < (uint64_t)a.n) {  // (always, for consistent counts)
-        a.order[pos] = (int32_t)kc.id(e[r]);
-        a.wait[pos] = (int64_t)wt;
-      }
-      const uint32_t c = kc.pp(kc.key(e[r]));
-      if (c != cur) {
-        if (cur != 0xffffffffu) {
-          const U128 v = {acc, 0};
-          atomic_add128(&sh.clo[cur], &sh.chi[cur], v);
-        }
-        cur = c;
-        acc = 0;
-      }
-      acc += wt;
-    }
-  }
-  // lanes that end in one class (nearly all waves) add up first
-  const uint32_t c0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)cur);
-  if (__builtin_amdgcn_ballot_w64(cur != c0) == 0) {
-    if (c0 != 0xffffffffu) {
-      const uint64_t sum = last_lane_u64(wave_incl_scan_u64(acc));  // below 2^60
-      const U128 v = {sum, 0};
-      if (lane == 0) atomic_add128(&sh.clo[c0], &sh.chi[c0], v);
-    }
-  } else if (cur != 0xffffffffu) {
-    const U128 v = {acc, 0};
-    atomic_add128(&sh.clo[cur], &sh.chi[cur], v);
-  }
+  place_tile<false>(kc, dig, small, e, cv, pos0, wait0, a.order, a.wait, (uint64_t)a.n, sh,
+                    [] {});
   block_sync();
 
   // Class totals: every tile publishes its sums, the last workgroup to finish

@@ -1,0 +1,65 @@
+"""GPU parity of the batched call's long queues (more than 16,384 requests) at
+the edges of their tiles and scans. Integers throughout: exact."""
+
+import numpy as np
+import pytest
+
+from oracle import c_oracle_batched
+from tests._lib import assert_same, ensure_built, gpu_available, gpu_batched
+from workloads import fuzz_segments
+
+pytestmark = [pytest.mark.gpu,
+              pytest.mark.skipif(not gpu_available(), reason="needs a GPU")]
+
+TILE = 8192
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _built():
+    ensure_built()
+
+
+def check(sizes, label, classes=5, max_len=32768, seed=1):
+    p, l, off = fuzz_segments(sizes, seed=seed, classes=classes, max_len=max_len)
+    want = c_oracle_batched(p, l, off, classes)
+    room = sum(s for s in sizes if s > 16384)
+    for blocking, long_requests in ((False, room), (True, None)):
+        print(f"[gpu] {label} sizes={list(sizes)[:6]} blocking={blocking}", flush=True)
+        got = gpu_batched(p, l, off, classes, blocking=blocking, long_requests=long_requests)
+        assert_same(got, want, label)
+
+
+# one request past the LDS size; whole tiles and one request either side; the
+# last queue scanned as one item (32 tiles), the first scanned in parts; runs
+# of more than one batch of rows per lane (1100 tiles)
+@pytest.mark.parametrize("m", [16385, 3 * TILE, 3 * TILE + 1, 32 * TILE, 32 * TILE + 1,
+                               100 * TILE - 1, 1100 * TILE + 5])
+def test_one_queue(m):
+    check([m], "one")
+
+
+def test_mixed_with_short_queues():
+    check([0, 16385, 1, 5000, 40 * TILE + 3, 256, 16384, 20000, 0, 300], "mixed")
+
+
+# digits of one value, up to 64, 256 and 1024; one and two middle passes; keys
+# above 32 bits
+@pytest.mark.parametrize("classes,max_len", [(1, 1000), (3, 9000), (256, 4095), (9, 2_000_000),
+                                             (5, 2**31 - 1), (256, 2**31 - 1)])
+def test_key_widths(classes, max_len):
+    check([50001, 17000, 35 * TILE], f"widths {classes}x{max_len}", classes, max_len)
+
+
+def test_workgroups_that_span_queues():
+    # more tiles than workgroups, so that one takes tiles of several queues
+    check([16385 + 13 * i for i in range(400)], "span")
+
+
+def test_largest_sums():
+    # waits whose sums over a wave reach 2^64, and class totals above it
+    sizes = np.array([1 << 21])
+    off = np.array([0, 1 << 21], np.int64)
+    p = np.repeat(np.array([0, 3], np.uint8), 1 << 20)
+    l = np.full(1 << 21, 2**31 - 1, np.int32)
+    got = gpu_batched(p, l, off, 4, long_requests=int(sizes.sum()))
+    assert_same(got, c_oracle_batched(p, l, off, 4), "largest sums")
