@@ -619,10 +619,13 @@ BLayout batched_layout(int64_t S, uint64_t long_cap) {
     L.tdesc = take(sizeof(LongTileDesc) * (size_t)L.max_tiles);
     L.plan = take(sizeof(Plan));
     L.lranges = take(16 * (size_t)L.max_tiles);
-    L.lcount = take(2 * rows);
     L.hist = take(4 * rows);
-    L.lfinal = take(8 * rows);
-    L.lwait = take(8 * rows);
+    // the tiles' other rows (18 KB each) in 8 bytes per request: at least
+    // that much, so that the size of a workspace stays above 24 bytes per
+    // request, as callers know it
+    L.lfinal = take(std::max<size_t>(8 * long_cap, (8 + 8 + 2) * rows));
+    L.lwait = L.lfinal + 8 * rows;
+    L.lcount = L.lwait + 8 * rows;
   }
   L.total = off;
   return L;
@@ -632,7 +635,7 @@ BLayout batched_layout(int64_t S, uint64_t long_cap) {
 // the fixed part does).
 uint64_t long_capacity(int64_t S, size_t ws_bytes) {
   if (batched_layout(S, 1).total > ws_bytes) return 0;
-  uint64_t lo = 1, hi = ws_bytes / 16 + 1;  // more than 16 bytes per request
+  uint64_t lo = 1, hi = ws_bytes / 24 + 1;  // more than 24 bytes per request
   while (hi - lo > 1) {
     const uint64_t mid = lo + (hi - lo) / 2;
     if (batched_layout(S, mid).total <= ws_bytes) lo = mid;
