@@ -1030,9 +1030,9 @@ int enqueue_select(const uint8_t* p, const int32_t* l, const uint8_t* stage, int
                    int32_t* pushed, int64_t* counts, void* ws, hipStream_t st) {
   SelArgs a = {p, l, stage, n_ids, heap, n_heap, buffer, n_buffer, ongoing, n_ongoing, b,
                batch, pushed, counts, static_cast<uint32_t*>(ws)};
-  if (launch_fill_zero(a.flags, 1, st) != hipSuccess) return SEM_EDEVICE;
-  if (select_in_lds(n_buffer, n_ongoing, b))
+  if (select_in_lds(n_buffer, n_ongoing, b))  // (the kernel resets the error bits)
     return launch_select(a, st) == hipSuccess ? SEM_OK : SEM_EDEVICE;
+  if (launch_fill_zero(a.flags, 1, st) != hipSuccess) return SEM_EDEVICE;
   // candidates (the heap's first b, then the buffer) and ongoing requests
   const int64_t nh = std::min(b, n_heap);
   const WideLayout L = wide_layout(nh + n_buffer + n_ongoing, false);
@@ -1108,10 +1108,10 @@ int enqueue_evict(const uint8_t* p, const int32_t* l, int64_t n_ids, const int32
                   void* ws, hipStream_t st) {
   EvictArgs a = {p, l, n_ids, cached, kv, n_cached, usage, capacity, demands, n_demands,
                  victims, upto, static_cast<uint32_t*>(ws)};
+  if (n_cached <= kEvictCap && n_cached + n_demands > 0)  // (the kernel resets the error bits)
+    return launch_evict_victims(a, st) == hipSuccess ? SEM_OK : SEM_EDEVICE;
   if (launch_fill_zero(a.flags, 1, st) != hipSuccess) return SEM_EDEVICE;
   if (n_cached + n_demands == 0) return SEM_OK;
-  if (n_cached <= kEvictCap)
-    return launch_evict_victims(a, st) == hipSuccess ? SEM_OK : SEM_EDEVICE;
   const WideLayout L = wide_layout(n_cached, true);
   char* base = static_cast<char*>(ws);
   WideSort w = {};

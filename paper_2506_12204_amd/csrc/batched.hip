@@ -163,34 +163,12 @@ __device__ __forceinline__ uint32_t group_excl_scan_u32(uint32_t v, uint32_t* sc
   }
 }
 
-// Wave reductions through DPP lane moves (no LDS traffic): row_shr steps
-// within rows of 16 lanes, then row_bcast:15 and row_bcast:31 across rows;
-// lanes whose source is outside the row (or masked off) take the identity.
-// The result is read from lane 63.
-#define SEMSCHED_DPP_REDUCE(NAME, OP, IDENT)                                                  \
-  __device__ __forceinline__ uint32_t NAME(uint32_t v) {                                      \
-    v = OP(v, (uint32_t)__builtin_amdgcn_update_dpp((int)(IDENT), (int)v, 0x111, 0xf, 0xf, false)); \
-    v = OP(v, (uint32_t)__builtin_amdgcn_update_dpp((int)(IDENT), (int)v, 0x112, 0xf, 0xf, false)); \
-    v = OP(v, (uint32_t)__builtin_amdgcn_update_dpp((int)(IDENT), (int)v, 0x114, 0xf, 0xf, false)); \
-    v = OP(v, (uint32_t)__builtin_amdgcn_update_dpp((int)(IDENT), (int)v, 0x118, 0xf, 0xf, false)); \
-    v = OP(v, (uint32_t)__builtin_amdgcn_update_dpp((int)(IDENT), (int)v, 0x142, 0xa, 0xf, false)); \
-    v = OP(v, (uint32_t)__builtin_amdgcn_update_dpp((int)(IDENT), (int)v, 0x143, 0xc, 0xf, false)); \
-    return (uint32_t)__builtin_amdgcn_readlane((int)v, kWave - 1);                             \
-  }
-__device__ __forceinline__ uint32_t op_min(uint32_t a, uint32_t b) { return min(a, b); }
-__device__ __forceinline__ uint32_t op_max(uint32_t a, uint32_t b) { return max(a, b); }
-__device__ __forceinline__ uint32_t op_add(uint32_t a, uint32_t b) { return a + b; }
-SEMSCHED_DPP_REDUCE(wave_rmin, op_min, 0xffffffffu)
-SEMSCHED_DPP_REDUCE(wave_rmax, op_max, 0u)
-SEMSCHED_DPP_REDUCE(wave_radd, op_add, 0u)
-#undef SEMSCHED_DPP_REDUCE
-
 // Wave sum of 64-bit values in three limbs of 22, 22 and 20 bits (each limb's
 // sum over 64 lanes stays below 2^28), exact modulo 2^64.
 __device__ __forceinline__ uint64_t wave_rsum_u64(uint64_t v) {
-  const uint64_t a = wave_radd((uint32_t)v & 0x3fffffu);
-  const uint64_t b = wave_radd((uint32_t)(v >> 22) & 0x3fffffu);
-  const uint64_t c = wave_radd((uint32_t)(v >> 44));
+  const uint64_t a = wave_add_u32((uint32_t)v & 0x3fffffu);
+  const uint64_t b = wave_add_u32((uint32_t)(v >> 22) & 0x3fffffu);
+  const uint64_t c = wave_add_u32((uint32_t)(v >> 44));
   return a + (b << 22) + (c << 44);
 }
 
@@ -346,10 +324,10 @@ __device__ bool schedule_loaded(const BArgs& a, int64_t s, int64_t base, int m,
       pmax = max(pmax, pv[r]);
     }
   }
-  lmin = wave_rmin(lmin);
-  lmax = wave_rmax(lmax);
-  pmin = wave_rmin(pmin);
-  pmax = wave_rmax(pmax);
+  lmin = wave_min_u32(lmin);
+  lmax = wave_max_u32(lmax);
+  pmin = wave_min_u32(pmin);
+  pmax = wave_max_u32(pmax);
   if constexpr (NW > 1) {
     if (lane == 0) {
       sh.red[0][w] = lmin;

@@ -195,35 +195,41 @@ __device__ __forceinline__ uint64_t last_lane_u64(uint64_t v) {
   return ((uint64_t)hi << 32) | lo;
 }
 
-// Inclusive wave scan of a 64-bit value.
+// Inclusive wave scan of a 64-bit value (modulo 2^64): limbs of 22, 21 and 21
+// bits, each limb's sum staying below 2^28. Lane moves only, where shuffles
+// of 64-bit values are twelve dependent LDS-path operations (0.6 us).
 __device__ __forceinline__ uint64_t wave_incl_scan_u64(uint64_t v) {
-#pragma unroll
-  for (int off = 1; off < kWave; off <<= 1) {
-    const uint64_t o = __shfl_up(v, off, kWave);
-    if (lane_id() >= off) v += o;
-  }
-  return v;
+  const uint64_t a = wave_incl_scan_dpp((uint32_t)v & 0x3fffffu);
+  const uint64_t b = wave_incl_scan_dpp((uint32_t)(v >> 22) & 0x1fffffu);
+  const uint64_t c = wave_incl_scan_dpp((uint32_t)(v >> 43));
+  return a + (b << 22) + (c << 43);
 }
 
 __device__ __forceinline__ uint32_t wave_incl_scan_u32(uint32_t v) { return wave_incl_scan_dpp(v); }
 
-__device__ __forceinline__ uint32_t wave_min_u32(uint32_t v) {
-#pragma unroll
-  for (int off = kWave / 2; off > 0; off >>= 1) v = min(v, (uint32_t)__shfl_xor(v, off, kWave));
-  return v;
-}
-
-__device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
-#pragma unroll
-  for (int off = kWave / 2; off > 0; off >>= 1) v = max(v, (uint32_t)__shfl_xor(v, off, kWave));
-  return v;
-}
-
-__device__ __forceinline__ uint32_t wave_or_u32(uint32_t v) {
-#pragma unroll
-  for (int off = kWave / 2; off > 0; off >>= 1) v |= (uint32_t)__shfl_xor(v, off, kWave);
-  return v;
-}
+// Wave reductions through DPP lane moves (no LDS-path operations): row_shr steps
+// within rows of 16 lanes, then row_bcast:15 and row_bcast:31 across rows;
+// lanes whose source is outside the row (or masked off) take the identity.
+// The result is read from lane 63 for every lane.
+#define SEMSCHED_DPP_REDUCE(NAME, OP, IDENT)                                                  \
+  __device__ __forceinline__ uint32_t NAME(uint32_t v) {                                      \
+    v = OP(v, (uint32_t)__builtin_amdgcn_update_dpp((int)(IDENT), (int)v, 0x111, 0xf, 0xf, false)); \
+    v = OP(v, (uint32_t)__builtin_amdgcn_update_dpp((int)(IDENT), (int)v, 0x112, 0xf, 0xf, false)); \
+    v = OP(v, (uint32_t)__builtin_amdgcn_update_dpp((int)(IDENT), (int)v, 0x114, 0xf, 0xf, false)); \
+    v = OP(v, (uint32_t)__builtin_amdgcn_update_dpp((int)(IDENT), (int)v, 0x118, 0xf, 0xf, false)); \
+    v = OP(v, (uint32_t)__builtin_amdgcn_update_dpp((int)(IDENT), (int)v, 0x142, 0xa, 0xf, false)); \
+    v = OP(v, (uint32_t)__builtin_amdgcn_update_dpp((int)(IDENT), (int)v, 0x143, 0xc, 0xf, false)); \
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, kWave - 1);                             \
+  }
+__device__ __forceinline__ uint32_t op_min(uint32_t a, uint32_t b) { return min(a, b); }
+__device__ __forceinline__ uint32_t op_max(uint32_t a, uint32_t b) { return max(a, b); }
+__device__ __forceinline__ uint32_t op_add(uint32_t a, uint32_t b) { return a + b; }
+__device__ __forceinline__ uint32_t op_or(uint32_t a, uint32_t b) { return a | b; }
+SEMSCHED_DPP_REDUCE(wave_min_u32, op_min, 0xffffffffu)
+SEMSCHED_DPP_REDUCE(wave_max_u32, op_max, 0u)
+SEMSCHED_DPP_REDUCE(wave_add_u32, op_add, 0u)
+SEMSCHED_DPP_REDUCE(wave_or_u32, op_or, 0u)
+#undef SEMSCHED_DPP_REDUCE
 
 // Unsigned 128-bit accumulator (waits are non-negative).
 struct U128 {
