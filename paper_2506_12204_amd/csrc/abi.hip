@@ -222,7 +222,6 @@ int enqueue_queue(const uint8_t* p, const int32_t* l, int64_t n, int32_t num_cla
     return SEM_OK;
   }
   if (!needs_global(n)) {
-    if (launch_fill_zero(flags, 1, st) != hipSuccess) return SEM_EDEVICE;
     BArgs a = {};
     a.priority = p;
     a.length = l;
@@ -379,9 +378,6 @@ int enqueue_insert(const uint8_t* p, const int32_t* l, int64_t n_old, int64_t m,
                          const_cast<int32_t*>(a.order_m), const_cast<int64_t*>(a.wait_m),
                          reinterpret_cast<sem_i128*>(base + L.totals_m), ws, st);
   if (rc != SEM_OK) return rc;
-  if (launch_fill_zero(reinterpret_cast<uint32_t*>(totals), 4 * (size_t)(1 + SEM_MAX_CLASSES),
-                       st) != hipSuccess)
-    return SEM_EDEVICE;
   hipEvent_t before = nullptr, after = nullptr;
   {
     std::lock_guard<std::mutex> guard(trace_mu());

@@ -740,8 +740,11 @@ __global__ __launch_bounds__(kMediumThreads, 5) void b_medium(BArgs a) {
 
 __global__ __launch_bounds__(kWideThreads) void b_wide(BArgs a) {
   __shared__ WideLds sh;
-  if (!a.offsets) {  // the single queue
+  if (!a.offsets) {  // the single queue; its error bits are reset here, by the thread
+                     // that may set one (a launch of their own took 3 of 13 us)
     if (blockIdx.x == 0 && a.n_single > 0) {
+      if (threadIdx.x == 0)
+        __hip_atomic_store(a.flags, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       if (!schedule_in_lds<16, 16, 14, 8, uint64_t>(a, 0, 0, (int)a.n_single, sh,
                                                      wave_index(), threadIdx.x))
         if (threadIdx.x == 0) atomicOr(a.flags, kFlagDevice);  // (cannot happen: 39 + 14 bits)

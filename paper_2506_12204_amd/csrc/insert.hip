@@ -38,6 +38,7 @@ constexpr int IT = 256;          // threads of the search kernel
 constexpr int MT = 256;          // threads of the merge kernel (4 waves)
 constexpr int MR = kInsUnit / kWave;  // rounds of 64 entries in a unit
 constexpr int kClassSlots = 257;  // class starts (classes 0..255 and the end)
+constexpr int kTotalWords = 2 * (1 + 256);  // u64 words of the totals
 constexpr int kMaxMergeBlocks = 4096;
 static_assert(MT == 256, "the merge kernel's final reduction keeps one class per thread");
 
@@ -73,52 +74,130 @@ __device__ __forceinline__ KeyPL new_key(const InsArgs& a, int64_t j) {
   return {a.priority[id], (uint32_t)a.length[id]};
 }
 
-// Threads 0 .. m-1: ins[j]. The next units + 1: desc[u]. The next 257: class
-// start c of the earlier sequence (the number of its entries with priority
-// < c). One more: the two length totals.
-__global__ __launch_bounds__(IT) void i_search(InsArgs a, int64_t units) {
-  const int64_t i = (int64_t)blockIdx.x * IT + threadIdx.x;
-  if (i < a.m) {
-    const KeyPL kj = new_key(a, i);
-    int64_t lo = 0, hi = a.n_old;  // upper bound: first earlier entry above kj
-    while (lo < hi) {
-      const int64_t mid = (lo + hi) >> 1;
-      if (key_le(old_key(a, mid), kj)) lo = mid + 1; else hi = mid;
+// Number of the n entries of a sorted sequence that are below the bound:
+// below(k) is true for the first ones only. Down to `wide` entries three are
+// probed per step, side by side: what a search takes is the chain of its
+// dependent loads, as long as the searches share the lines they read (the
+// upper steps of a long sequence; all steps of one in the caches).
+template <typename F>
+__device__ __forceinline__ int64_t count_first(int64_t n, int64_t wide, F&& below) {
+  int64_t lo = 0, hi = n;
+  while (hi - lo >= wide) {
+    const int64_t q = (hi - lo) >> 2;
+    const int64_t m1 = lo + q, m2 = m1 + q, m3 = m2 + q;
+    const bool b1 = below(m1), b2 = below(m2), b3 = below(m3);
+    lo = b3 ? m3 + 1 : b2 ? m2 + 1 : b1 ? m1 + 1 : lo;
+    hi = !b1 ? m1 : !b2 ? m2 : !b3 ? m3 : hi;
+  }
+  while (lo < hi) {
+    const int64_t mid = (lo + hi) >> 1;
+    if (below(mid)) lo = mid + 1; else hi = mid;
+  }
+  return lo;
+}
+
+// Number of earlier entries whose class is below c0 and below c1, found by the
+// whole wave (c0, c1 uniform): 64 entries are probed per step, so a search
+// over 2^26 entries is five steps of two dependent loads.
+__device__ __forceinline__ void class_starts(const InsArgs& a, uint32_t c0, uint32_t c1,
+                                             int64_t& s0, int64_t& s1) {
+  const int lane = lane_id();
+  int64_t lo[2] = {0, 0}, hi[2] = {a.n_old, a.n_old};
+  const uint32_t c[2] = {c0, c1};
+  while (lo[0] < hi[0] || lo[1] < hi[1]) {  // (uniform)
+    int64_t step[2];
+    bool below[2];
+#pragma unroll
+    for (int x = 0; x < 2; ++x) {
+      step[x] = max((hi[x] - lo[x]) >> 6, (int64_t)1);
+      const int64_t k = lo[x] + step[x] * (lane + 1) - 1;
+      below[x] = k < hi[x] &&
+                 (uint32_t)a.priority[clamp_id(a.order_old[min(k, a.n_old - 1)], a.n_old)] < c[x];
     }
-    a.ins[i] = (uint32_t)lo;
+#pragma unroll
+    for (int x = 0; x < 2; ++x) {
+      const int n = __popcll(__ballot(below[x]));
+      // the probes are ordered: the first n are below c, the next one is not
+      const int64_t first = lo[x] + step[x] * n;
+      if (n < kWave) hi[x] = min(hi[x], first + step[x] - 1);
+      lo[x] = min(first, hi[x]);
+    }
+  }
+  s0 = lo[0];
+  s1 = lo[1];
+}
+
+// By waves: 64 arrivals' ins[j] each; then 64 units' desc[u] each (units + 1 of
+// them); then one class start each (257: the number of earlier entries with
+// priority < c); the last ones the two length totals and the zeroing of the
+// schedule's totals, which the merge adds to.
+//
+// What bounds it is the chain of dependent cache misses of a search. An
+// earlier entry's key is two loads away (its id, then its rank and length) on
+// three lines. An arrival is therefore searched among its class's entries
+// only, whose lengths are the differences of neighbouring waits: one load on
+// one line, three probes side by side; the class's first and last entry come
+// from class_starts. 2^16 arrivals in 2^26 entries: 58 us by keys, one probe
+// per step; 45 us, some of it the write-back of the previous call's outputs.
+__global__ __launch_bounds__(IT) void i_search(InsArgs a, int64_t units) {
+  int64_t wv = (int64_t)blockIdx.x * (IT / kWave) +
+               __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
+  const int lane = lane_id();
+  const int64_t wa = (a.m + kWave - 1) / kWave;
+  if (wv < wa) {
+    const int64_t i = wv * kWave + lane;
+    const KeyPL kj = new_key(a, min(i, a.m - 1));
+    int64_t lo = 0, hi = 0;
+    uint64_t todo = ~0ull;
+    while (todo) {  // (uniform) a class of the wave's arrivals at a time, nearly always one
+      const uint32_t cls = (uint32_t)__builtin_amdgcn_readlane((int)kj.p, __builtin_ctzll(todo));
+      int64_t s0, s1;
+      class_starts(a, cls, cls + 1, s0, s1);
+      if (kj.p == cls) {
+        lo = s0;
+        hi = s1;
+      }
+      todo &= ~__ballot(kj.p == cls);
+    }
+    // the class's entries not longer; its last entry's length is not a
+    // difference inside the class, nor always inside the sequence
+    const int64_t at = lo + count_first(hi - lo, 4096, [&](int64_t k) {
+      const int64_t e = lo + k;
+      const uint64_t next = e + 1 < a.n_old ? (uint64_t)a.wait_old[e + 1]
+                                            : (uint64_t)a.wait_old[e] + old_key(a, e).l;
+      return next - (uint64_t)a.wait_old[e] <= (uint64_t)kj.l;
+    });
+    if (i < a.m) a.ins[i] = (uint32_t)at;
     return;
   }
-  int64_t r = i - a.m;
-  if (r <= units) {
+  wv -= wa;
+  const int64_t wu = (units + 1 + kWave - 1) / kWave;
+  if (wv < wu) {
+    const int64_t r = wv * kWave + lane;
+    if (r > units) return;
     // ins[j] <= k0 exactly when earlier entry k0 is above arrival j (the
     // earlier sequence is sorted), so c(k0) counts the arrivals below it
     const int64_t k0 = r * kInsUnit;
     uint64_t d = (uint64_t)a.m;
     if (k0 < a.n_old) {
       const KeyPL e = old_key(a, k0);
-      int64_t lo = 0, hi = a.m;
-      while (lo < hi) {
-        const int64_t mid = (lo + hi) >> 1;
-        if (key_lt(new_key(a, mid), e)) lo = mid + 1; else hi = mid;
-      }
       const uint32_t last = old_key(a, min(k0 + kInsUnit, a.n_old) - 1).p;
+      const int64_t lo = count_first(a.m, 4, [&](int64_t j) { return key_lt(new_key(a, j), e); });
       d = (uint64_t)lo | (uint64_t)e.p << 32 | (uint64_t)last << 40;
     }
     a.desc[r] = d;
     return;
   }
-  r -= units + 1;
-  if (r < kClassSlots) {
-    const uint32_t c = (uint32_t)r;
-    int64_t lo = 0, hi = a.n_old;  // first entry with priority >= c
-    while (lo < hi) {
-      const int64_t mid = (lo + hi) >> 1;
-      if (old_key(a, mid).p < c) lo = mid + 1; else hi = mid;
-    }
-    a.cs[r] = (uint32_t)lo;
+  wv -= wu;
+  if (wv < kClassSlots) {
+    int64_t s0, s1;
+    class_starts(a, (uint32_t)wv, (uint32_t)wv, s0, s1);
+    if (lane == 0) a.cs[wv] = (uint32_t)s0;
     return;
   }
-  if (r == kClassSlots) {
+  const int64_t r = (wv - kClassSlots) * kWave + lane;
+  if (r < kTotalWords) a.totals[r] = 0;
+  if (r == kTotalWords) {
     // total lengths: last wait + last length of each sequence
     a.lsum[0] = a.n_old > 0 ? (uint64_t)a.wait_old[a.n_old - 1] + old_key(a, a.n_old - 1).l : 0;
     a.lsum[1] = a.m > 0 ? (uint64_t)a.wait_m[a.m - 1] + new_key(a, a.m - 1).l : 0;
@@ -345,8 +424,11 @@ int64_t insert_units(int64_t n_old) { return (n_old + kInsUnit - 1) / kInsUnit; 
 
 hipError_t launch_insert(const InsArgs& a, hipStream_t st, hipEvent_t before, hipEvent_t after) {
   const int64_t units = insert_units(a.n_old);
-  const int64_t searches = a.m + units + 1 + kClassSlots + 1;
-  hipLaunchKernelGGL(i_search, dim3((unsigned)((searches + IT - 1) / IT)), dim3(IT), 0, st, a,
+  // waves of i_search (its sections, in order)
+  const int64_t waves = (a.m + kWave - 1) / kWave + (units + 1 + kWave - 1) / kWave +
+                        kClassSlots + (kTotalWords + 1 + kWave - 1) / kWave;
+  constexpr int WPB = IT / kWave;
+  hipLaunchKernelGGL(i_search, dim3((unsigned)((waves + WPB - 1) / WPB)), dim3(IT), 0, st, a,
                      units);
   static const int resident = merge_resident_blocks();
   const int64_t work = std::max(units, (a.m + kWave - 1) / kWave);  // in waves

@@ -289,7 +289,7 @@ struct InsArgs {
   uint64_t* sink;           // 16 bytes that absorb the stores of lanes without an entry
   int32_t* order;           // [n_old + m] the merged schedule
   int64_t* wait;
-  uint64_t* totals;         // (lo, hi) pairs, 1 + 256, zeroed by the caller
+  uint64_t* totals;         // (lo, hi) pairs, 1 + 256
 };
 
 // Units of kInsUnit earlier entries (desc holds one more entry).
