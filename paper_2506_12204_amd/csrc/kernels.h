@@ -261,7 +261,7 @@ void mark_stage(const StageEvents* ev, int stage, bool after, hipStream_t st);
 
 // The same schedule with one tile per workgroup, for queues of at most
 // kTileMaxItems requests (tile_sort.hip). Packed keys only (force_wide == 0).
-constexpr int kTileRows = 128;  // most tiles of such a queue
+constexpr int kTileRows = 256;  // most tiles of such a queue
 constexpr int64_t kTileMaxItems = (int64_t)kTileRows * 8192;
 hipError_t launch_tile_schedule(const GArgs& a, hipStream_t st, const StageEvents* ev);
 

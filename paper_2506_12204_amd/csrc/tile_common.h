@@ -177,8 +177,8 @@ struct PlaceLds {
 // wave*64*R + round*64 + lane, cv of them valid. pos0, wait0: output position
 // and wait of the tile's first item of the thread's digit. Positions of
 // `limit` and more are not written. WIDE_SUMS: a wave's waits may add up to
-// 2^64 and more (never for queues of at most 2^20 requests: 512 waits below
-// 2^51). `staged` is called once e is free to take other elements (the next
+// 2^64 and more (never for queues of at most 2^21 requests: 512 waits below
+// 2^52). `staged` is called once e is free to take other elements (the next
 // tile's, loaded while this one is placed). The LDS members may be used again
 // after the next barrier; clo/chi are complete after it.
 template <bool WIDE_SUMS, int R, typename Codec, typename Lds, typename Staged>

@@ -6,18 +6,20 @@
 // totals in the last pass), laid out for latency instead of bandwidth: such a
 // queue lies in the caches, so what counts is the number of launches and the
 // length of each kernel's chain, not the bytes. Tiles of 1024 to 8192
-// requests give 17 to 128 workgroups of 16 waves, elements are whole
+// requests give 17 to 256 workgroups of 16 waves, elements are whole
 // u64 (key above id, nothing to look up by position), and the offsets of a
 // tile are summed by the workgroup that needs them from the other tiles'
 // count rows, so no scan is launched between a count and its scatter:
 //   t_count   ranges and first-digit counts of every tile
 //   t_first   the plan from the ranges, the tile's offsets, first scatter
-//   t_histF   middle passes of wide keys, then final-digit counts and length
-//             sums of every tile
+//   t_mid     middle passes of wide keys (returns at once for two-pass keys)
+//   t_histF   final-digit counts and length sums of every tile
 //   t_final   offsets, order, waits; the last workgroup adds up the totals
 // Measured: a queue of 50,003 requests 156 us in the big-tile path's nine
 // launches (16K-item tiles: 4 workgroups), 28 us here; one of 2^20 76 us (64
 // workgroups), 51 us here.
+#include <algorithm>
+
 #include "tile_common.h"
 
 namespace semsched {
@@ -246,14 +248,14 @@ struct TileCountLds {
 
 // Digit counts of one tile of middle pass s.
 template <int R, typename Codec>
-__device__ void tile_count_mid(const GArgs& a, int s, TileCountLds& sh) {
+__device__ void tile_count_mid(const GArgs& a, int s, int me, TileCountLds& sh) {
   const int t = threadIdx.x;
   const uint32_t copy = (uint32_t)lane_id() & (kCountCopies - 1);
   const uint32_t dshift = a.plan->shift[s];
   Codec kc;
   kc.init(a.d0, a.plan);
   const uint64_t* in = a.keys[(s - 1) & 1];
-  const int64_t first = (int64_t)blockIdx.x * (TT * R);
+  const int64_t first = (int64_t)me * (TT * R);
   uint64_t e[R];
 #pragma unroll
   for (int r = 0; r < R; ++r) e[r] = in[min(first + r * TT + t, a.n - 1)];
@@ -265,15 +267,14 @@ __device__ void tile_count_mid(const GArgs& a, int s, TileCountLds& sh) {
     atomicAdd(&sh.cnt[d * kCountCopies + copy], first + r * TT + t < a.n ? 1u : 0u);
   }
   block_sync();
-  write_counts(sh.cnt, count_rows(a) + (size_t)blockIdx.x * kMaxBins);
+  write_counts(sh.cnt, count_rows(a) + (size_t)me * kMaxBins);
 }
 
 // Scatter of one tile of middle pass s.
 template <int R, typename Codec>
-__device__ void tile_scatter_mid(const GArgs& a, int s, TileFirstLds<R>& sh) {
+__device__ void tile_scatter_mid(const GArgs& a, int s, int me, int rows, TileFirstLds<R>& sh) {
   const int t = threadIdx.x;
   const int w = wave_no();
-  const int me = (int)blockIdx.x;
   const uint32_t dshift = a.plan->shift[s];
   constexpr uint32_t M = kMaxBins - 1;
   Codec kc;
@@ -286,7 +287,7 @@ __device__ void tile_scatter_mid(const GArgs& a, int s, TileFirstLds<R>& sh) {
   uint64_t e[R];
 #pragma unroll
   for (int r = 0; r < R; ++r) e[r] = in[first + min(j0 + r * kWave, cv - 1)];
-  fold_rows(a, me, (int)gridDim.x, sh.u.fold.before, sh.u.fold.after);
+  fold_rows(a, me, rows, sh.u.fold.before, sh.u.fold.after);
   clear_row(sh.cnt[w]);
   block_sync();
   const uint32_t mine = fold_offset(sh.u.fold.before, sh.u.fold.after, sh.scan32);
@@ -320,30 +321,58 @@ union TileMidLds {
   TileFirstLds<R> scatter;
 };
 
+// A phase of middle pass s over the tiles me, me + step, ...
 template <int R>
-__device__ void mid_count(const GArgs& a, int s, TileMidLds<R>& sh) {
-  if (a.plan->W == 32) tile_count_mid<R, KeyCodec32>(a, s, sh.count);
-  else tile_count_mid<R, KeyCodec64>(a, s, sh.count);
+__device__ void mid_count(const GArgs& a, int s, int me, int step, TileMidLds<R>& sh) {
+  const int rows = (int)((a.n + TT * R - 1) / (TT * R));
+  for (; me < rows; me += step) {
+    if (a.plan->W == 32) tile_count_mid<R, KeyCodec32>(a, s, me, sh.count);
+    else tile_count_mid<R, KeyCodec64>(a, s, me, sh.count);
+    block_sync();  // the counts are read before they are cleared
+  }
 }
 template <int R>
-__device__ void mid_scatter(const GArgs& a, int s, TileMidLds<R>& sh) {
-  if (a.plan->W == 32) tile_scatter_mid<R, KeyCodec32>(a, s, sh.scatter);
-  else tile_scatter_mid<R, KeyCodec64>(a, s, sh.scatter);
+__device__ void mid_scatter(const GArgs& a, int s, int me, int step, TileMidLds<R>& sh) {
+  const int rows = (int)((a.n + TT * R - 1) / (TT * R));
+  for (; me < rows; me += step) {
+    if (a.plan->W == 32) tile_scatter_mid<R, KeyCodec32>(a, s, me, rows, sh.scatter);
+    else tile_scatter_mid<R, KeyCodec64>(a, s, me, rows, sh.scatter);
+    block_sync();  // the stage is read before it is written
+  }
+}
+
+// All middle passes in one launch with bounded grid barriers between their
+// phases, as g_mid does for the big tiles; it returns at once for two-pass
+// keys. At most 64 workgroups (128 beyond 2^20 requests), as many as the
+// big-tile path would use at these sizes, so that as many calls on different
+// streams can be resident side by side.
+template <int R>
+__global__ __launch_bounds__(TT) void t_mid(GArgs a) {
+  __shared__ TileMidLds<R> sh;
+  const Plan* pl = a.plan;
+  if (!pl->ok || pl->nscatter <= 2) return;
+  uint32_t gen = 0;
+  for (int s = 1; s < (int)pl->nscatter - 1; ++s) {
+    if (s > 1 && !grid_barrier(a, ++gen)) return;
+    mid_count<R>(a, s, (int)blockIdx.x, (int)gridDim.x, sh);
+    if (!grid_barrier(a, ++gen)) return;
+    mid_scatter<R>(a, s, (int)blockIdx.x, (int)gridDim.x, sh);
+  }
 }
 
 // The middle passes as separate launches (keys known to be wide, and a schedule
-// run again after the barrier below gave up).
+// run again after the barrier gave up).
 template <int R>
 __global__ __launch_bounds__(TT) void t_mid_count(GArgs a, int s) {
   __shared__ TileMidLds<R> sh;
   if (!a.plan->ok || s >= (int)a.plan->nscatter - 1) return;
-  mid_count<R>(a, s, sh);
+  mid_count<R>(a, s, (int)blockIdx.x, (int)gridDim.x, sh);
 }
 template <int R>
 __global__ __launch_bounds__(TT) void t_mid_scatter(GArgs a, int s) {
   __shared__ TileMidLds<R> sh;
   if (!a.plan->ok || s >= (int)a.plan->nscatter - 1) return;
-  mid_scatter<R>(a, s, sh);
+  mid_scatter<R>(a, s, (int)blockIdx.x, (int)gridDim.x, sh);
 }
 
 // Final-digit counts and length sums of one tile of the last pass's input.
@@ -363,30 +392,12 @@ __device__ void tile_histF(const GArgs& a, uint64_t* s_bin) {
               final_rows(a) + (size_t)blockIdx.x * kMaxBins);
 }
 
-// The final digit's counts, after any middle passes that were not launched
-// on their own (`mids`): those run here with bounded grid barriers between
-// their phases (at most kTileRows workgroups, all resident on an idle
-// device), as g_mid does for the big tiles. A launch of their own, which
-// returns at once for two-pass keys, would cost every call about 3 us.
 template <int R>
-__global__ __launch_bounds__(TT) void t_histF(GArgs a, int mids) {
-  __shared__ union {
-    TileMidLds<R> mid;
-    uint64_t bin[kFinalSlots];
-  } sh;
-  const Plan* pl = a.plan;
-  if (!pl->ok) return;
-  if (mids && pl->nscatter > 2) {
-    uint32_t gen = 0;
-    for (int s = 1; s < (int)pl->nscatter - 1; ++s) {
-      mid_count<R>(a, s, sh.mid);
-      if (!grid_barrier(a, ++gen)) return;
-      mid_scatter<R>(a, s, sh.mid);
-      if (!grid_barrier(a, ++gen)) return;
-    }
-  }
-  if (pl->W == 32) tile_histF<R, KeyCodec32>(a, sh.bin);
-  else tile_histF<R, KeyCodec64>(a, sh.bin);
+__global__ __launch_bounds__(TT) void t_histF(GArgs a) {
+  __shared__ uint64_t s_bin[kFinalSlots];
+  if (!a.plan->ok) return;
+  if (a.plan->W == 32) tile_histF<R, KeyCodec32>(a, s_bin);
+  else tile_histF<R, KeyCodec64>(a, s_bin);
 }
 
 template <int R>
@@ -554,9 +565,12 @@ hipError_t launch_tiles(const GArgs& a, hipStream_t st, const StageEvents* ev) {
       hipLaunchKernelGGL(t_mid_count<R>, g, dim3(TT), 0, st, a, s);
       hipLaunchKernelGGL(t_mid_scatter<R>, g, dim3(TT), 0, st, a, s);
     }
+  } else {
+    const unsigned most = a.n <= (1ll << 20) ? 64 : 128;
+    hipLaunchKernelGGL(t_mid<R>, dim3(std::min(g.x, most)), dim3(TT), 0, st, a);
   }
-  hipLaunchKernelGGL(t_histF<R>, g, dim3(TT), 0, st, a, a.split_mid ? 0 : 1);
   mark_stage(ev, 6, true, st);
+  hipLaunchKernelGGL(t_histF<R>, g, dim3(TT), 0, st, a);
   mark_stage(ev, 2, false, st);
   hipLaunchKernelGGL(t_final<R>, g, dim3(TT), 0, st, a);
   mark_stage(ev, 2, true, st);
@@ -569,10 +583,12 @@ hipError_t launch_tile_schedule(const GArgs& a, hipStream_t st, const StageEvent
   // Small tiles make more workgroups and shorter chains in each, but every
   // workgroup reads every tile's count rows: 64 tiles are best up to 2^18
   // requests (262,144: 36.8 us in 64 tiles, 37.9 in 128, 44.7 in 256), 128
-  // above (524,288: 45.0 us in 64, 42.8 in 128, 48.0 in 256).
+  // above (524,288: 45.0 us in 64, 42.8 in 128, 48.0 in 256), and from 2^20 as
+  // many of 8192 as it takes, up to one per CU (2^21: 65 us in 256, 79 in the
+  // big-tile path; 2,500,000: 114 in 306, 79).
   if (a.n <= 64ll * TT) return launch_tiles<1>(a, st, ev);
   if (a.n <= 64ll * TT * 2) return launch_tiles<2>(a, st, ev);
-  if (a.n <= (int64_t)kTileRows * TT * 4) return launch_tiles<4>(a, st, ev);
+  if (a.n <= 128ll * TT * 4) return launch_tiles<4>(a, st, ev);
   return launch_tiles<8>(a, st, ev);
 }
 

@@ -1,5 +1,5 @@
 """GPU parity of the two paths a queue above the LDS size can take: one tile
-per workgroup (up to 2^20 requests) and big tiles (SEMSCHED_NO_TILES=1 sends
+per workgroup (up to 2^21 requests) and big tiles (SEMSCHED_NO_TILES=1 sends
 the same queues there). Integers throughout, so every comparison is exact."""
 
 import numpy as np
@@ -13,10 +13,10 @@ pytestmark = [pytest.mark.gpu,
               pytest.mark.skipif(not gpu_available(), reason="needs a GPU")]
 
 # one past the LDS size; around the limits of the tile sizes (64 tiles of 1024
-# and 2048, 128 of 4096 and 8192); a last tile of one request; the last size
-# of the path and the first beyond it
+# and 2048, 128 of 4096, 256 of 8192); a last tile of one request; the last
+# size of the path and the first beyond it
 SIZES = [16385, 65536, 65537, 131073, 262145, 524288, 524289, (1 << 20) - 1, 1 << 20,
-         (1 << 20) + 1]
+         (1 << 20) + 1, (1 << 21) - 1, 1 << 21, (1 << 21) + 1]
 
 
 @pytest.fixture(scope="module", autouse=True)
@@ -43,7 +43,7 @@ def test_sizes(n, monkeypatch):
 # it takes its own width)
 @pytest.mark.parametrize("classes,max_len", [(1, 1000), (9, 4096), (5, 32768), (256, 4095),
                                              (9, 2_000_000), (5, 2**31 - 1), (256, 2**31 - 1)])
-@pytest.mark.parametrize("n", [20001, 150000])
+@pytest.mark.parametrize("n", [20001, 150000, 1_200_000])
 def test_key_widths(n, classes, max_len, monkeypatch):
     p, l = fuzz_queue(n, seed=classes, classes=classes, max_len=max_len, tie_frac=0.1, min_len=0)
     check(p, l, f"widths {classes}x{max_len}", monkeypatch)
@@ -52,8 +52,8 @@ def test_key_widths(n, classes, max_len, monkeypatch):
 
 
 def test_largest_sums(monkeypatch):
-    # 2^20 lengths of 2^31 - 1: tile sums at their limit, totals above 2^64
-    n = 1 << 20
+    # 2^21 lengths of 2^31 - 1: wave sums near 2^61, totals above 2^64
+    n = 1 << 21
     check(np.zeros(n, np.uint8), np.full(n, 2**31 - 1, np.int32), "largest sums", monkeypatch)
 
 
