@@ -2262,9 +2262,10 @@ __device__ __forceinline__ void load_final_compact(const uint32_t* keys, int64_t
     e[r] = __builtin_amdgcn_raw_buffer_load_b32(rk, (lane + r * kWave) * 4, 0, 0);
 }
 
-// WIN_LDS: the block's sub-bucket starts fit the LDS window and n is below
-// kBufferStoreItems; else the starts are read from global memory and the
-// outputs stored through plain pointers (separate kernels, see g_final_cglb).
+// WIN_LDS: every block's sub-bucket starts fit the LDS window and n is below
+// kBufferStoreItems (Plan::cglb is 0); else the starts are read from global
+// memory and the outputs stored through plain pointers (separate kernels, see
+// g_final_cglb).
 // PAY: the elements carry the caller's ranks (Plan::pay); the totals are
 // split by those instead of by the ordering classes.
 template <bool WIN_LDS, bool PAY>
@@ -2331,7 +2332,6 @@ __device__ void final_compact(const GArgs& a, int g, FinalCompactShared& sh) {
   const int d_hi = hi > lo ? bucket_of(sh.bstart, nd, (uint32_t)(hi - 1)) : 0;
   const int win0 = d_lo << kpb;
   const int wn = (d_hi - d_lo + 1) << kpb;
-  if (WIN_LDS != (wn <= kWinCap && a.n < kBufferStoreItems)) return;  // the other kernel's block
   if (WIN_LDS) {
     for (int j = t; j < wn; j += NTB)
       sh.win[j] = sh.bstart[(win0 + j) >> kpb] + a.sub_start[win0 + j];
@@ -2621,18 +2621,21 @@ __global__ __launch_bounds__(NTB) void g_final_big(GArgs a) {
   const Plan* pl = a.plan;
   if (!pl->ok) return;
   if (pl->compact) {
-    if (!pl->pay) final_compact<true, false>(a, blockIdx.x, sh.compact);
+    if (!pl->pay && !pl->cglb) final_compact<true, false>(a, blockIdx.x, sh.compact);
     return;
   }
   if (!use_big_final(pl)) return;
   final_big<false>(a, blockIdx.x, sh.big);
 }
 
-// The compact final pass for the blocks whose sub-bucket starts do not fit
-// the LDS window (rare: a block must span hundreds of first-digit buckets);
-// they are searched in global memory. A kernel of its own, so that the common
+// The compact final pass of queues some block of which spans more sub-buckets
+// than the LDS window holds (long tails of lengths: hundreds of first-digit
+// buckets in a block); the starts are searched in global memory, in every
+// block of the queue. With only the blocks that need it here, the others ran
+// first in g_final_big and these few took as long again: 2^26 requests with
+// lognormal lengths 329 + 388 us, all of them here XX us. A kernel of its own, so that the common
 // kind's loop holds no global loads besides the element prefetch and the
-// compiler's wait counts stay exact there. Returns at once for other blocks.
+// compiler's wait counts stay exact there.
 __global__ __launch_bounds__(NTB) void g_final_cglb(GArgs a) {
   __shared__ union {
     FinalCompactShared compact;
@@ -2654,7 +2657,7 @@ __global__ __launch_bounds__(NTB) void g_final_cglb(GArgs a) {
 __global__ __launch_bounds__(NTB) void g_final_pay(GArgs a) {
   __shared__ FinalCompactShared sh;
   const Plan* pl = a.plan;
-  if (!pl->ok || !pl->compact || !pl->pay) return;
+  if (!pl->ok || !pl->compact || !pl->pay || pl->cglb) return;
   final_compact<true, true>(a, blockIdx.x, sh);
 }
 

@@ -170,7 +170,7 @@ struct Plan {
                       // final digit (the rank takes no part in the order)
   uint32_t pay_shift; // bit of a compact element where that rank starts
   uint32_t cglb;      // compact: 1 if some block of the final pass needs the
-                      // global-window kernel (sub-bucket starts beyond the LDS
+                      // global-window kernel, which then takes every block (sub-bucket starts beyond the LDS
                       // window, or a queue too long for buffer-resource stores)
   uint32_t sum64;     // batched long queues: a wave's waits add up below 2^64
   uint32_t shift[kMaxScatter];  // digit = (u2 >> shift) & (bins - 1), passes >= 1
