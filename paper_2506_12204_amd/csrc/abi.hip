@@ -94,6 +94,13 @@ int no_tiles() {
   return (e && e[0] == '1') ? 1 : 0;
 }
 
+// Queues that one tile per workgroup covers take the latency-oriented path; the
+// knobs that name a layout of the big-tile path keep that path.
+bool takes_tiles(int64_t n) {
+  return needs_global(n) && n <= kTileMaxItems && !no_tiles() && !force_wide() && !no_compact() &&
+         d0_bits() == 10;
+}
+
 // SEMSCHED_SPLIT_MID=1 runs the middle passes as separate launches per phase
 // (the form a blocking call falls back to when the grid barrier gives up).
 int split_mid_forced() {
@@ -204,12 +211,13 @@ int run_blocking(void* ws, hipStream_t st, F enqueue) {
 }
 
 // Enqueue one queue (any n >= 0). Arguments already checked.
-// payload / pay_pmax (optional, SJF): ranks carried through the long-queue
-// path and their largest value; see GArgs. wide_keys: the caller expects key
+// carry_ranks, pay_pmax (SJF, queues above the LDS size): the order ignores the
+// ranks, which the sort carries to split the totals by where it can; see GArgs.
+// wide_keys: the caller expects key
 // ranges that need middle passes.
 int enqueue_queue(const uint8_t* p, const int32_t* l, int64_t n, int32_t num_classes,
                   int32_t* order, int64_t* wait, sem_i128* totals, void* ws, hipStream_t st,
-                  const uint8_t* payload = nullptr, const uint32_t* pay_pmax = nullptr,
+                  bool carry_ranks = false, uint32_t* pay_pmax = nullptr,
                   bool wide_keys = false) {
   char* base = static_cast<char*>(ws);
   uint32_t* flags = reinterpret_cast<uint32_t*>(base);
@@ -278,7 +286,7 @@ int enqueue_queue(const uint8_t* p, const int32_t* l, int64_t n, int32_t num_cla
   g.chunk_part = reinterpret_cast<uint32_t*>(base + L.chunk_part);
   g.sub_start = reinterpret_cast<uint32_t*>(base + L.sub_start);
   g.msync = reinterpret_cast<MidSync*>(base + L.msync);
-  g.payload = payload;
+  g.payload = carry_ranks ? p : nullptr;
   g.pay_pmax = pay_pmax;
   StageEvents ev = {};
   bool armed = false;
@@ -291,10 +299,7 @@ int enqueue_queue(const uint8_t* p, const int32_t* l, int64_t n, int32_t num_cla
       trace_slots().before[k] = trace_slots().after[k] = nullptr;
     }
   }
-  // Queues that one tile per workgroup covers take the latency-oriented path;
-  // the knobs that name a layout of the big-tile path keep that path.
-  const bool tiled = n <= kTileMaxItems && !no_tiles() && !g.force_wide && !no_compact() &&
-                     g.d0 == 10;
+  const bool tiled = takes_tiles(n);
   if (tiled) g.chunked = 0;
   return (tiled ? launch_tile_schedule(g, st, armed ? &ev : nullptr)
                 : launch_global_schedule(g, st, armed ? &ev : nullptr)) == hipSuccess
@@ -490,11 +495,18 @@ int enqueue_cost_schedule(const uint8_t* p, const int32_t* prompt, const int32_t
   if (launch_service(a, st, before, after) != hipSuccess) return SEM_EDEVICE;
   // service times span about 30 bits: two or more middle passes
   const int rc = enqueue_queue(p, a.service, n, SEM_MAX_CLASSES, order, wait, totals, ws, st,
-                               nullptr, nullptr, true);
+                               false, nullptr, true);
   if (rc != SEM_OK) return rc;
   return launch_merge_flags(reinterpret_cast<uint32_t*>(base), cflags, st) == hipSuccess
              ? SEM_OK
              : SEM_EDEVICE;
+}
+
+// The tile path always splits SJF's totals itself: the stage is empty.
+hipError_t no_class_totals(hipStream_t st, hipEvent_t before, hipEvent_t after) {
+  if (before) (void)hipEventRecord(before, st);
+  if (after) (void)hipEventRecord(after, st);
+  return hipSuccess;
 }
 
 int enqueue_policy(int policy, const uint8_t* p, const int32_t* l, int64_t n, int32_t* order,
@@ -528,20 +540,24 @@ int enqueue_policy(int policy, const uint8_t* p, const int32_t* l, int64_t n, in
   a.ctot_len = reinterpret_cast<uint64_t*>(base + L.ctot_len);
   a.part = reinterpret_cast<uint64_t*>(base + L.part);
   a.sink = reinterpret_cast<uint64_t*>(base + L.sink);
-  if (policy == SEM_POLICY_SJF) {
-    // The order by (length, id): the queue kernels with every rank read as
-    // 0. The largest rank comes first, so that a long queue's compact
-    // elements can carry the ranks to its final pass (then that pass splits
-    // the totals; else s_classes does, after it).
+  if (policy == SEM_POLICY_SJF && needs_global(n)) {
+    // The order by (length, id): the sort takes every ordering rank as 0 and
+    // carries the ranks along (then its final pass splits the totals; else
+    // s_classes does, after it).
+    const int rc = enqueue_queue(p, l, n, SEM_MAX_CLASSES, order, wait, totals, ws, st, true,
+                                 a.pmax);
+    if (rc != SEM_OK) return rc;
+    a.pay = &reinterpret_cast<const Plan*>(base + layout_for(n).plan)->pay;
+  } else if (policy == SEM_POLICY_SJF) {
+    // one workgroup's LDS: the queue kernel on a zeroed rank array
     uint32_t* zeros = reinterpret_cast<uint32_t*>(base + L.zeros);
     if (launch_fill_zero(zeros, ((size_t)n + 3) / 4, st) != hipSuccess ||
         launch_fill_zero(a.pmax, 1, st) != hipSuccess ||
         launch_policy_range(a, st) != hipSuccess)
       return SEM_EDEVICE;
     const int rc = enqueue_queue(reinterpret_cast<const uint8_t*>(zeros), l, n, SEM_MAX_CLASSES,
-                                 order, wait, totals, ws, st, p, a.pmax);
+                                 order, wait, totals, ws, st);
     if (rc != SEM_OK) return rc;
-    if (needs_global(n)) a.pay = &reinterpret_cast<const Plan*>(base + layout_for(n).plan)->pay;
   } else if (launch_fill_zero(flags, 1, st) != hipSuccess ||
              launch_fill_zero(a.pmax, 1, st) != hipSuccess ||
              launch_fill_zero(tot32, tot_words, st) != hipSuccess) {
@@ -556,6 +572,7 @@ int enqueue_policy(int policy, const uint8_t* p, const int32_t* l, int64_t n, in
   }
   hipError_t e = policy == SEM_POLICY_FCFS   ? launch_fcfs(a, st, before, after)
                  : policy == SEM_POLICY_HPJF ? launch_hpjf(a, st, before, after)
+                 : takes_tiles(n)            ? no_class_totals(st, before, after)
                                              : launch_class_totals(a, st, before, after);
   return e == hipSuccess ? SEM_OK : SEM_EDEVICE;
 }

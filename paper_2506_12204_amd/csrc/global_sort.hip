@@ -71,6 +71,7 @@ __device__ void reset_call_state(const GArgs& a) {
     a.plan->ok = 0;
     a.plan->pay = 0;
     a.plan->pay_shift = 32;
+    if (a.payload) *a.pay_pmax = 0;
   }
   for (int i = t; i < kMaxScatter * kMaxBins; i += THREADS) a.hist_cnt[i] = 0;
   for (int i = t; i < kMaxBins; i += THREADS) a.hist_w[i] = 0;
@@ -117,15 +118,16 @@ __device__ __forceinline__ void row_range(const GArgs& a, const Split& sp, int r
 // Reduce the block ranges and turn them into the Plan (one workgroup).
 __device__ void write_plan(const GArgs& a, int G) {
   __shared__ uint32_t s_red[4][SCT_WAVES];
-  uint32_t pl_ = 0xffu, ph = 0, ll = 0xffffffffu, lh = 0;
+  const bool carried = a.payload != nullptr;
+  uint32_t pl_ = carried ? 0u : 0xffu, ph = 0, ll = 0xffffffffu, lh = 0;
   for (int g = threadIdx.x; g < G; g += SCT) {
     const uint32_t* r = a.block_ranges + 4 * (size_t)g;
-    pl_ = min(pl_, r[0]);
+    pl_ = carried ? max(pl_, r[0]) : min(pl_, r[0]);  // (the largest carried rank)
     ph = max(ph, r[1]);  // bit 31: the block found a range error
     ll = min(ll, r[2]);
     lh = max(lh, r[3]);
   }
-  pl_ = wave_min_u32(pl_);
+  pl_ = carried ? wave_max_u32(pl_) : wave_min_u32(pl_);
   ph = wave_max_u32(ph);
   ll = wave_min_u32(ll);
   lh = wave_max_u32(lh);
@@ -138,9 +140,9 @@ __device__ void write_plan(const GArgs& a, int G) {
   }
   block_sync();
   if (threadIdx.x != 0) return;
-  uint32_t gpmin = 0xffu, gpmax = 0, glmin = 0xffffffffu, glmax = 0;
+  uint32_t gpmin = carried ? 0u : 0xffu, gpmax = 0, glmin = 0xffffffffu, glmax = 0;
   for (int i = 0; i < SCT_WAVES; ++i) {
-    gpmin = min(gpmin, s_red[0][i]);
+    gpmin = carried ? max(gpmin, s_red[0][i]) : min(gpmin, s_red[0][i]);
     gpmax = max(gpmax, s_red[1][i]);
     glmin = min(glmin, s_red[2][i]);
     glmax = max(glmax, s_red[3][i]);
@@ -151,12 +153,17 @@ __device__ void write_plan(const GArgs& a, int G) {
     pl->ok = 0;
     return;
   }
+  const uint32_t pay_max = gpmin;
+  if (carried) {
+    *a.pay_pmax = pay_max;
+    gpmin = 0;
+  }
   make_plan((uint32_t)a.d0, (uint32_t)(a.n - 1), a.force_wide != 0, a.chunked != 0, gpmin,
             gpmax, glmin, glmax, pl);
   // carried ranks: above the final digit's bits, if they fit the u32 element
   if (pl->compact && a.payload) {
     const uint32_t at = kChunkBits + pl->nbits[1];
-    if (at + bit_width32(*a.pay_pmax) <= 32) {
+    if (at + bit_width32(pay_max) <= 32) {
       pl->pay = 1;
       pl->pay_shift = at;
     }
@@ -252,9 +259,12 @@ __global__ __launch_bounds__(HT) void g_hist0(GArgs a, int vec_ok) {
       ph = max(ph, s_red[3][i] & 0xffu);
       bb |= s_red[3][i] >> 31;
     }
+    // (an empty block leaves the neutral values). Carried ranks take no part
+    // in the order: the ordering ranks are all 0, and the first word holds the
+    // largest carried rank.
     uint32_t* r = a.block_ranges + 4 * (size_t)g;
-    r[0] = pl;  // an empty block leaves the neutral values
-    r[1] = ph | (bb << 31);
+    r[0] = a.payload ? ph : pl;
+    r[1] = (a.payload ? 0u : ph) | (bb << 31);
     r[2] = bl;
     r[3] = bh;
   }
@@ -541,7 +551,7 @@ __device__ void scatter_block(const GArgs& a, int s, int g, Split sp, ScatterSha
       if (il < cv) {
         const int64_t i = tb + il;
         if (FIRST) {
-          key[r] = kc.make(a.priority[i], (uint32_t)a.length[i]);
+          key[r] = kc.make(a.payload ? 0u : a.priority[i], (uint32_t)a.length[i]);
           id[r] = (uint32_t)i;
         } else if (packed) {
           const uint64_t e = keys_in[i];
@@ -616,12 +626,13 @@ constexpr int kLoadStream = 2;
 // Inputs of one big tile of `cnt` items starting at item tb, round-major per
 // wave (round r of wave w holds items w*64*R1 + r*64 + lane). Items past the
 // tile's end read as zero.
-__device__ __forceinline__ void load_first(const GArgs& a, const uint8_t* pri, int64_t tb, int cnt,
+// With `ranks` false they read as zero too (an empty range, no memory access).
+__device__ __forceinline__ void load_first(const GArgs& a, bool ranks, int64_t tb, int cnt,
                                            uint32_t (&pv)[R1], uint32_t (&lv)[R1]) {
   const int wb = wave_id() * kWave * R1;
   // items of this wave's share (uniform; stated so the descriptor stays scalar)
   const int lim = __builtin_amdgcn_readfirstlane(max(0, min(cnt - wb, kWave * R1)));
-  const __amdgpu_buffer_rsrc_t rp = raw_rsrc(pri + tb + wb, (uint32_t)lim);
+  const __amdgpu_buffer_rsrc_t rp = raw_rsrc(a.priority + tb + wb, ranks ? (uint32_t)lim : 0u);
   const __amdgpu_buffer_rsrc_t rl = raw_rsrc(a.length + tb + wb, (uint32_t)lim * 4u);
   const int lane = lane_id();
 #pragma unroll
@@ -646,7 +657,7 @@ __device__ __forceinline__ void clear_wave_counters(uint16_t* cnt) {
 // low kChunkBits bits of the id); the key ranked and staged is then
 // u2 << D0 | first digit instead of the packed key.
 // PAY (compact only): the ordering ranks are all zero (u2 = h) and the
-// caller's ranks (GArgs::payload) ride along: bits 24 and up of the staged
+// caller's ranks ride along: bits 24 and up of the staged
 // key, then bits pay_shift and up of the element.
 template <int D0, bool COMPACT, bool PAY>
 __device__ void first_fast(const GArgs& a, int g, FirstFastShared<D0>& sh) {
@@ -665,7 +676,9 @@ __device__ void first_fast(const GArgs& a, int g, FirstFastShared<D0>& sh) {
   const uint32_t hoff = pl->hmin << D0;
   const uint32_t H = pl->H;
   const uint32_t pay_shift = pl->pay_shift;
-  const uint8_t* pri = PAY ? a.payload : a.priority;
+  // carried ranks that the elements have no room for are not read: the
+  // ordering ranks are 0
+  const bool ranks = PAY || !a.payload;
   uint64_t* out = a.keys[0];
   uint32_t* out32 = reinterpret_cast<uint32_t*>(a.keys[0]);
   uint16_t* mycnt = sh.cnt[w];
@@ -733,13 +746,13 @@ __device__ void first_fast(const GArgs& a, int g, FirstFastShared<D0>& sh) {
     for (int r = 0; r < R1; ++r) rk[r] = rank_round_mask(key[r] & M0, masks, mycnt);
   };
 
-  load_first(a, pri, lo, tile_items(lo), pv, lv);
+  load_first(a, ranks, lo, tile_items(lo), pv, lv);
   rank_tile(tile_items(lo));
   for (int64_t tb = lo; tb < hi; tb += T1) {
     const int cv = tile_items(tb);
     const bool more = tb + T1 < hi;
     // the next tile's inputs load while this one is offset, staged and written
-    if (more) load_first(a, pri, tb + T1, tile_items(tb + T1), pv, lv);
+    if (more) load_first(a, ranks, tb + T1, tile_items(tb + T1), pv, lv);
     block_sync();  // every wave's counters are complete
 
     uint32_t cw[OWN][NW], tot[OWN];
@@ -2633,7 +2646,7 @@ __global__ __launch_bounds__(NTB) void g_final_big(GArgs a) {
 // buckets in a block); the starts are searched in global memory, in every
 // block of the queue. With only the blocks that need it here, the others ran
 // first in g_final_big and these few took as long again: 2^26 requests with
-// lognormal lengths 329 + 388 us, all of them here XX us. A kernel of its own, so that the common
+// lognormal lengths 1109 us, all of them here 814 us. A kernel of its own, so that the common
 // kind's loop holds no global loads besides the element prefetch and the
 // compiler's wait counts stay exact there.
 __global__ __launch_bounds__(NTB) void g_final_cglb(GArgs a) {

@@ -172,6 +172,7 @@ struct Plan {
   uint32_t cglb;      // compact: 1 if some block of the final pass needs the
                       // global-window kernel, which then takes every block (sub-bucket starts beyond the LDS
                       // window, or a queue too long for buffer-resource stores)
+  uint32_t pay_max;   // tile path: the largest carried rank (pay set)
   uint32_t sum64;     // batched long queues: a wave's waits add up below 2^64
   uint32_t shift[kMaxScatter];  // digit = (u2 >> shift) & (bins - 1), passes >= 1
   uint32_t nbits[kMaxScatter];
@@ -229,12 +230,12 @@ struct GArgs {
                         // chunk boundary k's block that lie below the boundary
   uint32_t* sub_start;  // [kMaxBins][Kp] start of sub-bucket (digit d, chunk k)
                         // relative to bucket d's start; k >= K hold the bucket size
-  // Optional (SJF): ranks carried through the sort but not ordered by, and
-  // their largest value (written by an earlier kernel). When the compact
-  // layout has room for them, the final pass splits the totals by these
-  // ranks instead of by `priority`.
+  // SJF (payload == priority, else null): the ranks take no part in the order
+  // (every ordering rank is 0) but are carried through the sort where the
+  // elements have room for them; the totals are then split by them in the
+  // final pass (Plan::pay). Their largest value goes to pay_pmax.
   const uint8_t* payload;
-  const uint32_t* pay_pmax;
+  uint32_t* pay_pmax;
 };
 
 // Optional events recorded around one stage's kernel (null: not armed).

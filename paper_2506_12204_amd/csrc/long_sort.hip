@@ -529,7 +529,7 @@ __device__ void long_final(const BArgs& a, Codec kc, uint32_t lo, uint32_t hi,
     };
     const int64_t qfirst = cur.first - cur.lo;  // the queue's first request
     set_queue(kc, a, cur);
-    place_tile<WIDE_SUMS>(kc, dig, small, e, cur.cnt, pos0, w0, a.order + qfirst,
+    place_tile<WIDE_SUMS, false>(kc, dig, small, e, cur.cnt, pos0, w0, a.order + qfirst,
                           a.wait + qfirst, limit, sh, next);
   }
   block_sync();

@@ -41,13 +41,17 @@ struct TileRanges {
     pmin = min(pmin, in ? p : 0xffu);
     pmax = max(pmax, in ? p : 0u);
   }
-  // The workgroup's ranges to out[0 .. 3]. Holds a barrier.
-  __device__ __forceinline__ void write(uint32_t (*red)[TWV], uint32_t* out);
+  // The workgroup's ranges to out[0 .. 3]. Holds a barrier. (Carried ranks:
+  // the caller adds rank 0 and sets pmin to the largest carried rank, which
+  // then reduces by its maximum.)
+  __device__ __forceinline__ void write(uint32_t (*red)[TWV], uint32_t* out, bool carried = false);
 };
 
-// A wave's ranges to its column of red; a barrier must follow.
-__device__ __forceinline__ void stage_ranges(uint4 rg, uint32_t (*red)[TWV]) {
-  const uint32_t pl = wave_min_u32(rg.x), ph = wave_max_u32(rg.y & 0xffu);
+// A wave's ranges to its column of red; a barrier must follow. `carried`: the
+// first word is the largest carried rank.
+__device__ __forceinline__ void stage_ranges(uint4 rg, uint32_t (*red)[TWV],
+                                             bool carried = false) {
+  const uint32_t pl = carried ? wave_max_u32(rg.x) : wave_min_u32(rg.x), ph = wave_max_u32(rg.y & 0xffu);
   const uint32_t bad = wave_or_u32(rg.y & 0x80000000u);
   const uint32_t ll = wave_min_u32(rg.z), lh = wave_max_u32(rg.w);
   if (lane_id() == 0) {
@@ -60,11 +64,12 @@ __device__ __forceinline__ void stage_ranges(uint4 rg, uint32_t (*red)[TWV]) {
 }
 
 // The ranges of the first `waves` columns (one thread).
-__device__ __forceinline__ uint4 collect_ranges(const uint32_t (*red)[TWV], int waves) {
-  uint4 v = make_uint4(0xffu, 0u, 0xffffffffu, 0u);
+__device__ __forceinline__ uint4 collect_ranges(const uint32_t (*red)[TWV], int waves,
+                                                bool carried = false) {
+  uint4 v = make_uint4(carried ? 0u : 0xffu, 0u, 0xffffffffu, 0u);
   uint32_t bad = 0;
   for (int i = 0; i < waves; ++i) {
-    v.x = min(v.x, red[0][i]);
+    v.x = carried ? max(v.x, red[0][i]) : min(v.x, red[0][i]);
     v.y = max(v.y, red[1][i] & 0xffu);
     bad |= red[1][i] & 0x80000000u;
     v.z = min(v.z, red[2][i]);
@@ -74,10 +79,11 @@ __device__ __forceinline__ uint4 collect_ranges(const uint32_t (*red)[TWV], int 
   return v;
 }
 
-__device__ __forceinline__ void TileRanges::write(uint32_t (*red)[TWV], uint32_t* out) {
-  stage_ranges(make_uint4(pmin, pmax | (bad << 31), lmin, lmax), red);
+__device__ __forceinline__ void TileRanges::write(uint32_t (*red)[TWV], uint32_t* out,
+                                                  bool carried) {
+  stage_ranges(make_uint4(pmin, pmax | (bad << 31), lmin, lmax), red, carried);
   block_sync();
-  if (threadIdx.x == 0) *reinterpret_cast<uint4*>(out) = collect_ranges(red, TWV);
+  if (threadIdx.x == 0) *reinterpret_cast<uint4*>(out) = collect_ranges(red, TWV, carried);
 }
 
 // Digit counts of a tile, kCountCopies copies of each: cleared (a barrier must
@@ -116,6 +122,10 @@ __device__ __forceinline__ uint32_t tile_positions(uint16_t (*cnt)[kMaxBins], ui
   }
   return ex;
 }
+
+// Elements that carry a rank have it above the low 24 bits of the id.
+constexpr uint32_t kPayIdBits = 24;
+constexpr uint32_t kPayIdMask = (1u << kPayIdBits) - 1;
 
 // A digit of the mixed-radix value u2.
 struct TileDigit {
@@ -181,11 +191,15 @@ struct PlaceLds {
 // 2^52). `staged` is called once e is free to take other elements (the next
 // tile's, loaded while this one is placed). The LDS members may be used again
 // after the next barrier; clo/chi are complete after it.
-template <bool WIDE_SUMS, int R, typename Codec, typename Lds, typename Staged>
+// PAY: the ids' bits 24 and up carry the caller's rank, and the totals are
+// split by it: its sums go to copies of the class sums (rank << pay_shift |
+// lane), 16 of them for up to 16 ranks, which 64 bits hold.
+template <bool WIDE_SUMS, bool PAY, int R, typename Codec, typename Lds, typename Staged>
 __device__ __forceinline__ void place_tile(const Codec& kc, const TileDigit& dig, bool small,
                                            const uint64_t (&e)[R], int cv, uint32_t pos0,
                                            uint64_t wait0, int32_t* order, int64_t* wait,
-                                           uint64_t limit, Lds& sh, Staged&& staged) {
+                                           uint64_t limit, Lds& sh, Staged&& staged,
+                                           uint32_t pay_shift = 0) {
   const int t = threadIdx.x;
   const int lane = lane_id();
   const int w = wave_no();
@@ -257,8 +271,16 @@ __device__ __forceinline__ void place_tile(const Codec& kc, const TileDigit& dig
       const uint64_t wt = sh.wb[dg[r]] + lp[r];
       const uint64_t x = stage[j];
       if (pos < limit) {  // (always, for consistent counts)
-        order[pos] = (int32_t)kc.id(x);
+        order[pos] = (int32_t)(PAY ? kc.id(x) & kPayIdMask : kc.id(x));
         wait[pos] = (int64_t)wt;
+      }
+      if constexpr (PAY) {
+        const uint32_t at = (kc.id(x) >> kPayIdBits << pay_shift) | (lane & ((1u << pay_shift) - 1));
+        if (pay_shift >= 4)  // (uniform) 512 waits at most per copy and tile
+          atomicAdd(reinterpret_cast<unsigned long long*>(&sh.clo[at]), (unsigned long long)wt);
+        else
+          atomic_add128(&sh.clo[at], &sh.chi[at], U128{wt, 0});
+        continue;
       }
       const uint32_t c = kc.pp_of(x);
       if (c != cur) {
@@ -273,6 +295,7 @@ __device__ __forceinline__ void place_tile(const Codec& kc, const TileDigit& dig
     // the next tile's elements)
     if (r % 2 == 1) __builtin_amdgcn_sched_barrier(0);
   }
+  if constexpr (PAY) return;
   // lanes that end in one class (nearly all waves) add up first
   const uint32_t c0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)cur);
   if (__builtin_amdgcn_ballot_w64(cur != c0) == 0) {

@@ -69,14 +69,18 @@ __global__ __launch_bounds__(TT) void t_count(GArgs a) {
   block_sync();
   const uint32_t mask = (1u << a.d0) - 1;
   TileRanges rg;
+  const bool carried = a.payload != nullptr;
+  uint32_t pay = 0;
 #pragma unroll
   for (int r = 0; r < R; ++r) {
     const bool in = first + r * TT + t < a.n;
-    rg.add(in, pv[r], lv[r], a.num_classes);
+    rg.add(in, carried ? 0u : pv[r], lv[r], a.num_classes);
+    if (in) pay = max(pay, pv[r]);
     atomicAdd(&s_cnt[((uint32_t)lv[r] & mask) * kCountCopies + (lane & (kCountCopies - 1))],
               in ? 1u : 0u);
   }
-  rg.write(s_red, a.block_ranges + 4 * (size_t)blockIdx.x);  // (holds a barrier)
+  if (carried) rg.pmin = pay;
+  rg.write(s_red, a.block_ranges + 4 * (size_t)blockIdx.x, carried);  // (holds a barrier)
   write_counts(s_cnt, count_rows(a) + (size_t)blockIdx.x * kMaxBins);
 }
 
@@ -162,12 +166,14 @@ __device__ __forceinline__ void tile_scatter(const GArgs& a, TileFirstLds<R>& sh
                                              const uint32_t (&rk)[R]) {
   const int w = wave_no();
   const int j0 = w * kWave * R + lane_id();
+  const bool carried = a.payload != nullptr;  // the rank rides above the id
   Codec kc;
   kc.init(a.d0, &sh.plan);
 #pragma unroll
   for (int r = 0; r < R; ++r)
     sh.u.stage[rk[r] + sh.cnt[w][dg[r]]] =
-        kc.make(pv[r], lv[r], (uint32_t)(first + j0 + r * kWave));
+        kc.make(carried ? 0u : pv[r], lv[r],
+                (uint32_t)(first + j0 + r * kWave) | (carried ? pv[r] << kPayIdBits : 0u));
   block_sync();
   uint64_t* out = a.keys[0];
 #pragma unroll
@@ -200,22 +206,27 @@ __global__ __launch_bounds__(TT) void t_first(GArgs a) {
     lv[r] = (uint32_t)a.length[i];
   }
   // ranges of all tiles (rows <= kTileRows <= TT)
-  uint4 rg = make_uint4(0xffu, 0u, 0xffffffffu, 0u);
+  const bool carried = a.payload != nullptr;
+  uint4 rg = make_uint4(carried ? 0u : 0xffu, 0u, 0xffffffffu, 0u);
   if (t < rows) rg = reinterpret_cast<const uint4*>(a.block_ranges)[t];
   fold_rows(a, me, rows, sh.u.fold.before, sh.u.fold.after);
-  stage_ranges(rg, sh.red);
+  stage_ranges(rg, sh.red, carried);
   clear_row(sh.cnt[w]);
   block_sync();
   if (t == 0) {
-    const uint4 all = collect_ranges(sh.red, (rows + kWave - 1) / kWave);
+    const uint4 all = collect_ranges(sh.red, (rows + kWave - 1) / kWave, carried);
     sh.plan.cglb = 0;
     sh.plan.ok = 0;
     const bool bad = (all.y >> 31) != 0;
     if (bad) {
       if (me == 0) atomicOr(a.flags, kFlagRange);
     } else {
-      make_plan((uint32_t)a.d0, (uint32_t)(a.n - 1), false, false, all.x, all.y,
+      make_plan((uint32_t)a.d0, (uint32_t)(a.n - 1), false, false, carried ? 0u : all.x, all.y,
                 all.z, all.w, &sh.plan);
+      if (carried) {  // (keys of lengths alone: at most 31 bits, so W is 32)
+        sh.plan.pay = 1;
+        sh.plan.pay_max = all.x;
+      }
       sh.plan.ok = 1;
     }
     if (me == 0 && !bad) *a.plan = sh.plan;
@@ -412,7 +423,7 @@ struct TileFinalLds : PlaceLds {
   uint32_t last;
 };
 
-template <int R, typename Codec>
+template <bool PAY, int R, typename Codec>
 __device__ void tile_final(const GArgs& a, TileFinalLds<R>& sh) {
   const Plan* pl = a.plan;
   const int t = threadIdx.x;
@@ -423,7 +434,9 @@ __device__ void tile_final(const GArgs& a, TileFinalLds<R>& sh) {
   const int s = (int)pl->nscatter - 1;
   const int nb = (int)pl->nbins[s];
   const TileDigit dig = {pl->shift[s], pl->nbits[s]};
-  const uint32_t P = pl->P;
+  const uint32_t P = PAY ? pl->pay_max + 1 : pl->P;  // totals to write
+  // copies of a carried rank's sum in the 256 class sums
+  const uint32_t csh = PAY ? min(4u, 8u - bit_width32(P - 1)) : 0u;
   const bool small = pl->small != 0;
   Codec kc;
   kc.init(a.d0, pl);
@@ -443,9 +456,9 @@ __device__ void tile_final(const GArgs& a, TileFinalLds<R>& sh) {
   sh.u.fold.tw[t] = 0;
   sh.u.fold.bc[t] = 0;
   sh.u.fold.tc[t] = 0;
-  for (uint32_t c = t; c < P; c += TT) {
-    sh.clo[c] = 0;
-    sh.chi[c] = 0;
+  if (t < 256) {
+    sh.clo[t] = 0;
+    sh.chi[t] = 0;
   }
   block_sync();
   {
@@ -494,8 +507,8 @@ __device__ void tile_final(const GArgs& a, TileFinalLds<R>& sh) {
     wait0 += block_excl_scan_u64<TT>(tw, sh.scan64, all64);
   }
 
-  place_tile<false>(kc, dig, small, e, cv, pos0, wait0, a.order, a.wait, (uint64_t)a.n, sh,
-                    [] {});
+  place_tile<false, PAY>(kc, dig, small, e, cv, pos0, wait0, a.order, a.wait, (uint64_t)a.n, sh,
+                         [] {}, csh);
   block_sync();
 
   // Class totals: every tile publishes its sums, the last workgroup to finish
@@ -506,8 +519,11 @@ __device__ void tile_final(const GArgs& a, TileFinalLds<R>& sh) {
   uint64_t* part = class_parts(a);
   for (uint32_t c = t; c < P; c += TT) {
     uint64_t* o = part + 2 * ((size_t)me * P + c);
-    __hip_atomic_store(o, sh.clo[c], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_store(o + 1, sh.chi[c], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    U128 v = {0, 0};
+    for (uint32_t k = 0; k < (1u << csh); ++k)
+      add128(v, U128{sh.clo[(c << csh) | k], sh.chi[(c << csh) | k]});
+    __hip_atomic_store(o, v.lo, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(o + 1, v.hi, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
   __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): the stores above are complete
   block_sync();
@@ -527,7 +543,7 @@ __device__ void tile_final(const GArgs& a, TileFinalLds<R>& sh) {
   }
   block_sync();
   for (uint32_t c = t; c < P; c += TT) {
-    uint64_t* o = a.totals + 2 * (1 + (size_t)pl->pmin + c);
+    uint64_t* o = a.totals + 2 * (1 + (size_t)(PAY ? 0u : pl->pmin) + c);
     o[0] = sh.clo[c];
     o[1] = sh.chi[c];
   }
@@ -546,8 +562,9 @@ template <int R>
 __global__ __launch_bounds__(TT) void t_final(GArgs a) {
   __shared__ TileFinalLds<R> sh;
   if (!a.plan->ok) return;
-  if (a.plan->W == 32) tile_final<R, KeyCodec32>(a, sh);
-  else tile_final<R, KeyCodec64>(a, sh);
+  if (a.payload) tile_final<true, R, KeyCodec32>(a, sh);
+  else if (a.plan->W == 32) tile_final<false, R, KeyCodec32>(a, sh);
+  else tile_final<false, R, KeyCodec64>(a, sh);
 }
 
 template <int R>
