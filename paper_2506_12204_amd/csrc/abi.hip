@@ -525,6 +525,7 @@ int enqueue_policy(int policy, const uint8_t* p, const int32_t* l, int64_t n, in
   }
   const PolLayout L = policy_layout(policy, n);
   PolArgs a = {};
+  a.range = policy_range(n);
   a.priority = p;
   a.length = l;
   a.n = n;

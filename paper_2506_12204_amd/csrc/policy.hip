@@ -4,8 +4,8 @@
 // the exclusive prefix of the lengths in the policy's order and the totals
 // are split by each request's own rank, as for the semantic order.
 //
-// Every kernel gives each wave one range of kPolRange consecutive positions
-// (64 rounds of 64 lanes); a block's four waves are independent. With at most
+// Every kernel gives each wave one range of PolArgs::range consecutive positions
+// (8 to 64 rounds of 64 lanes); a block's four waves are independent. With at most
 // kRegClasses ranks every lane keeps its own per-class sums in registers
 // (one compare and two selects per class and element) and the wave reduces
 // them once per range. With more ranks the sums are formed once per round
@@ -42,11 +42,13 @@ namespace {
 
 constexpr int PT = 256;                // threads of the range kernels (4 waves)
 constexpr int kWaves = PT / kWave;
-constexpr int kRounds = kPolRange / kWave;  // 64 rounds per range
 constexpr int kBatch = 8;              // rounds loaded together
-constexpr int kBatches = kRounds / kBatch;
+// The same in f_write and h_scatter, which the waves in flight bound: with 8
+// they take 196 and 105 registers (2 and 4 waves per SIMD; 33.5 million: FCFS
+// 192 us, HPJF 326), with 4 they take 96 and 88 (5 waves; 173 and 315).
+constexpr int kWriteBatch = 4;
 constexpr int ST = 1024;               // threads of the scan kernels
-static_assert(kRounds % kBatch == 0, "whole batches per range");
+static_assert(kPolRangeMin % (kWave * kBatch) == 0, "whole batches per range");
 
 typedef const __attribute__((address_space(4))) uint64_t ConstU64;
 typedef const __attribute__((address_space(4))) uint32_t ConstU32;
@@ -284,40 +286,47 @@ __global__ __launch_bounds__(PT) void p_range(PolArgs a) {
 }
 
 // Calls f(length, rank, live) for every element of the range starting at k0
-// (kPolRange elements, in no particular order). With vec (lengths 16-byte
+// (a.range elements, in no particular order). With vec (lengths 16-byte
 // and ranks 4-byte aligned) every lane loads four consecutive elements at a
 // time; elements past n come with live = false. All lanes call f together.
 template <typename F>
 __device__ __forceinline__ void range_elements(const PolArgs& a, int64_t k0, bool vec, F&& f) {
+  static_assert(kPolRangeMin % (4 * kWave) == 0, "whole rounds of four per lane");
   if (vec) {
-#pragma unroll 4
-    for (int r = 0; r < kRounds / 4; ++r) {
-      const int64_t k = k0 + 4 * ((int64_t)r * kWave + lane_id());
-      int32_t l[4];
-      uint32_t p[4];
-      if (k + 3 < a.n) {
-        const int4 lv = *reinterpret_cast<const int4*>(a.length + k);
-        const uint32_t pv = *reinterpret_cast<const uint32_t*>(a.priority + k);
-        l[0] = lv.x, l[1] = lv.y, l[2] = lv.z, l[3] = lv.w;
+#pragma unroll 1
+    for (int b = 0; b < a.range; b += kPolRangeMin) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) p[i] = (pv >> (8 * i)) & 0xffu;
-      } else {
+      for (int r = 0; r < kPolRangeMin / (4 * kWave); ++r) {
+        const int64_t k = k0 + b + 4 * (r * kWave + lane_id());
+        int32_t l[4];
+        uint32_t p[4];
+        if (k + 3 < a.n) {
+          const int4 lv = *reinterpret_cast<const int4*>(a.length + k);
+          const uint32_t pv = *reinterpret_cast<const uint32_t*>(a.priority + k);
+          l[0] = lv.x, l[1] = lv.y, l[2] = lv.z, l[3] = lv.w;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int64_t ki = min(k + i, a.n - 1);
-          l[i] = a.length[ki];
-          p[i] = a.priority[ki];
+          for (int i = 0; i < 4; ++i) p[i] = (pv >> (8 * i)) & 0xffu;
+        } else {
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const int64_t ki = min(k + i, a.n - 1);
+            l[i] = a.length[ki];
+            p[i] = a.priority[ki];
+          }
         }
-      }
 #pragma unroll
-      for (int i = 0; i < 4; ++i) f(l[i], p[i], k + i < a.n);
+        for (int i = 0; i < 4; ++i) f(l[i], p[i], k + i < a.n);
+      }
     }
   } else {
-#pragma unroll 16
-    for (int r = 0; r < kRounds; ++r) {
-      const int64_t k = k0 + r * kWave + lane_id();
-      const int64_t kc = min(k, a.n - 1);
-      f(a.length[kc], (uint32_t)a.priority[kc], k < a.n);
+#pragma unroll 1
+    for (int b = 0; b < a.range; b += kPolRangeMin) {
+#pragma unroll
+      for (int r = 0; r < kPolRangeMin / kWave; ++r) {
+        const int64_t k = k0 + b + r * kWave + lane_id();
+        const int64_t kc = min(k, a.n - 1);
+        f(a.length[kc], (uint32_t)a.priority[kc], k < a.n);
+      }
     }
   }
 }
@@ -331,21 +340,24 @@ __device__ __forceinline__ bool vec_ok(const PolArgs& a) {
 __global__ __launch_bounds__(PT) void f_sums(PolArgs a, int64_t ranges) {
   const int64_t w = min(wave_index(), ranges - 1);  // (waves past the end repeat the last range)
   const bool live = wave_index() < ranges;
-  const int64_t k0 = w * kPolRange;
+  const int64_t k0 = w * a.range;
   uint64_t s = 0;
   uint32_t m = 0;
   bool bad = false;
   // (one element per lane: this first kernel of a schedule runs while the
   // caches write back the previous schedule's output, and loading four per
   // lane did not help it)
-#pragma unroll 16
-  for (int r = 0; r < kRounds; ++r) {
-    const int64_t k = k0 + r * kWave + lane_id();
-    const int64_t kc = min(k, a.n - 1);
-    const int32_t l = k < a.n ? a.length[kc] : 0;
-    m = max(m, (uint32_t)a.priority[kc]);
-    bad |= l < 0;
-    s += (uint32_t)l;
+#pragma unroll 1
+  for (int b = 0; b < a.range; b += kPolRangeMin) {
+#pragma unroll
+    for (int r = 0; r < kPolRangeMin / kWave; ++r) {
+      const int64_t k = k0 + b + r * kWave + lane_id();
+      const int64_t kc = min(k, a.n - 1);
+      const int32_t l = k < a.n ? a.length[kc] : 0;
+      m = max(m, (uint32_t)a.priority[kc]);
+      bad |= l < 0;
+      s += (uint32_t)l;
+    }
   }
   if (__ballot(bad)) {
     if (lane_id() == 0) atomicOr(a.flags, kFlagRange);
@@ -410,25 +422,26 @@ __device__ __forceinline__ void fcfs_range(const PolArgs& a, int64_t w, uint32_t
   LaneAcc<SETS> acc;
   rs.zero();
   acc.zero();
-  const int64_t k0 = w * kPolRange;
+  const int64_t k0 = w * a.range;
   uint64_t base = *((ConstU64*)(a.rsum + w));
-  int32_t len[kBatch], nlen[kBatch];  // this batch, the next one
-  uint8_t pri[kBatch], npri[kBatch];
+  int32_t len[kWriteBatch], nlen[kWriteBatch];  // this batch, the next one
+  uint8_t pri[kWriteBatch], npri[kWriteBatch];
   auto load = [&](int b, int32_t* l, uint8_t* p) {
 #pragma unroll
-    for (int r = 0; r < kBatch; ++r) {
-      const int64_t k = min(k0 + (b * kBatch + r) * kWave + lane_id(), a.n - 1);
+    for (int r = 0; r < kWriteBatch; ++r) {
+      const int64_t k = min(k0 + (b * kWriteBatch + r) * kWave + lane_id(), a.n - 1);
       l[r] = a.length[k];
       p[r] = a.priority[k];
     }
   };
   load(0, len, pri);
+  const int batches = a.range / (kWave * kWriteBatch);
 #pragma unroll 1
-  for (int b = 0; b < kBatches; ++b) {
-    load(min(b + 1, kBatches - 1), nlen, npri);  // (the last batch reloads itself)
+  for (int b = 0; b < batches; ++b) {
+    load(min(b + 1, batches - 1), nlen, npri);  // (the last batch reloads itself)
 #pragma unroll
-    for (int r = 0; r < kBatch; ++r) {
-      const int64_t kr = k0 + (b * kBatch + r) * kWave;
+    for (int r = 0; r < kWriteBatch; ++r) {
+      const int64_t kr = k0 + (b * kWriteBatch + r) * kWave;
       const int64_t k = kr + lane_id();
       const bool live = k < a.n;
       const uint32_t lv = live ? (uint32_t)len[r] : 0u;
@@ -450,7 +463,7 @@ __device__ __forceinline__ void fcfs_range(const PolArgs& a, int64_t w, uint32_t
       base += readlane_u64(incl, 63);
     }
 #pragma unroll
-    for (int r = 0; r < kBatch; ++r) {
+    for (int r = 0; r < kWriteBatch; ++r) {
       len[r] = nlen[r];
       pri[r] = npri[r];
     }
@@ -491,7 +504,7 @@ __device__ __forceinline__ void hpjf_count(const PolArgs& a, int64_t w, int64_t 
   rc.zero();
   cnt.zero();
   lsum.zero();
-  const int64_t k0 = w * kPolRange;
+  const int64_t k0 = w * a.range;
   bool bad = false;
   range_elements(a, k0, vec_ok(a), [&](int32_t l, uint32_t p, bool live) {
     bad |= live && l < 0;
@@ -603,24 +616,25 @@ __device__ __forceinline__ void hpjf_range(const PolArgs& a, int64_t w, int64_t 
   LaneAcc<SETS> acc;
   rs.zero();
   acc.zero();
-  const int64_t k0 = w * kPolRange;
-  int32_t len[kBatch], nlen[kBatch];  // this batch, the next one
-  uint8_t pri[kBatch], npri[kBatch];
+  const int64_t k0 = w * a.range;
+  int32_t len[kWriteBatch], nlen[kWriteBatch];  // this batch, the next one
+  uint8_t pri[kWriteBatch], npri[kWriteBatch];
   auto load = [&](int b, int32_t* l, uint8_t* p) {
 #pragma unroll
-    for (int r = 0; r < kBatch; ++r) {
-      const int64_t k = min(k0 + (b * kBatch + r) * kWave + lane_id(), a.n - 1);
+    for (int r = 0; r < kWriteBatch; ++r) {
+      const int64_t k = min(k0 + (b * kWriteBatch + r) * kWave + lane_id(), a.n - 1);
       l[r] = a.length[k];
       p[r] = a.priority[k];
     }
   };
   load(0, len, pri);
+  const int batches = a.range / (kWave * kWriteBatch);
 #pragma unroll 1
-  for (int b = 0; b < kBatches; ++b) {
-    load(min(b + 1, kBatches - 1), nlen, npri);  // (the last batch reloads itself)
+  for (int b = 0; b < batches; ++b) {
+    load(min(b + 1, batches - 1), nlen, npri);  // (the last batch reloads itself)
 #pragma unroll
-    for (int r = 0; r < kBatch; ++r) {
-      const int64_t k = k0 + (b * kBatch + r) * kWave + lane_id();
+    for (int r = 0; r < kWriteBatch; ++r) {
+      const int64_t k = k0 + (b * kWriteBatch + r) * kWave + lane_id();
       const bool live = k < a.n;
       const uint32_t lv = live ? (uint32_t)len[r] : 0u;
       const uint32_t cls = pri[r];
@@ -716,7 +730,7 @@ __device__ __forceinline__ void hpjf_range(const PolArgs& a, int64_t w, int64_t 
       *pw = (int64_t)wt;
     }
 #pragma unroll
-    for (int r = 0; r < kBatch; ++r) {
+    for (int r = 0; r < kWriteBatch; ++r) {
       len[r] = nlen[r];
       pri[r] = npri[r];
     }
@@ -755,9 +769,9 @@ __device__ __forceinline__ void class_range(const PolArgs& a, int64_t w, uint32_
   LaneAcc<SETS> acc;
   rs.zero();
   acc.zero();
-  const int64_t k0 = w * kPolRange;
+  const int64_t k0 = w * a.range;
 #pragma unroll 1
-  for (int b = 0; b < kBatches; ++b) {
+  for (int b = 0; b < a.range / (kWave * kBatch); ++b) {
     int32_t id[kBatch];
     uint64_t wt[kBatch];
     uint32_t p[kBatch];
@@ -837,7 +851,7 @@ __global__ __launch_bounds__(PT) void p_total(PolArgs a, int64_t blocks) {
   }
 }
 
-int64_t ranges_of(int64_t n) { return (n + kPolRange - 1) / kPolRange; }
+int64_t ranges_of(int64_t n) { return (n + policy_range(n) - 1) / policy_range(n); }
 int64_t blocks_of(int64_t n) { return (ranges_of(n) + kWaves - 1) / kWaves; }
 
 hipError_t launch_p_range(const PolArgs& a, hipStream_t st) {
@@ -852,8 +866,15 @@ void mark(hipEvent_t e, hipStream_t st) {
 
 }  // namespace
 
-int64_t policy_ranges(int64_t n) { return ranges_of(n); }
-int64_t policy_blocks(int64_t n) { return blocks_of(n); }
+// Ranges a workspace for n requests has room for: never fewer than a smaller
+// queue has, so that a workspace holds every queue up to the size it is for.
+int64_t policy_ranges(int64_t n) {
+  int64_t r = ranges_of(n);
+  for (int64_t edge : kPolRangeEdges)
+    if (n >= edge) r = std::max(r, ranges_of(edge - 1));
+  return r;
+}
+int64_t policy_blocks(int64_t n) { return (policy_ranges(n) + kWaves - 1) / kWaves; }
 
 hipError_t launch_fcfs(const PolArgs& a, hipStream_t st, hipEvent_t before, hipEvent_t after) {
   const int64_t ranges = ranges_of(a.n), blocks = blocks_of(a.n);
