@@ -455,7 +455,7 @@ __global__ __launch_bounds__(BT) void b_select(SelArgs a) {
     sh.bad = 0;
     sh.count = 0;
     a.flags[0] = 0;
-    __builtin_amdgcn_s_waitcnt(0x0F70);  // before any other thread's error bit
+    wait_stores();  // before any other thread's error bit
   }
   // the ids of both lists, then their ranks and lengths, each in one go
   int32_t ci[EC], oi[EO];
@@ -741,7 +741,7 @@ __global__ __launch_bounds__(BT) void b_evict(EvictArgs a) {
     sh.bad = 0;
     sh.count = 0;
     a.flags[0] = 0;
-    __builtin_amdgcn_s_waitcnt(0x0F70);  // before any other thread's error bit
+    wait_stores();  // before any other thread's error bit
   }
   // ids and KV sizes, the demands' sum, then ranks and lengths
   int32_t ci[E];

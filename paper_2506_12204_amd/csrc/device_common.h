@@ -32,6 +32,14 @@ __device__ __forceinline__ void block_sync() {
   __syncthreads();
 }
 
+// Waits until the wave's stores (and loads) are complete, for a barrier after
+// which another thread publishes them: neither block_sync nor a fence of that
+// other thread waits for them. The clobber keeps the compiler from moving a
+// store below the wait.
+__device__ __forceinline__ void wait_stores() {
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+}
+
 __device__ __forceinline__ uint32_t bit_width32(uint32_t x) {
   return x ? 32u - __clz(x) : 0u;
 }

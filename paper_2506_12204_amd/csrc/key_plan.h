@@ -77,7 +77,7 @@ static __device__ bool grid_barrier(const GArgs& a, uint32_t gen) {
   // one thread's fence after the wait drops the CU's and L2's stale lines for
   // it. (A fence in every wave made sixteen write-backs of the L2 per
   // workgroup and barrier: a middle pass over 2^20 requests took 82 us.)
-  __builtin_amdgcn_s_waitcnt(0x0F70);
+  wait_stores();
   block_sync();
   if (threadIdx.x == 0) {
     uint32_t ok = 1;

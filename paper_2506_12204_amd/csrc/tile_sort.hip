@@ -525,7 +525,7 @@ __device__ void tile_final(const GArgs& a, TileFinalLds<R>& sh) {
     __hip_atomic_store(o, v.lo, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __hip_atomic_store(o + 1, v.hi, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
-  __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): the stores above are complete
+  wait_stores();
   block_sync();
   if (t == 0)
     sh.last = atomicAdd(reinterpret_cast<unsigned long long*>(a.hist_w), 1ull) ==

@@ -68,6 +68,22 @@ def test_arrivals_tie_every_earlier_key():
     check(p, l, n_old, "ties")
 
 
+# The search for an arrival's place: class starts by 64 probes a step, then the
+# class's lengths as differences of waits (the last entry's from its own
+# length), four ways down to 4096 entries and halving below.
+@pytest.mark.parametrize("n_old", [1, 2, 63, 64, 65, 4095, 4097, 64 * 64 + 1, 70001])
+@pytest.mark.parametrize("classes,max_len", [(1, 3), (3, 2**31 - 1), (256, 40)])
+def test_search_edges(n_old, classes, max_len):
+    rng = np.random.default_rng(n_old + classes)
+    m = 67
+    p = rng.integers(0, classes, n_old + m).astype(np.uint8)
+    p[:n_old] &= 0xfe  # classes that only arrivals have, between the others
+    l = rng.integers(0, max_len, n_old + m, endpoint=True).astype(np.int32)
+    l[n_old:n_old + 4] = [0, max_len, 0, max_len]
+    p[n_old:n_old + 4] = [0, 0, classes - 1, classes - 1]
+    check(p, l, n_old, f"search {classes}x{max_len}")
+
+
 def test_chained_inserts_equal_one_schedule():
     p, l = fuzz_queue(200000, seed=43, classes=5, max_len=32768, tie_frac=0.2)
     cuts = [0, 60000, 60001, 150000, 200000]
