@@ -54,7 +54,7 @@ CSRC = os.path.join(ROOT, "paper_2506_12204_amd", "csrc")
 # the headers every kernel is built with: a counter measurement belongs to a
 # kernel source together with these
 COMMON = tuple(os.path.join(CSRC, h) for h in ("device_common.h", "block_common.h", "kernels.h"))
-FINAL_SOURCE = (os.path.join(CSRC, "global_sort.hip"),) + COMMON
+FINAL_SOURCE = tuple(os.path.join(CSRC, f) for f in ("global_sort.hip", "key_plan.h")) + COMMON
 MERGE_COUNTERS = os.path.join(ROOT, "profiles", "insert_merge_c3_counters.md")
 MERGE_SOURCE = (os.path.join(CSRC, "insert.hip"),) + COMMON
 WORKLOAD_TEXT = {
