@@ -18,6 +18,7 @@
 //   l_histF   final-digit counts and length sums of every tile
 //   l_scan    their prefixes
 //   l_final   order, waits, class totals
+// Small batches leave out the l_scan launches after the first (kFoldTiles).
 // Launches instead of one cooperative kernel with grid syncs: 16 queues of
 // 2^20 requests took 760 us there (its launch alone 24 us), 317 us here; 1000 of
 // 20,000 923 us, 462 us here.
@@ -33,6 +34,14 @@ namespace {
 constexpr int LR = kLongTile / TT;  // rounds per thread
 static_assert(LR * TT == kLongTile, "a tile is whole rounds of the workgroup");
 constexpr int kFirstBits = 10;
+// Room for at most kFoldTiles tiles, and kFoldRows for each queue if all were
+// long: the middle and final passes sum their queue's count rows themselves
+// instead of reading l_scan's prefixes, which saves three of the twelve
+// launches (each about 4 us, also when it returns at once). 4 queues of 20,665:
+// 77 us with l_scan, 63 so; 70 of 20,000: 88, 73; one of 2^19: 83, 74; two: 91,
+// 83 (wide keys). From 128 rows on the sums cost what the launches did: one
+// queue of 2^20 90, 87, with wide keys 102, 106.
+constexpr uint32_t kFoldTiles = 256, kFoldRows = 96;
 
 // Runs f with the element form of the plan's keys.
 template <typename F>
@@ -281,6 +290,42 @@ __device__ __forceinline__ uint32_t queue_digit_start(const BArgs& a, const Long
   return block_excl_scan_u32<TT>(a.hist[last] + a.lcount[last], scan32, sum);
 }
 
+// Small batches: what l_scan would have left for tile `tt`, summed here from
+// the queue's own count rows (every thread its digit): the counts and length
+// sums of the tiles before it, and of all of them.
+struct Folded {
+  uint32_t before, all;
+  uint64_t wbefore, wall;
+};
+template <bool FINAL>
+__device__ __forceinline__ Folded fold_rows(const BArgs& a, const LongTileDesc& x, uint32_t tt) {
+  constexpr uint32_t U = FINAL ? 8 : 16;  // rows in flight
+  const uint32_t r1 = x.item0 + x.rows;
+  Folded f = {0, 0, 0, 0};
+  for (uint32_t r = x.item0; r < r1; r += U) {
+    typename std::conditional<FINAL, uint64_t, uint32_t>::type v[U];
+#pragma unroll
+    for (uint32_t u = 0; u < U; ++u) {
+      const size_t at = (size_t)min(r + u, r1 - 1) * kMaxBins + threadIdx.x;
+      if constexpr (FINAL) v[u] = a.lfinal[at];
+      else v[u] = a.lcount[at];
+    }
+#pragma unroll
+    for (uint32_t u = 0; u < U; ++u) {
+      if (r + u >= r1) continue;  // (uniform)
+      const uint32_t c = FINAL ? (uint32_t)(v[u] >> (FINAL ? kSumBits : 0)) : (uint32_t)v[u];
+      const uint64_t l = FINAL ? (uint64_t)v[u] & kSumMask : 0ull;
+      f.all += c;
+      f.wall += l;
+      if (r + u < tt) {
+        f.before += c;
+        f.wbefore += l;
+      }
+    }
+  }
+  return f;
+}
+
 struct LongFirstLds {
   uint64_t stage[kLongTile];
   uint16_t cnt[TWV][kMaxBins];
@@ -289,8 +334,9 @@ struct LongFirstLds {
 };
 
 // Scatter of this workgroup's tiles by a 10-bit digit: the first pass (FIRST:
-// from the requests, by the low length bits) or a middle pass.
-template <bool FIRST, typename Codec>
+// from the requests, by the low length bits) or a middle pass. FOLD: no l_scan
+// ran after the counts.
+template <bool FIRST, bool FOLD, typename Codec>
 __device__ void long_scatter(const BArgs& a, Codec kc, int s, uint32_t lo, uint32_t hi,
                              LongFirstLds& sh) {
   const int t = threadIdx.x;
@@ -320,14 +366,21 @@ __device__ void long_scatter(const BArgs& a, Codec kc, int s, uint32_t lo, uint3
   if (lo >= hi) return;  // (uniform)
   LongTileDesc x = a.tdesc[lo];
   load(x);
-  uint32_t off = a.hist[(size_t)lo * kMaxBins + t];
+  uint32_t off = FOLD ? 0u : a.hist[(size_t)lo * kMaxBins + t];
   uint32_t queue0 = 0;  // start of the thread's digit in the queue
   int64_t in_queue = -1;
   for (uint32_t tt = lo; tt < hi; ++tt) {
     set_queue(kc, a, x);
     if (x.s != in_queue) {  // (uniform) another queue: its digit totals
       in_queue = x.s;
-      queue0 = queue_digit_start(a, x, sh.scan32);
+      if constexpr (FOLD) {
+        const Folded f = fold_rows<false>(a, x, tt);
+        uint32_t sum;
+        off = f.before;
+        queue0 = block_excl_scan_u32<TT>(f.all, sh.scan32, sum);
+      } else {
+        queue0 = queue_digit_start(a, x, sh.scan32);
+      }
     }
     uint64_t e[LR];
     uint32_t dg[LR], rk[LR];
@@ -346,7 +399,8 @@ __device__ void long_scatter(const BArgs& a, Codec kc, int s, uint32_t lo, uint3
     if (tt + 1 < hi) {  // the next tile's input loads while this one is written
       x = a.tdesc[tt + 1];
       load(x);
-      off = a.hist[(size_t)(tt + 1) * kMaxBins + t];
+      if constexpr (FOLD) off += a.lcount[(size_t)tt * kMaxBins + t];
+      else off = a.hist[(size_t)(tt + 1) * kMaxBins + t];
     }
     block_sync();
     const uint32_t ex = tile_positions(sh.cnt, sh.scan32);
@@ -375,16 +429,17 @@ __global__ __launch_bounds__(TT) void l_first(BArgs a) {
   if (tiles == 0 || !a.plan->ok) return;
   uint32_t lo, hi;
   tile_run(tiles, lo, hi);
-  with_codec(a.plan, [&](auto kc) { long_scatter<true>(a, kc, 0, lo, hi, sh); });
+  with_codec(a.plan, [&](auto kc) { long_scatter<true, false>(a, kc, 0, lo, hi, sh); });
 }
 
+template <bool FOLD>
 __global__ __launch_bounds__(TT) void l_mid_scatter(BArgs a, int s) {
   __shared__ LongFirstLds sh;
   const uint32_t tiles = long_tiles(a);
   if (tiles == 0 || !a.plan->ok || s >= (int)a.plan->nscatter - 1) return;
   uint32_t lo, hi;
   tile_run(tiles, lo, hi);
-  with_codec(a.plan, [&](auto kc) { long_scatter<false>(a, kc, s, lo, hi, sh); });
+  with_codec(a.plan, [&](auto kc) { long_scatter<false, FOLD>(a, kc, s, lo, hi, sh); });
 }
 
 // Digit counts of this workgroup's tiles in middle pass s.
@@ -456,7 +511,7 @@ __device__ __forceinline__ void add_total(uint64_t* o, const U128& v) {
 
 // Order, waits and class totals of this workgroup's tiles. The class sums stay
 // in LDS over consecutive tiles of one queue, then go to its totals.
-template <bool WIDE_SUMS, typename Codec>
+template <bool WIDE_SUMS, bool FOLD, typename Codec>
 __device__ void long_final(const BArgs& a, Codec kc, uint32_t lo, uint32_t hi,
                            LongFinalLds& sh) {
   const int t = threadIdx.x;
@@ -491,8 +546,8 @@ __device__ void long_final(const BArgs& a, Codec kc, uint32_t lo, uint32_t hi,
   const bool own = (uint32_t)t < nb;  // (rows hold nb digits)
   LongTileDesc x = a.tdesc[lo];
   load(x, e);
-  uint32_t off = own ? a.hist[(size_t)lo * kMaxBins + t] : 0u;
-  uint64_t woff = own ? a.lwait[(size_t)lo * kMaxBins + t] : 0ull;
+  uint32_t off = own && !FOLD ? a.hist[(size_t)lo * kMaxBins + t] : 0u;
+  uint64_t woff = own && !FOLD ? a.lwait[(size_t)lo * kMaxBins + t] : 0ull;
   for (uint32_t c = t; c < P; c += TT) {
     sh.clo[c] = 0;
     sh.chi[c] = 0;
@@ -506,14 +561,21 @@ __device__ void long_final(const BArgs& a, Codec kc, uint32_t lo, uint32_t hi,
       if (in_queue >= 0) flush(in_queue);
       in_queue = x.s;
       limit = (uint64_t)(a.offsets[x.s + 1] - a.offsets[x.s]);
-      const size_t last = (size_t)(x.item0 + x.rows - 1) * kMaxBins + t;
-      const uint64_t f = own ? a.lfinal[last] : 0ull;
+      Folded f = {0, 0, 0, 0};
+      if constexpr (FOLD) {
+        if (own) f = fold_rows<true>(a, x, tt);
+        off = f.before;
+        woff = f.wbefore;
+      } else if (own) {
+        const size_t last = (size_t)(x.item0 + x.rows - 1) * kMaxBins + t;
+        const uint64_t v = a.lfinal[last];
+        f.all = a.hist[last] + (uint32_t)(v >> kSumBits);
+        f.wall = a.lwait[last] + (v & kSumMask);
+      }
       uint32_t sum;
       uint64_t wsum;
-      queue0 = block_excl_scan_u32<TT>(own ? a.hist[last] + (uint32_t)(f >> kSumBits) : 0u,
-                                       sh.scan32, sum);
-      wait0 = block_excl_scan_u64<TT>(own ? a.lwait[last] + (f & kSumMask) : 0ull, sh.scan64,
-                                      wsum);
+      queue0 = block_excl_scan_u32<TT>(f.all, sh.scan32, sum);
+      wait0 = block_excl_scan_u64<TT>(f.wall, sh.scan64, wsum);
     }
     const LongTileDesc cur = x;
     const uint32_t pos0 = queue0 + off;
@@ -523,8 +585,14 @@ __device__ void long_final(const BArgs& a, Codec kc, uint32_t lo, uint32_t hi,
       if (tt + 1 < hi) {
         x = a.tdesc[tt + 1];
         load(x, e);
-        off = own ? a.hist[(size_t)(tt + 1) * kMaxBins + t] : 0u;
-        woff = own ? a.lwait[(size_t)(tt + 1) * kMaxBins + t] : 0ull;
+        if constexpr (FOLD) {
+          const uint64_t v = own ? a.lfinal[(size_t)tt * kMaxBins + t] : 0ull;
+          off += (uint32_t)(v >> kSumBits);
+          woff += v & kSumMask;
+        } else {
+          off = own ? a.hist[(size_t)(tt + 1) * kMaxBins + t] : 0u;
+          woff = own ? a.lwait[(size_t)(tt + 1) * kMaxBins + t] : 0ull;
+        }
       }
     };
     const int64_t qfirst = cur.first - cur.lo;  // the queue's first request
@@ -536,6 +604,7 @@ __device__ void long_final(const BArgs& a, Codec kc, uint32_t lo, uint32_t hi,
   flush(in_queue);
 }
 
+template <bool FOLD>
 __global__ __launch_bounds__(TT) void l_final(BArgs a) {
   __shared__ LongFinalLds sh;
   const uint32_t tiles = long_tiles(a);
@@ -545,9 +614,9 @@ __global__ __launch_bounds__(TT) void l_final(BArgs a) {
   if (a.plan->W == 32 && a.plan->sum64) {
     KeyCodec32 kc;
     kc.init(kFirstBits, a.plan);
-    long_final<false>(a, kc, lo, hi, sh);
+    long_final<false, FOLD>(a, kc, lo, hi, sh);
   } else {
-    with_codec(a.plan, [&](auto kc) { long_final<true>(a, kc, lo, hi, sh); });
+    with_codec(a.plan, [&](auto kc) { long_final<true, FOLD>(a, kc, lo, hi, sh); });
   }
 }
 
@@ -565,11 +634,26 @@ int resident_groups(K kernel) {
   return cus * occ;
 }
 
+// The middle passes, final counts and final pass; FOLD: without l_scan launches.
+template <bool FOLD, typename Grid>
+void launch_passes(const BArgs& a, unsigned scan, Grid&& grid, hipStream_t st) {
+  static const int r_count = resident_groups(l_count), r_histF = resident_groups(l_histF),
+                   r_mid = resident_groups(l_mid_scatter<FOLD>),
+                   r_final = resident_groups(l_final<FOLD>);
+  for (int s = 1; s <= max_mid_passes(kFirstBits); ++s) {
+    hipLaunchKernelGGL(l_mid_count, grid(r_count), dim3(TT), 0, st, a, s);
+    if (!FOLD) hipLaunchKernelGGL(l_scan<false>, dim3(scan), dim3(TT), 0, st, a, s);
+    hipLaunchKernelGGL(l_mid_scatter<FOLD>, grid(r_mid), dim3(TT), 0, st, a, s);
+  }
+  hipLaunchKernelGGL(l_histF, grid(r_histF), dim3(TT), 0, st, a);
+  if (!FOLD) hipLaunchKernelGGL(l_scan<true>, dim3(scan), dim3(TT), 0, st, a, 0);
+  hipLaunchKernelGGL(l_final<FOLD>, grid(r_final), dim3(TT), 0, st, a);
+}
+
 }  // namespace
 
 hipError_t launch_long_queues(const BArgs& a, hipStream_t st) {
-  static const int r_count = resident_groups(l_count), r_first = resident_groups(l_first),
-                   r_histF = resident_groups(l_histF), r_final = resident_groups(l_final);
+  static const int r_count = resident_groups(l_count), r_first = resident_groups(l_first);
   auto grid = [&](int resident) {
     return dim3((unsigned)std::max<int64_t>(1, std::min<int64_t>(resident, a.max_tiles)));
   };
@@ -579,14 +663,10 @@ hipError_t launch_long_queues(const BArgs& a, hipStream_t st) {
   hipLaunchKernelGGL(l_count, grid(r_count), dim3(TT), 0, st, a);
   hipLaunchKernelGGL(l_scan<false>, dim3(scan + 1), dim3(TT), 0, st, a, 0);
   hipLaunchKernelGGL(l_first, grid(r_first), dim3(TT), 0, st, a);
-  for (int s = 1; s <= max_mid_passes(kFirstBits); ++s) {
-    hipLaunchKernelGGL(l_mid_count, grid(r_count), dim3(TT), 0, st, a, s);
-    hipLaunchKernelGGL(l_scan<false>, dim3(scan), dim3(TT), 0, st, a, s);
-    hipLaunchKernelGGL(l_mid_scatter, grid(r_first), dim3(TT), 0, st, a, s);
-  }
-  hipLaunchKernelGGL(l_histF, grid(r_histF), dim3(TT), 0, st, a);
-  hipLaunchKernelGGL(l_scan<true>, dim3(scan), dim3(TT), 0, st, a, 0);
-  hipLaunchKernelGGL(l_final, grid(r_final), dim3(TT), 0, st, a);
+  if (a.max_tiles <= kFoldTiles && a.max_tiles <= kFoldRows * (uint64_t)a.num_segments)
+    launch_passes<true>(a, scan, grid, st);
+  else
+    launch_passes<false>(a, scan, grid, st);
   return hipGetLastError();
 }
 

@@ -63,3 +63,16 @@ def test_largest_sums():
     l = np.full(1 << 21, 2**31 - 1, np.int32)
     got = gpu_batched(p, l, off, 4, long_requests=int(sizes.sum()))
     assert_same(got, c_oracle_batched(p, l, off, 4), "largest sums")
+
+
+# The same queues with their exact room (the passes sum the count rows
+# themselves) and with room for 300 tiles more (the rows' prefixes are launched)
+@pytest.mark.parametrize("sizes", [[16385], [96 * TILE - 1], [30 * TILE, 17000, 65 * TILE + 1]])
+@pytest.mark.parametrize("classes,max_len", [(5, 32768), (9, 2_000_000), (256, 2**31 - 1)])
+def test_both_sides_of_the_fold_rule(sizes, classes, max_len):
+    p, l, off = fuzz_segments(sizes, seed=len(sizes), classes=classes, max_len=max_len)
+    want = c_oracle_batched(p, l, off, classes)
+    for more in (0, 300 * TILE):
+        print(f"[gpu] fold sizes={sizes} {classes}x{max_len} more={more}", flush=True)
+        got = gpu_batched(p, l, off, classes, long_requests=sum(sizes) + more)
+        assert_same(got, want, f"fold more={more}")
