@@ -45,6 +45,7 @@ struct BCtl {
   uint32_t empty[kLists][kSubLists];  // 1 once a segment was found exhausted (a hint)
   uint64_t long_elems;                // requests in the long list's queues
   uint32_t long_tiles, long_items;    // their tiles and scan items
+  uint32_t long_run;                  // tiles the passes after l_count work on (0 after an error)
 };
 // One segment of a list, alone in its 128-byte line: its entry count (the
 // planner's filing atomics) and the next batch to grab (the kernels'

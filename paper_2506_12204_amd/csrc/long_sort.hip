@@ -69,8 +69,12 @@ __device__ __forceinline__ void set_queue(KeyCodecGather& kc, const BArgs& a,
 
 // Tiles of the batch's long queues, or 0 when there is nothing to do here: no
 // such queues, or an error ends the call (the planner raises one for long
-// queues that do not fit the workspace and then leaves their descriptors
-// unwritten).
+// queues that do not fit the workspace and then leaves their places
+// unwritten). Only l_count asks: no kernel that runs beside it writes the
+// error bits, so all its waves see the same. The passes after it take its
+// answer (BCtl::long_run), not the bits: l_scan's first pass raises one itself
+// while it runs, and waves of a workgroup that read the word before and after
+// would part ahead of a barrier. From then on Plan::ok says whether to go on.
 __device__ __forceinline__ uint32_t long_tiles(const BArgs& a) {
   if (a.ctl->count[kListLong] == 0 || a.ctl->long_elems > a.long_cap || load_agent(a.flags) != 0)
     return 0;
@@ -87,9 +91,11 @@ __device__ __forceinline__ void tile_run(uint32_t tiles, uint32_t& lo, uint32_t&
 __global__ __launch_bounds__(TT) void l_count(BArgs a) {
   __shared__ uint32_t s_cnt[kMaxBins * kCountCopies];
   __shared__ uint32_t s_red[4][TWV];
+  const uint32_t tiles = long_tiles(a);
   uint32_t lo, hi;
-  tile_run(long_tiles(a), lo, hi);
+  tile_run(tiles, lo, hi);
   const int t = threadIdx.x;
+  if (blockIdx.x == 0 && t == 0) a.ctl->long_run = tiles;
   const uint32_t copy = (uint32_t)lane_id() & (kCountCopies - 1);
   if (lo >= hi) return;  // (uniform)
   // the queue of the first tile by a search, of the others by walking on
@@ -190,7 +196,7 @@ __global__ __launch_bounds__(TT) void l_scan(BArgs a, int s) {
   __shared__ uint32_t s_c[TWV][PD];
   __shared__ uint64_t s_w[FINAL ? TWV : 1][PD];
   __shared__ uint32_t s_red[4][TWV];
-  const uint32_t tiles = long_tiles(a);
+  const uint32_t tiles = a.ctl->long_run;
   if (tiles == 0) return;
   const bool planner = !FINAL && s == 0;  // workgroup 0 makes the plan instead
   if (planner && blockIdx.x == 0) {
@@ -425,7 +431,7 @@ __device__ void long_scatter(const BArgs& a, Codec kc, int s, uint32_t lo, uint3
 
 __global__ __launch_bounds__(TT) void l_first(BArgs a) {
   __shared__ LongFirstLds sh;
-  const uint32_t tiles = long_tiles(a);
+  const uint32_t tiles = a.ctl->long_run;
   if (tiles == 0 || !a.plan->ok) return;
   uint32_t lo, hi;
   tile_run(tiles, lo, hi);
@@ -435,7 +441,7 @@ __global__ __launch_bounds__(TT) void l_first(BArgs a) {
 template <bool FOLD>
 __global__ __launch_bounds__(TT) void l_mid_scatter(BArgs a, int s) {
   __shared__ LongFirstLds sh;
-  const uint32_t tiles = long_tiles(a);
+  const uint32_t tiles = a.ctl->long_run;
   if (tiles == 0 || !a.plan->ok || s >= (int)a.plan->nscatter - 1) return;
   uint32_t lo, hi;
   tile_run(tiles, lo, hi);
@@ -445,7 +451,7 @@ __global__ __launch_bounds__(TT) void l_mid_scatter(BArgs a, int s) {
 // Digit counts of this workgroup's tiles in middle pass s.
 __global__ __launch_bounds__(TT) void l_mid_count(BArgs a, int s) {
   __shared__ uint32_t s_cnt[kMaxBins * kCountCopies];
-  const uint32_t tiles = long_tiles(a);
+  const uint32_t tiles = a.ctl->long_run;
   if (tiles == 0 || !a.plan->ok || s >= (int)a.plan->nscatter - 1) return;
   uint32_t lo, hi;
   tile_run(tiles, lo, hi);
@@ -473,7 +479,7 @@ __global__ __launch_bounds__(TT) void l_mid_count(BArgs a, int s) {
 
 __global__ __launch_bounds__(TT) void l_histF(BArgs a) {
   __shared__ uint64_t s_bin[kFinalSlots];
-  const uint32_t tiles = long_tiles(a);
+  const uint32_t tiles = a.ctl->long_run;
   const Plan* pl = a.plan;
   if (tiles == 0 || !pl->ok) return;
   uint32_t lo, hi;
@@ -607,7 +613,7 @@ __device__ void long_final(const BArgs& a, Codec kc, uint32_t lo, uint32_t hi,
 template <bool FOLD>
 __global__ __launch_bounds__(TT) void l_final(BArgs a) {
   __shared__ LongFinalLds sh;
-  const uint32_t tiles = long_tiles(a);
+  const uint32_t tiles = a.ctl->long_run;
   if (tiles == 0 || !a.plan->ok) return;
   uint32_t lo, hi;
   tile_run(tiles, lo, hi);

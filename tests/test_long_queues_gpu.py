@@ -76,3 +76,43 @@ def test_both_sides_of_the_fold_rule(sizes, classes, max_len):
         print(f"[gpu] fold sizes={sizes} {classes}x{max_len} more={more}", flush=True)
         got = gpu_batched(p, l, off, classes, long_requests=sum(sizes) + more)
         assert_same(got, want, f"fold more={more}")
+
+
+# A range error in one long queue: found in the first or the last tile, by the
+# lengths or by the ranks, with the scans of many workgroups running beside the
+# one that raises it; then the next call on the same workspace
+@pytest.mark.parametrize("sizes", [[16385], [17000] * 60, [40 * TILE, 16385, 100, 33 * TILE + 1]])
+@pytest.mark.parametrize("where", ["first", "last"])
+@pytest.mark.parametrize("what", ["length", "rank"])
+def test_range_error_and_next_call(sizes, where, what):
+    import torch
+    import paper_2506_12204_amd as ss
+    from tests._lib import to_gpu
+    classes = 5
+    p, l, off = fuzz_segments(sizes, seed=7, classes=classes, max_len=32768)
+    n, s = len(p), len(sizes)
+    ws = torch.empty(ss.workspace_bytes(n, s), dtype=torch.uint8, device="cuda")
+    order = torch.empty(n, dtype=torch.int32, device="cuda")
+    wait = torch.empty(n, dtype=torch.int64, device="cuda")
+    totals = torch.empty((s, 1 + classes, 2), dtype=torch.int64, device="cuda")
+    stream = ss._stream_handle(ws.device)
+
+    def call(pri, length):
+        tp, tl, to = to_gpu(pri, length, off.astype(np.int64))
+        rc = ss.lib.sem_schedule_batched_async(
+            ss._ptr(tp), ss._ptr(tl), ss._ptr(to), s, classes, ss._ptr(order), ss._ptr(wait),
+            ss._ptr(totals), ss._ptr(ws), ws.numel(), stream)
+        assert rc == ss.SEM_OK
+        return ss.lib.sem_check(ss._ptr(ws), stream)
+
+    print(f"[gpu] range error sizes={sizes[:4]} {where} {what}", flush=True)
+    bp, bl = p.copy(), l.copy()
+    at = 0 if where == "first" else n - 1
+    if what == "length":
+        bl[at] = -1
+    else:
+        bp[at] = classes
+    assert call(bp, bl) == ss.SEM_ERANGE
+    assert call(p, l) == ss.SEM_OK
+    got = (order.cpu().numpy(), wait.cpu().numpy(), ss.totals_to_ints(totals))
+    assert_same(got, c_oracle_batched(p, l, off, classes), "after an error")
