@@ -265,6 +265,18 @@ void mark_stage(const StageEvents* ev, int stage, bool after, hipStream_t st);
 // kTileMaxItems requests (tile_sort.hip). Packed keys only (force_wide == 0).
 constexpr int kTileRows = 256;  // most tiles of such a queue
 constexpr int64_t kTileMaxItems = (int64_t)kTileRows * 8192;
+// Workgroups of its middle-pass kernel, which wait for one another and so must
+// all be resident: at most `resident`, what the device holds at once of that
+// kernel alone (a smaller or partitioned device: 32 compute units hold 32 to
+// 64), and at most 64 (128 beyond 2^20 requests), as many as the big-tile path
+// would use at these sizes, so that as many calls on different streams can be
+// resident side by side. Each takes every grid'th tile.
+inline int tile_mid_groups(int64_t n, int64_t tiles, int resident) {
+  int64_t g = n <= (1ll << 20) ? 64 : 128;
+  if (g > tiles) g = tiles;
+  if (g > resident) g = resident;
+  return g > 1 ? (int)g : 1;
+}
 hipError_t launch_tile_schedule(const GArgs& a, hipStream_t st, const StageEvents* ev);
 
 // Zeroes `count` 32-bit words (graph-safe replacement for a memset).

@@ -626,20 +626,6 @@ __global__ __launch_bounds__(TT) void l_final(BArgs a) {
   }
 }
 
-template <typename K>
-int resident_groups(K kernel) {
-  int dev = 0, cus = 256, occ = 1;
-  if (hipGetDevice(&dev) == hipSuccess) {
-    hipDeviceProp_t prop;
-    if (hipGetDeviceProperties(&prop, dev) == hipSuccess) cus = prop.multiProcessorCount;
-  }
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, reinterpret_cast<const void*>(kernel),
-                                                   TT, 0) != hipSuccess ||
-      occ < 1)
-    occ = 1;
-  return cus * occ;
-}
-
 // The middle passes, final counts and final pass; FOLD: without l_scan launches.
 template <bool FOLD, typename Grid>
 void launch_passes(const BArgs& a, unsigned scan, Grid&& grid, hipStream_t st) {

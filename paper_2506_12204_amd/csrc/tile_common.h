@@ -123,6 +123,21 @@ __device__ __forceinline__ uint32_t tile_positions(uint16_t (*cnt)[kMaxBins], ui
   return ex;
 }
 
+// Workgroups of a kernel of TT threads that the device holds at once (of it alone).
+template <typename K>
+int resident_groups(K kernel) {
+  int dev = 0, cus = 256, occ = 1;
+  if (hipGetDevice(&dev) == hipSuccess) {
+    hipDeviceProp_t prop;
+    if (hipGetDeviceProperties(&prop, dev) == hipSuccess) cus = prop.multiProcessorCount;
+  }
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, reinterpret_cast<const void*>(kernel),
+                                                   TT, 0) != hipSuccess ||
+      occ < 1)
+    occ = 1;
+  return cus * occ;
+}
+
 // Elements that carry a rank have it above the low 24 bits of the id.
 constexpr uint32_t kPayIdBits = 24;
 constexpr uint32_t kPayIdMask = (1u << kPayIdBits) - 1;

@@ -18,8 +18,6 @@
 // Measured: a queue of 50,003 requests 156 us in the big-tile path's nine
 // launches (16K-item tiles: 4 workgroups), 28 us here; one of 2^20 76 us (64
 // workgroups), 51 us here.
-#include <algorithm>
-
 #include "tile_common.h"
 
 namespace semsched {
@@ -354,9 +352,7 @@ __device__ void mid_scatter(const GArgs& a, int s, int me, int step, TileMidLds<
 
 // All middle passes in one launch with bounded grid barriers between their
 // phases, as g_mid does for the big tiles; it returns at once for two-pass
-// keys. At most 64 workgroups (128 beyond 2^20 requests), as many as the
-// big-tile path would use at these sizes, so that as many calls on different
-// streams can be resident side by side.
+// keys. Its grid is tile_mid_groups'.
 template <int R>
 __global__ __launch_bounds__(TT) void t_mid(GArgs a) {
   __shared__ TileMidLds<R> sh;
@@ -583,8 +579,9 @@ hipError_t launch_tiles(const GArgs& a, hipStream_t st, const StageEvents* ev) {
       hipLaunchKernelGGL(t_mid_scatter<R>, g, dim3(TT), 0, st, a, s);
     }
   } else {
-    const unsigned most = a.n <= (1ll << 20) ? 64 : 128;
-    hipLaunchKernelGGL(t_mid<R>, dim3(std::min(g.x, most)), dim3(TT), 0, st, a);
+    static const int resident = resident_groups(t_mid<R>);
+    hipLaunchKernelGGL(t_mid<R>, dim3((unsigned)tile_mid_groups(a.n, g.x, resident)), dim3(TT), 0,
+                       st, a);
   }
   mark_stage(ev, 6, true, st);
   hipLaunchKernelGGL(t_histF<R>, g, dim3(TT), 0, st, a);
