@@ -84,6 +84,23 @@ def test_search_edges(n_old, classes, max_len):
     check(p, l, n_old, f"search {classes}x{max_len}")
 
 
+# The search by class starts takes waves of one or two classes, the search by
+# keys the others: 64 sorted arrivals of exactly 1, 2, 3 or 64 classes, and 200
+# whose waves are of both kinds.
+@pytest.mark.parametrize("n_old", [0, 1, 65, 5000, 70001])
+@pytest.mark.parametrize("m,classes", [(64, 1), (64, 2), (64, 3), (64, 64), (200, 5)])
+def test_search_by_classes_of_a_wave(n_old, m, classes):
+    rng = np.random.default_rng(n_old + 64 * classes)
+    p_old = rng.integers(0, 70, n_old).astype(np.uint8)
+    l_old = rng.integers(0, 30, n_old).astype(np.int32)
+    l_old[rng.random(n_old) < 0.05] = 2**31 - 1
+    cls = rng.choice(70, classes, replace=False).astype(np.uint8)
+    l_new = rng.integers(0, 31, m).astype(np.int32)
+    l_new[::9] = 2**31 - 1
+    p, l = np.concatenate([p_old, cls[np.arange(m) % classes]]), np.concatenate([l_old, l_new])
+    check(p, l, n_old, f"{m} arrivals of {classes} classes")
+
+
 def test_chained_inserts_equal_one_schedule():
     p, l = fuzz_queue(200000, seed=43, classes=5, max_len=32768, tie_frac=0.2)
     cuts = [0, 60000, 60001, 150000, 200000]
