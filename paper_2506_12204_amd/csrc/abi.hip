@@ -191,6 +191,14 @@ uint32_t mid_spin_limit() {
   return e ? (uint32_t)std::strtoul(e, nullptr, 10) : (1u << 20);
 }
 
+// Polls of a workgroup of the batched call's long queues at the end of a
+// kernel's first phase before it takes a further share of it
+// (SEMSCHED_CLAIM_POLLS, to have workgroups take several while others start).
+uint32_t claim_polls() {
+  const char* e = std::getenv("SEMSCHED_CLAIM_POLLS");
+  return e ? std::max(1u, (uint32_t)std::strtoul(e, nullptr, 10)) : 64u;
+}
+
 // A blocking call: enqueue, synchronise, map the device's flags. When the
 // middle passes' grid barrier gave up (its workgroups were not all resident
 // on the device), the schedule is run once more with those passes as
@@ -700,6 +708,7 @@ int enqueue_batched(const uint8_t* p, const int32_t* l, const int64_t* offsets,
     a.hist = reinterpret_cast<uint32_t*>(base + L.hist);
     a.lfinal = reinterpret_cast<uint64_t*>(base + L.lfinal);
     a.lwait = reinterpret_cast<uint64_t*>(base + L.lwait);
+    a.claim_polls = claim_polls();
   }
   return launch_batched(a, st) == hipSuccess ? SEM_OK : SEM_EDEVICE;
 }

@@ -689,7 +689,12 @@ __device__ void block_list_loop(const BArgs& a, int L, GroupLds<NW, R, D, ET>& s
 
 // Where the long queues' elements, tiles and scan items start (one workgroup:
 // the first of b_medium, which saves a launch; the long list is complete since
-// the planner).
+// the planner). One thread decides whether the long queues' kernels work at
+// all: not when the planner raised an error, which leaves some queue's extent
+// unknown. They take the decision, not the error bits: one of them raises a bit
+// itself while it runs, and waves of a workgroup that read the word before and
+// after would part ahead of a barrier. (An error that another workgroup raises
+// meanwhile may or may not be seen: the call ends in it either way.)
 template <typename Lds>
 __device__ __forceinline__ void long_layout(const BArgs& a, Lds& sh) {
   constexpr int NT = kMediumThreads;
@@ -725,8 +730,8 @@ __device__ __forceinline__ void long_layout(const BArgs& a, Lds& sh) {
   }
   if (threadIdx.x == 0) {
     a.tstart[K] = tiles;
-    a.ctl->long_tiles = tiles;
     a.ctl->long_items = items;
+    a.ctl->long_run = load_agent(a.flags) == 0 ? tiles : 0u;
   }
 }
 
@@ -803,7 +808,7 @@ hipError_t launch_batched(const BArgs& a, hipStream_t st) {
   // Room for fewer requests than the shortest long queue has takes none: there
   // is then nothing to launch (a long queue all the same is an error that
   // long_layout raises). 64 queues of 256 with room for all 16,384 requests:
-  // 57 us with the launches, which return at once, 18 without.
+  // 57 us with nine launches that return at once, 18 without.
   if (a.long_cap > (uint64_t)kSegLargeCap) {
     const hipError_t e = launch_long_queues(a, st);
     if (e != hipSuccess) return e;

@@ -44,8 +44,8 @@ struct BCtl {
   uint32_t count[kLists];             // entries of the long list (count[kListLong])
   uint32_t empty[kLists][kSubLists];  // 1 once a segment was found exhausted (a hint)
   uint64_t long_elems;                // requests in the long list's queues
-  uint32_t long_tiles, long_items;    // their tiles and scan items
-  uint32_t long_run;                  // tiles the passes after l_count work on (0 after an error)
+  uint32_t long_items;                // their scan items
+  uint32_t long_run;                  // their tiles; 0 when there is nothing to do (an error)
 };
 // One segment of a list, alone in its 128-byte line: its entry count (the
 // planner's filing atomics) and the next batch to grab (the kernels'
@@ -56,6 +56,18 @@ struct alignas(128) GrabLine {
   uint32_t count;
   uint32_t pad[30];
 };
+// The long queues' kernels of several phases (next_work) use lines of the lists
+// that have no segments, the long and the tiny one, kPhaseLines each. The
+// first's `next` hands out the shares, its `count` is the number of phases
+// done. The others count the shares done, a quarter of them each (additions to
+// one line queue at about 11 ns each), the second's `next` the quarters done.
+constexpr int kPhaseLines = 5;
+enum PhaseKernel { kRunCount = 0, kRunMid = 1, kRunMidLast = 2 };
+static_assert((kRunMidLast + 1) * kPhaseLines <= 2 * kSubLists, "lines of the two lists");
+__device__ __forceinline__ GrabLine* phase_line(GrabLine* grab, int kernel, int i) {
+  const int at = kernel * kPhaseLines + i;
+  return grab + (at < kSubLists ? kListLong * kSubLists + at : kListTiny * kSubLists + at - kSubLists);
+}
 
 // One tile of the segmented sort of the long queues: found once per call by a
 // search over the queues' first tiles, then read by every later phase with
@@ -102,6 +114,7 @@ struct BArgs {
   uint32_t* hist;           // [max_tiles][1024] their prefixes over the queue's tiles
   uint64_t* lfinal;         // [max_tiles][1024] final-digit counts and length sums
   uint64_t* lwait;          // [max_tiles][1024] prefixes of the length sums
+  uint32_t claim_polls;     // next_work: polls before a further share is taken (> 0)
 };
 
 // Single queue of a.n_single <= kSegLargeCap requests (a.offsets null), one
@@ -254,7 +267,7 @@ hipError_t launch_global_schedule(const GArgs& a, hipStream_t st, const StageEve
 // Most middle passes a key can need: ranks below 2^8 and lengths below 2^31
 // make the mixed-radix value below 2^(39 - d0), of which the final pass takes
 // at most 10 bits.
-inline int max_mid_passes(int d0) {
+constexpr int max_mid_passes(int d0) {
   const int m = (38 - d0) / 10;
   return m < kMaxScatter - 2 ? m : kMaxScatter - 2;
 }

@@ -9,16 +9,23 @@
 // laid them out (long_layout); the number of tiles is known on the device
 // only, so the grids are the workgroups that fit and each takes a run of
 // consecutive tiles, loading the next tile's input while it works on one.
-//   l_count   descriptors, ranges and first-digit counts of every tile
-//   l_scan    the counts' prefix over each queue's tiles; one more workgroup
-//             makes the plan from the ranges
+//   l_count   descriptors, ranges and first-digit counts of every tile; then the
+//             counts' prefix over each queue's tiles, and the plan from the ranges
 //   l_first   first scatter
-//   l_mid_count, l_scan, l_mid_scatter   per middle pass of wide keys (they
-//             return at once for two-digit keys)
+//   l_mid_rows, l_mid_scatter   per middle pass of wide keys (they return at
+//             once for two-digit keys): the digit counts and their prefixes,
+//             the scatter
 //   l_histF   final-digit counts and length sums of every tile
-//   l_scan    their prefixes
+//   l_scanF   their prefixes
 //   l_final   order, waits, class totals
-// Small batches leave out the l_scan launches after the first (kFoldTiles).
+// Small batches take all middle passes in one launch, l_mid, and do without the
+// prefixes after the first (kFoldTiles).
+//
+// A batch that turns out to have no long queue, in a workspace with room for
+// some, pays for these launches all the same, 3 to 4 us each on the host and 2
+// to 3 on the device. Hence kernels of several phases (next_work): 512 queues
+// of 256 with room for long ones take 35 us with five launches here, 49 with
+// nine; 4096 of 1024 take 80 us with nine, 91 with twelve.
 // Launches instead of one cooperative kernel with grid syncs: 16 queues of
 // 2^20 requests took 760 us there (its launch alone 24 us), 317 us here; 1000 of
 // 20,000 923 us, 462 us here.
@@ -36,11 +43,10 @@ static_assert(LR * TT == kLongTile, "a tile is whole rounds of the workgroup");
 constexpr int kFirstBits = 10;
 // Room for at most kFoldTiles tiles, and kFoldRows for each queue if all were
 // long: the middle and final passes sum their queue's count rows themselves
-// instead of reading l_scan's prefixes, which saves three of the twelve
-// launches (each about 4 us, also when it returns at once). 4 queues of 20,665:
-// 77 us with l_scan, 63 so; 70 of 20,000: 88, 73; one of 2^19: 83, 74; two: 91,
-// 83 (wide keys). From 128 rows on the sums cost what the launches did: one
-// queue of 2^20 90, 87, with wide keys 102, 106.
+// instead of reading prefixes that other launches leave. With such launches 4
+// queues of 20,665 took 77 us, 63 so; 70 of 20,000: 88, 73; one of 2^19: 83, 74;
+// two: 91, 83 (wide keys). From 128 rows on the sums cost what the launches did:
+// one queue of 2^20 90, 87, with wide keys 102, 106.
 constexpr uint32_t kFoldTiles = 256, kFoldRows = 96;
 
 // Runs f with the element form of the plan's keys.
@@ -67,35 +73,100 @@ __device__ __forceinline__ void set_queue(KeyCodecGather& kc, const BArgs& a,
   kc.lengths = a.length + (x.first - x.lo);
 }
 
-// Tiles of the batch's long queues, or 0 when there is nothing to do here: no
-// such queues, or an error ends the call (the planner raises one for long
-// queues that do not fit the workspace and then leaves their places
-// unwritten). Only l_count asks: no kernel that runs beside it writes the
-// error bits, so all its waves see the same. The passes after it take its
-// answer (BCtl::long_run), not the bits: l_scan's first pass raises one itself
-// while it runs, and waves of a workgroup that read the word before and after
-// would part ahead of a barrier. From then on Plan::ok says whether to go on.
-__device__ __forceinline__ uint32_t long_tiles(const BArgs& a) {
-  if (a.ctl->count[kListLong] == 0 || a.ctl->long_elems > a.long_cap || load_agent(a.flags) != 0)
-    return 0;
-  return a.ctl->long_tiles;
-}
-
-// This workgroup's run of tiles [lo, hi).
-__device__ __forceinline__ void tile_run(uint32_t tiles, uint32_t& lo, uint32_t& hi) {
+// The run of tiles [lo, hi) of workgroup `me`.
+__device__ __forceinline__ void tile_run(uint32_t tiles, uint32_t me, uint32_t& lo,
+                                         uint32_t& hi) {
   const uint32_t per = (tiles + gridDim.x - 1) / gridDim.x;
-  lo = min(tiles, blockIdx.x * per);
+  lo = min(tiles, me * per);
   hi = min(tiles, lo + per);
 }
 
-__global__ __launch_bounds__(TT) void l_count(BArgs a) {
-  __shared__ uint32_t s_cnt[kMaxBins * kCountCopies];
-  __shared__ uint32_t s_red[4][TWV];
-  const uint32_t tiles = long_tiles(a);
-  uint32_t lo, hi;
-  tile_run(tiles, lo, hi);
+// A kernel of several phases, each of which needs all of the one before. Each
+// is cut into gridDim.x shares; a workgroup takes one share of the first phase
+// as it starts and has the same share of the later ones. It does not rely on
+// all workgroups being resident: one that has waited for the end of the first
+// phase while shares are left (some workgroup has not started) takes a further
+// one, and a workgroup that starts and finds none left ends. So every share
+// belongs to a workgroup that runs, waits only for such, and every wait ends.
+// What a later phase reads is written by agent-scope stores, complete (vmcnt 0)
+// before the share is counted as done, and read by agent-scope loads: no fence,
+// which would write back or invalidate the L2 in every workgroup (10 to 15 us
+// a phase).
+constexpr uint32_t kMaxShares = 512;
+struct WorkLds {
+  uint32_t phase, me;   // the share to work on now
+  uint32_t at, owned;   // its place among the workgroup's shares, their number
+  uint32_t mine[kMaxShares];
+};
+// Counts the share just worked on and finds the next one to do (w.phase, w.me);
+// false when none is left. Every thread of the workgroup calls it; `begin`: the
+// first time. One branch takes all of thread 0's steps, with a barrier on
+// either side: were a share counted at the end of the caller's loop body,
+// nothing convergent would lie between that branch and this one, and the
+// compiler threads them into each other, which sends the other lanes of
+// thread 0's wave around the loop ahead of it.
+__device__ __forceinline__ bool next_work(const BArgs& a, PhaseKernel kernel, uint32_t phases,
+                                          bool begin, WorkLds& w) {
+  wait_stores();
+  block_sync();
+  if (threadIdx.x == 0) {
+    const uint32_t shares = gridDim.x;
+    constexpr uint32_t kDone = kPhaseLines - 1;
+    uint32_t* next = &phase_line(a.grab, kernel, 0)->next;
+    uint32_t* done = &phase_line(a.grab, kernel, 0)->count;
+    uint32_t phase = begin ? 0u : w.phase;
+    uint32_t got = shares;  // a share taken now
+    if (begin) {
+      w.owned = 0;
+      got = atomicAdd(next, 1u);
+      if (got >= shares) phase = phases;
+    } else {
+      if (phase + 1 < phases) {  // the last of a quarter counts it, the last of those the phase
+        const uint32_t k = w.me % kDone, due = (shares + kDone - 1 - k) / kDone;
+        if (atomicAdd(&phase_line(a.grab, kernel, 1 + (int)k)->count, 1u) + 1 == (phase + 1) * due &&
+            atomicAdd(&phase_line(a.grab, kernel, 1)->next, 1u) + 1 ==
+                (phase + 1) * min(shares, (uint32_t)kDone))
+          store_agent(done, phase + 1);
+      }
+      if (phase > 0 && w.at + 1 < w.owned) {
+        w.at += 1;
+      } else if (phase + 1 == phases) {
+        phase = phases;
+      } else {
+        for (uint32_t polls = 1; load_agent(done) <= phase; ++polls) {
+          if (phase == 0 && polls % a.claim_polls == 0 && load_agent(next) < shares) {
+            got = atomicAdd(next, 1u);
+            if (got < shares) break;
+          }
+          __builtin_amdgcn_s_sleep(1);
+        }
+        if (got >= shares) {
+          phase += 1;
+          w.at = 0;
+        }
+      }
+    }
+    if (got < shares) {  // (at most `shares` in all, which the list holds)
+      w.at = w.owned;
+      w.mine[w.owned] = got;
+      w.owned += 1;
+    }
+    w.phase = phase;
+    w.me = phase < phases ? w.mine[w.at] : 0u;
+  }
+  block_sync();
+  return (uint32_t)__builtin_amdgcn_readfirstlane((int)w.phase) < phases;
+}
+
+struct CountLds {
+  uint32_t cnt[kMaxBins * kCountCopies];
+  uint32_t red[4][TWV];
+};
+
+// Descriptors, ranges and first-digit counts of the tiles [lo, hi).
+__device__ void count_tiles(const BArgs& a, uint32_t lo, uint32_t hi, CountLds& sh) {
+  uint32_t* s_cnt = sh.cnt;
   const int t = threadIdx.x;
-  if (blockIdx.x == 0 && t == 0) a.ctl->long_run = tiles;
   const uint32_t copy = (uint32_t)lane_id() & (kCountCopies - 1);
   if (lo >= hi) return;  // (uniform)
   // the queue of the first tile by a search, of the others by walking on
@@ -119,7 +190,7 @@ __global__ __launch_bounds__(TT) void l_count(BArgs a) {
     if (t == 0) a.tdesc[tt] = x;
     if (x.lo == 0) {  // (uniform) the queue's first tile: its scan items, its totals
       const uint32_t parts = x.rows <= kLongRowsFew ? 1u : (uint32_t)kLongScanParts;
-      if ((uint32_t)t < parts) a.imap[a.istart[k] + t] = k * kLongScanParts + t;
+      if ((uint32_t)t < parts) store_agent(a.imap + a.istart[k] + t, k * (uint32_t)kLongScanParts + t);
       const int64_t C2 = 2 * (1 + (int64_t)a.num_classes);
       for (int64_t i = t; i < C2; i += TT) a.totals[x.s * C2 + i] = 0;
     }
@@ -141,8 +212,8 @@ __global__ __launch_bounds__(TT) void l_count(BArgs a) {
       atomicAdd(&s_cnt[((uint32_t)lv[r] & ((1u << kFirstBits) - 1)) * kCountCopies + copy],
                 in ? 1u : 0u);
     }
-    rg.write(s_red, a.lranges + 4 * (size_t)tt);  // (holds a barrier)
-    write_counts(s_cnt, a.lcount + (size_t)tt * kMaxBins);
+    rg.write<true>(sh.red, a.lranges + 4 * (size_t)tt);  // (holds a barrier)
+    write_counts<true>(s_cnt, a.lcount + (size_t)tt * kMaxBins);
     block_sync();  // the counts are read before they are cleared
   }
 }
@@ -153,13 +224,18 @@ __device__ void long_plan(const BArgs& a, uint32_t tiles, uint32_t (*red)[TWV]) 
   uint4 v = make_uint4(0xffu, 0u, 0xffffffffu, 0u);
   uint32_t bad = 0, longest = 0;
   for (uint32_t i = t; i < tiles; i += TT) {
-    const uint4 x = reinterpret_cast<const uint4*>(a.lranges)[i];
+    const uint32_t* r4 = a.lranges + 4 * (size_t)i;
+    const uint4 x = make_uint4(load_agent(r4), load_agent(r4 + 1), load_agent(r4 + 2),
+                               load_agent(r4 + 3));
     v.x = min(v.x, x.x);
     v.y = max(v.y, x.y & 0xffu);
     bad |= x.y & 0x80000000u;
     v.z = min(v.z, x.z);
     v.w = max(v.w, x.w);
-    longest = max(longest, a.tdesc[i].lo + (uint32_t)a.tdesc[i].cnt);
+  }
+  for (uint32_t k = t; k < a.ctl->count[kListLong]; k += TT) {
+    const int64_t s = a.lists[2 * kSubLists * a.seg_cap + k];
+    longest = max(longest, (uint32_t)(a.offsets[s + 1] - a.offsets[s]));
   }
   v.y |= bad;
   stage_ranges(v, red);
@@ -170,7 +246,9 @@ __device__ void long_plan(const BArgs& a, uint32_t tiles, uint32_t (*red)[TWV]) 
   if (t != 0) return;
   const uint4 all = collect_ranges(red, TWV);
   for (int i = 0; i < TWV; ++i) longest = max(longest, s_longest[i]);
-  Plan p = {};
+  __shared__ Plan p;  // (its arrays are indexed: scratch memory otherwise)
+  p.ok = 0;
+  p.nscatter = 0;
   if (all.y >> 31) {
     atomicOr(a.flags, kFlagRange);
   } else {
@@ -182,35 +260,29 @@ __device__ void long_plan(const BArgs& a, uint32_t tiles, uint32_t (*red)[TWV]) 
   *a.plan = p;
 }
 
-// Prefixes of the count rows over each queue's tiles, per digit: pass s's
+// Prefixes of the count rows over each queue's tiles, per digit: a scatter pass's
 // counts, or (FINAL) the final digit's counts and length sums. A queue of at
 // most kLongRowsFew tiles is one item, a wave per 64 digits running down the
 // rows; a longer one is an item per PD digits (64 or 128 bytes of a row), its
 // rows split over the workgroup's lanes in NC runs, each read twice: once for
 // the runs' sums, once to write the prefixes.
 template <bool FINAL>
-__global__ __launch_bounds__(TT) void l_scan(BArgs a, int s) {
-  constexpr int PD = FINAL ? 16 : 32;
+struct ScanLds {
+  static constexpr int PD = FINAL ? 16 : 32;
+  uint32_t c[TWV][PD];
+  uint64_t w[FINAL ? TWV : 1][PD];
+};
+// Worker `me` of `workers`, a workgroup each.
+template <bool FINAL>
+__device__ void scan_rows(const BArgs& a, uint32_t me, uint32_t workers, ScanLds<FINAL>& sh) {
+  constexpr int PD = ScanLds<FINAL>::PD;
   constexpr int RL = kWave / PD;   // runs of a wave
   static_assert(kMaxBins / PD <= kLongScanParts, "an item per part");
-  __shared__ uint32_t s_c[TWV][PD];
-  __shared__ uint64_t s_w[FINAL ? TWV : 1][PD];
-  __shared__ uint32_t s_red[4][TWV];
-  const uint32_t tiles = a.ctl->long_run;
-  if (tiles == 0) return;
-  const bool planner = !FINAL && s == 0;  // workgroup 0 makes the plan instead
-  if (planner && blockIdx.x == 0) {
-    long_plan(a, tiles, s_red);
-    return;
-  }
-  if (FINAL && !a.plan->ok) return;
-  if (!FINAL && s > 0 && (!a.plan->ok || s >= (int)a.plan->nscatter - 1)) return;
   const uint32_t items = a.ctl->long_items;
-  const uint32_t workers = gridDim.x - (planner ? 1u : 0u);
   const int w = wave_no();
   const int lane = lane_id();
   const uint32_t nb = FINAL ? a.plan->nbins[a.plan->nscatter - 1] : (uint32_t)kMaxBins;
-  constexpr int U = FINAL ? 8 : 16;  // rows in flight
+  constexpr int U = 8;  // rows in flight
   // Adds rows [r0, r1) of digit d, and with WRITE stores every row's prefix.
   auto run_rows = [&](auto write, uint32_t r0, uint32_t r1, uint32_t d, uint32_t& c,
                       uint64_t& l) {
@@ -220,7 +292,7 @@ __global__ __launch_bounds__(TT) void l_scan(BArgs a, int s) {
       for (int u = 0; u < U; ++u) {
         const size_t at = (size_t)min(r + u, r1 - 1) * kMaxBins + d;
         if constexpr (FINAL) x[u] = a.lfinal[at];
-        else x[u] = a.lcount[at];
+        else x[u] = load_agent(a.lcount + at);
       }
 #pragma unroll
       for (int u = 0; u < U; ++u) {
@@ -240,8 +312,8 @@ __global__ __launch_bounds__(TT) void l_scan(BArgs a, int s) {
       }
     }
   };
-  for (uint32_t it = blockIdx.x - (planner ? 1u : 0u); it < items; it += workers) {
-    const uint32_t im = a.imap[it];
+  for (uint32_t it = me; it < items; it += workers) {
+    const uint32_t im = load_agent(a.imap + it);
     const uint32_t k = im / kLongScanParts, part = im % kLongScanParts;
     const uint32_t row0 = a.tstart[k], rows = a.tstart[k + 1] - row0;
     if (rows <= kLongRowsFew) {  // (uniform)
@@ -272,18 +344,44 @@ __global__ __launch_bounds__(TT) void l_scan(BArgs a, int s) {
       }
     }
     if (lane >= kWave - PD) {
-      s_c[w][dl] = ic;
-      if constexpr (FINAL) s_w[w][dl] = il;
+      sh.c[w][dl] = ic;
+      if constexpr (FINAL) sh.w[w][dl] = il;
     }
     block_sync();
     c = ic - c;
     l = il - l;
     for (int v = 0; v < w; ++v) {  // (w is uniform)
-      c += s_c[v][dl];
-      if constexpr (FINAL) l += s_w[v][dl];
+      c += sh.c[v][dl];
+      if constexpr (FINAL) l += sh.w[v][dl];
     }
     block_sync();  // the sums are read before the next item writes them
     if (d < nb) run_rows(std::true_type{}, r0, r1, d, c, l);
+  }
+}
+
+__global__ __launch_bounds__(TT) void l_count(BArgs a) {
+  __shared__ WorkLds work;
+  __shared__ union {
+    CountLds count;
+    ScanLds<false> scan;
+  } sh;
+  const uint32_t tiles = a.ctl->long_run;
+  if (tiles == 0) return;
+  for (bool begin = true; next_work(a, kRunCount, 2, begin, work); begin = false) {
+    const uint32_t me = (uint32_t)__builtin_amdgcn_readfirstlane((int)work.me);
+    if (work.phase == 0) {  // (uniform)
+      uint32_t lo, hi;
+      tile_run(tiles, me, lo, hi);
+      count_tiles(a, lo, hi, sh.count);
+      continue;
+    }
+    // the first share makes the plan, the others scan (it too, if alone)
+    const uint32_t planner = gridDim.x > 1 ? 1 : 0;
+    if (me == 0) {
+      long_plan(a, tiles, sh.count.red);
+      block_sync();
+    }
+    if (me >= planner) scan_rows<false>(a, me - planner, gridDim.x - planner, sh.scan);
   }
 }
 
@@ -296,7 +394,7 @@ __device__ __forceinline__ uint32_t queue_digit_start(const BArgs& a, const Long
   return block_excl_scan_u32<TT>(a.hist[last] + a.lcount[last], scan32, sum);
 }
 
-// Small batches: what l_scan would have left for tile `tt`, summed here from
+// Small batches: what a scan would have left for tile `tt`, summed here from
 // the queue's own count rows (every thread its digit): the counts and length
 // sums of the tiles before it, and of all of them.
 struct Folded {
@@ -314,7 +412,7 @@ __device__ __forceinline__ Folded fold_rows(const BArgs& a, const LongTileDesc& 
     for (uint32_t u = 0; u < U; ++u) {
       const size_t at = (size_t)min(r + u, r1 - 1) * kMaxBins + threadIdx.x;
       if constexpr (FINAL) v[u] = a.lfinal[at];
-      else v[u] = a.lcount[at];
+      else v[u] = load_agent(a.lcount + at);  // (counted in this launch)
     }
 #pragma unroll
     for (uint32_t u = 0; u < U; ++u) {
@@ -340,8 +438,8 @@ struct LongFirstLds {
 };
 
 // Scatter of this workgroup's tiles by a 10-bit digit: the first pass (FIRST:
-// from the requests, by the low length bits) or a middle pass. FOLD: no l_scan
-// ran after the counts.
+// from the requests, by the low length bits) or a middle pass. FOLD: the
+// counts were not scanned, and are of this launch (as the elements are).
 template <bool FIRST, bool FOLD, typename Codec>
 __device__ void long_scatter(const BArgs& a, Codec kc, int s, uint32_t lo, uint32_t hi,
                              LongFirstLds& sh) {
@@ -360,7 +458,7 @@ __device__ void long_scatter(const BArgs& a, Codec kc, int s, uint32_t lo, uint3
         pv[r] = a.priority[x.first + i];
         lv[r] = (uint32_t)a.length[x.first + i];
       } else {
-        const uint64_t v = in[x.at + i];
+        const uint64_t v = FOLD ? load_agent(in + x.at + i) : in[x.at + i];
         pv[r] = (uint32_t)(v >> 32);
         lv[r] = (uint32_t)v;
       }
@@ -405,7 +503,7 @@ __device__ void long_scatter(const BArgs& a, Codec kc, int s, uint32_t lo, uint3
     if (tt + 1 < hi) {  // the next tile's input loads while this one is written
       x = a.tdesc[tt + 1];
       load(x);
-      if constexpr (FOLD) off += a.lcount[(size_t)tt * kMaxBins + t];
+      if constexpr (FOLD) off += load_agent(a.lcount + (size_t)tt * kMaxBins + t);
       else off = a.hist[(size_t)(tt + 1) * kMaxBins + t];
     }
     block_sync();
@@ -423,7 +521,10 @@ __device__ void long_scatter(const BArgs& a, Codec kc, int s, uint32_t lo, uint3
       if (j < cur.cnt) {
         const uint64_t v = sh.stage[j];
         const uint32_t pos = sh.base[digit(v)] + (uint32_t)j;
-        if (pos < room) out[pos] = v;  // (always, for consistent counts)
+        if (pos < room) {  // (always, for consistent counts)
+          if constexpr (FOLD) store_agent(out + pos, v);  // (read in this launch)
+          else out[pos] = v;
+        }
       }
     }
   }
@@ -434,27 +535,13 @@ __global__ __launch_bounds__(TT) void l_first(BArgs a) {
   const uint32_t tiles = a.ctl->long_run;
   if (tiles == 0 || !a.plan->ok) return;
   uint32_t lo, hi;
-  tile_run(tiles, lo, hi);
+  tile_run(tiles, blockIdx.x, lo, hi);
   with_codec(a.plan, [&](auto kc) { long_scatter<true, false>(a, kc, 0, lo, hi, sh); });
 }
 
+// Digit counts of the tiles [lo, hi) in middle pass s.
 template <bool FOLD>
-__global__ __launch_bounds__(TT) void l_mid_scatter(BArgs a, int s) {
-  __shared__ LongFirstLds sh;
-  const uint32_t tiles = a.ctl->long_run;
-  if (tiles == 0 || !a.plan->ok || s >= (int)a.plan->nscatter - 1) return;
-  uint32_t lo, hi;
-  tile_run(tiles, lo, hi);
-  with_codec(a.plan, [&](auto kc) { long_scatter<false, FOLD>(a, kc, s, lo, hi, sh); });
-}
-
-// Digit counts of this workgroup's tiles in middle pass s.
-__global__ __launch_bounds__(TT) void l_mid_count(BArgs a, int s) {
-  __shared__ uint32_t s_cnt[kMaxBins * kCountCopies];
-  const uint32_t tiles = a.ctl->long_run;
-  if (tiles == 0 || !a.plan->ok || s >= (int)a.plan->nscatter - 1) return;
-  uint32_t lo, hi;
-  tile_run(tiles, lo, hi);
+__device__ void mid_count(const BArgs& a, int s, uint32_t lo, uint32_t hi, uint32_t* s_cnt) {
   const int t = threadIdx.x;
   const uint32_t copy = (uint32_t)lane_id() & (kCountCopies - 1);
   const uint32_t dshift = a.plan->shift[s];
@@ -463,7 +550,10 @@ __global__ __launch_bounds__(TT) void l_mid_count(BArgs a, int s) {
       const LongTileDesc x = a.tdesc[tt];
       uint64_t e[LR];
 #pragma unroll
-      for (int r = 0; r < LR; ++r) e[r] = a.keys[(s - 1) & 1][x.at + min(r * TT + t, x.cnt - 1)];
+      for (int r = 0; r < LR; ++r) {
+        const uint64_t* in = (s & 1 ? a.keys[0] : a.keys[1]) + x.at + min(r * TT + t, x.cnt - 1);
+        e[r] = FOLD ? load_agent(in) : *in;
+      }
       clear_counts(s_cnt);
       block_sync();
 #pragma unroll
@@ -471,10 +561,66 @@ __global__ __launch_bounds__(TT) void l_mid_count(BArgs a, int s) {
         atomicAdd(&s_cnt[((kc.u2_of(e[r]) >> dshift) & (kMaxBins - 1)) * kCountCopies + copy],
                   r * TT + t < x.cnt ? 1u : 0u);
       block_sync();
-      write_counts(s_cnt, a.lcount + (size_t)tt * kMaxBins);
+      write_counts<true>(s_cnt, a.lcount + (size_t)tt * kMaxBins);
       block_sync();  // the counts are read before they are cleared
     }
   });
+}
+
+__global__ __launch_bounds__(TT, 8) void l_mid_rows(BArgs a, int s, PhaseKernel kernel) {
+  __shared__ WorkLds work;
+  __shared__ union {
+    uint32_t cnt[kMaxBins * kCountCopies];
+    ScanLds<false> scan;
+  } sh;
+  const uint32_t tiles = a.ctl->long_run;
+  if (tiles == 0 || !a.plan->ok || s >= (int)a.plan->nscatter - 1) return;
+  for (bool begin = true; next_work(a, kernel, 2, begin, work); begin = false) {
+    const uint32_t me = (uint32_t)__builtin_amdgcn_readfirstlane((int)work.me);
+    if (work.phase == 0) {  // (uniform)
+      uint32_t lo, hi;
+      tile_run(tiles, me, lo, hi);
+      mid_count<false>(a, s, lo, hi, sh.cnt);
+    } else {
+      scan_rows<false>(a, me, gridDim.x, sh.scan);
+    }
+  }
+}
+
+__global__ __launch_bounds__(TT) void l_mid_scatter(BArgs a, int s) {
+  __shared__ LongFirstLds sh;
+  const uint32_t tiles = a.ctl->long_run;
+  if (tiles == 0 || !a.plan->ok || s >= (int)a.plan->nscatter - 1) return;
+  uint32_t lo, hi;
+  tile_run(tiles, blockIdx.x, lo, hi);
+  with_codec(a.plan, [&](auto kc) { long_scatter<false, false>(a, kc, s, lo, hi, sh); });
+}
+
+// All middle passes of a small batch in one launch: count and scatter of each.
+// (Not for larger ones: the scatter is slower here than alone, 96 us against 87
+// over 2^24 requests, and the counts have one workgroup per compute unit
+// instead of two; four queues of 2^22 with 31-bit lengths 610 us so, 540 in
+// separate launches. 70 queues of 20,000 with such lengths 112 us so, 107 in
+// separate launches.)
+__global__ __launch_bounds__(TT) void l_mid(BArgs a) {
+  __shared__ WorkLds work;
+  __shared__ union {
+    uint32_t cnt[kMaxBins * kCountCopies];
+    LongFirstLds scatter;
+  } sh;
+  const uint32_t tiles = a.ctl->long_run;
+  if (tiles == 0 || !a.plan->ok || a.plan->nscatter <= 2) return;
+  const uint32_t phases = 2 * (a.plan->nscatter - 2);
+  for (bool begin = true; next_work(a, kRunMid, phases, begin, work); begin = false) {
+    const uint32_t phase = (uint32_t)__builtin_amdgcn_readfirstlane((int)work.phase);
+    const int s = 1 + (int)(phase >> 1);
+    uint32_t lo, hi;
+    tile_run(tiles, (uint32_t)__builtin_amdgcn_readfirstlane((int)work.me), lo, hi);
+    if ((phase & 1) == 0)
+      mid_count<true>(a, s, lo, hi, sh.cnt);
+    else
+      with_codec(a.plan, [&](auto kc) { long_scatter<false, true>(a, kc, s, lo, hi, sh.scatter); });
+  }
 }
 
 __global__ __launch_bounds__(TT) void l_histF(BArgs a) {
@@ -483,7 +629,7 @@ __global__ __launch_bounds__(TT) void l_histF(BArgs a) {
   const Plan* pl = a.plan;
   if (tiles == 0 || !pl->ok) return;
   uint32_t lo, hi;
-  tile_run(tiles, lo, hi);
+  tile_run(tiles, blockIdx.x, lo, hi);
   const int s = (int)pl->nscatter - 1;
   const TileDigit dig = {pl->shift[s], pl->nbits[s]};
   with_codec(pl, [&](auto kc) {
@@ -498,6 +644,12 @@ __global__ __launch_bounds__(TT) void l_histF(BArgs a) {
       block_sync();  // the bins are read before they are cleared
     }
   });
+}
+
+__global__ __launch_bounds__(TT) void l_scanF(BArgs a) {
+  __shared__ ScanLds<true> sh;
+  if (a.ctl->long_run == 0 || !a.plan->ok) return;
+  scan_rows<true>(a, blockIdx.x, gridDim.x, sh);
 }
 
 struct LongFinalLds : PlaceLds {
@@ -616,7 +768,7 @@ __global__ __launch_bounds__(TT) void l_final(BArgs a) {
   const uint32_t tiles = a.ctl->long_run;
   if (tiles == 0 || !a.plan->ok) return;
   uint32_t lo, hi;
-  tile_run(tiles, lo, hi);
+  tile_run(tiles, blockIdx.x, lo, hi);
   if (a.plan->W == 32 && a.plan->sum64) {
     KeyCodec32 kc;
     kc.init(kFirstBits, a.plan);
@@ -626,39 +778,40 @@ __global__ __launch_bounds__(TT) void l_final(BArgs a) {
   }
 }
 
-// The middle passes, final counts and final pass; FOLD: without l_scan launches.
-template <bool FOLD, typename Grid>
-void launch_passes(const BArgs& a, unsigned scan, Grid&& grid, hipStream_t st) {
-  static const int r_count = resident_groups(l_count), r_histF = resident_groups(l_histF),
-                   r_mid = resident_groups(l_mid_scatter<FOLD>),
-                   r_final = resident_groups(l_final<FOLD>);
-  for (int s = 1; s <= max_mid_passes(kFirstBits); ++s) {
-    hipLaunchKernelGGL(l_mid_count, grid(r_count), dim3(TT), 0, st, a, s);
-    if (!FOLD) hipLaunchKernelGGL(l_scan<false>, dim3(scan), dim3(TT), 0, st, a, s);
-    hipLaunchKernelGGL(l_mid_scatter<FOLD>, grid(r_mid), dim3(TT), 0, st, a, s);
-  }
-  hipLaunchKernelGGL(l_histF, grid(r_histF), dim3(TT), 0, st, a);
-  if (!FOLD) hipLaunchKernelGGL(l_scan<true>, dim3(scan), dim3(TT), 0, st, a, 0);
-  hipLaunchKernelGGL(l_final<FOLD>, grid(r_final), dim3(TT), 0, st, a);
-}
-
 }  // namespace
 
 hipError_t launch_long_queues(const BArgs& a, hipStream_t st) {
-  static const int r_count = resident_groups(l_count), r_first = resident_groups(l_first);
   auto grid = [&](int resident) {
     return dim3((unsigned)std::max<int64_t>(1, std::min<int64_t>(resident, a.max_tiles)));
   };
-  const int64_t queues =
-      std::min<int64_t>(a.num_segments, (int64_t)(a.long_cap / (kSegLargeCap + 1)));
-  const unsigned scan = (unsigned)std::min<uint64_t>(1024, long_items_max(a.long_cap, queues));
-  hipLaunchKernelGGL(l_count, grid(r_count), dim3(TT), 0, st, a);
-  hipLaunchKernelGGL(l_scan<false>, dim3(scan + 1), dim3(TT), 0, st, a, 0);
-  hipLaunchKernelGGL(l_first, grid(r_first), dim3(TT), 0, st, a);
-  if (a.max_tiles <= kFoldTiles && a.max_tiles <= kFoldRows * (uint64_t)a.num_segments)
-    launch_passes<true>(a, scan, grid, st);
-  else
-    launch_passes<false>(a, scan, grid, st);
+  auto launch = [&](auto kernel, int resident, auto... more) {
+    hipLaunchKernelGGL(kernel, grid(resident), dim3(TT), 0, st, a, more...);
+  };
+  static const int r_count = resident_groups(l_count), r_first = resident_groups(l_first),
+                   r_histF = resident_groups(l_histF);
+  const int most = (int)kMaxShares;
+  launch(l_count, std::min(r_count, most));
+  launch(l_first, r_first);
+  if (a.max_tiles <= kFoldTiles && a.max_tiles <= kFoldRows * (uint64_t)a.num_segments) {
+    static const int r_mid = resident_groups(l_mid), r_final = resident_groups(l_final<true>);
+    launch(l_mid, std::min(r_mid, most));
+    launch(l_histF, r_histF);
+    launch(l_final<true>, r_final);
+  } else {
+    static const int r_rows = resident_groups(l_mid_rows), r_mid = resident_groups(l_mid_scatter),
+                     r_final = resident_groups(l_final<false>);
+    static_assert(max_mid_passes(kFirstBits) <= kRunMidLast - kRunMid + 1, "counters per pass");
+    for (int s = 1; s <= max_mid_passes(kFirstBits); ++s) {
+      launch(l_mid_rows, std::min(r_rows, most), s, (PhaseKernel)(kRunMid + s - 1));
+      launch(l_mid_scatter, r_mid, s);
+    }
+    launch(l_histF, r_histF);
+    const int64_t queues =
+        std::min<int64_t>(a.num_segments, (int64_t)(a.long_cap / (kSegLargeCap + 1)));
+    const unsigned scan = (unsigned)std::min<uint64_t>(1024, long_items_max(a.long_cap, queues));
+    hipLaunchKernelGGL(l_scanF, dim3(scan), dim3(TT), 0, st, a);
+    launch(l_final<false>, r_final);
+  }
   return hipGetLastError();
 }
 

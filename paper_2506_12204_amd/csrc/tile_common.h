@@ -44,6 +44,7 @@ struct TileRanges {
   // The workgroup's ranges to out[0 .. 3]. Holds a barrier. (Carried ranks:
   // the caller adds rank 0 and sets pmin to the largest carried rank, which
   // then reduces by its maximum.)
+  template <bool AGENT = false>
   __device__ __forceinline__ void write(uint32_t (*red)[TWV], uint32_t* out, bool carried = false);
 };
 
@@ -79,11 +80,21 @@ __device__ __forceinline__ uint4 collect_ranges(const uint32_t (*red)[TWV], int 
   return v;
 }
 
+template <bool AGENT>
 __device__ __forceinline__ void TileRanges::write(uint32_t (*red)[TWV], uint32_t* out,
                                                   bool carried) {
   stage_ranges(make_uint4(pmin, pmax | (bad << 31), lmin, lmax), red, carried);
   block_sync();
-  if (threadIdx.x == 0) *reinterpret_cast<uint4*>(out) = collect_ranges(red, TWV, carried);
+  if (threadIdx.x != 0) return;
+  const uint4 v = collect_ranges(red, TWV, carried);
+  if constexpr (AGENT) {
+    store_agent(out, v.x);
+    store_agent(out + 1, v.y);
+    store_agent(out + 2, v.z);
+    store_agent(out + 3, v.w);
+  } else {
+    *reinterpret_cast<uint4*>(out) = v;
+  }
 }
 
 // Digit counts of a tile, kCountCopies copies of each: cleared (a barrier must
@@ -93,12 +104,15 @@ __device__ __forceinline__ void clear_counts(uint32_t* s_cnt) {
   for (int i = threadIdx.x; i < kMaxBins * kCountCopies / 4; i += TT)
     reinterpret_cast<uint4*>(s_cnt)[i] = make_uint4(0, 0, 0, 0);
 }
+template <bool AGENT = false>
 __device__ __forceinline__ void write_counts(const uint32_t* s_cnt, uint16_t* row) {
   static_assert(kCountCopies == 8, "two quads per digit");
   const int t = threadIdx.x;
   const uint4 c0 = reinterpret_cast<const uint4*>(s_cnt)[2 * t];
   const uint4 c1 = reinterpret_cast<const uint4*>(s_cnt)[2 * t + 1];
-  row[t] = (uint16_t)(c0.x + c0.y + c0.z + c0.w + c1.x + c1.y + c1.z + c1.w);
+  const uint16_t sum = (uint16_t)(c0.x + c0.y + c0.z + c0.w + c1.x + c1.y + c1.z + c1.w);
+  if constexpr (AGENT) store_agent(row + t, sum);
+  else row[t] = sum;
 }
 
 // Turns the waves' counters of a ranked tile into the positions of each

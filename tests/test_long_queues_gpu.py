@@ -116,3 +116,46 @@ def test_range_error_and_next_call(sizes, where, what):
     assert call(p, l) == ss.SEM_OK
     got = (order.cpu().numpy(), wait.cpu().numpy(), ss.totals_to_ints(totals))
     assert_same(got, c_oracle_batched(p, l, off, classes), "after an error")
+
+
+# A kernel of several phases hands its shares out as workgroups start: with one
+# poll a workgroup that is done early takes the shares of those that have not
+# started, and has several in all phases
+@pytest.mark.parametrize("sizes", [[16385], [95 * TILE + 7], [20000] * 70, [17000 + i for i in range(400)]])
+@pytest.mark.parametrize("classes,max_len", [(5, 32768), (9, 2_000_000), (256, 2**31 - 1)])
+def test_shares_taken_over(sizes, classes, max_len, monkeypatch):
+    monkeypatch.setenv("SEMSCHED_CLAIM_POLLS", "1")
+    check(sizes, f"claims {classes}x{max_len}", classes, max_len, seed=classes)
+
+
+# Launches of a batch in a workspace with room for long queues, whether it has
+# any or not: every one costs a caller 3 to 4 us on the host
+@pytest.mark.parametrize("n,segments,most", [(131072, 512, 9), (1 << 22, 4096, 13)])
+def test_launches_with_room_for_long_queues(n, segments, most):
+    import ctypes
+    import torch
+    import paper_2506_12204_amd as ss
+    p, l, off = fuzz_segments([n // segments] * segments, seed=1, classes=4)
+    from tests._lib import to_gpu
+    tp, tl, to = to_gpu(p, l, off.astype(np.int64))
+    ws = torch.empty(ss.workspace_bytes(n, segments), dtype=torch.uint8, device="cuda")
+    order = torch.empty(n, dtype=torch.int32, device="cuda")
+    wait = torch.empty(n, dtype=torch.int64, device="cuda")
+    totals = torch.empty((segments, 5, 2), dtype=torch.int64, device="cuda")
+
+    def call():
+        rc = ss.lib.sem_schedule_batched_async(
+            ss._ptr(tp), ss._ptr(tl), ss._ptr(to), segments, 4, ss._ptr(order), ss._ptr(wait),
+            ss._ptr(totals), ss._ptr(ws), ws.numel(), ss._stream_handle(ws.device))
+        assert rc == ss.SEM_OK
+    call()  # before the capture: occupancies are looked up once
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(g):
+        call()
+    nodes = ctypes.c_size_t(0)
+    rc = ctypes.CDLL("libamdhip64.so").hipGraphGetNodes(ctypes.c_void_p(g.raw_cuda_graph()), None,
+                                                        ctypes.byref(nodes))
+    assert rc == 0
+    print(f"[gpu] {segments} queues: {nodes.value} launches", flush=True)
+    assert nodes.value <= most
