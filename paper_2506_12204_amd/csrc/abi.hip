@@ -41,9 +41,9 @@ Layout layout_for(int64_t n) {
   if (!needs_global(n)) return L;
   L.tiles = (n + kGlobalTile - 1) / kGlobalTile;
   // histogram rows: whole blocks of kHistRows rows, never more than kMaxBlocks
-  // (the one-tile-per-workgroup path's rows: at most kTileRows)
+  // (the one-tile-per-workgroup path has its rows elsewhere: place_tile_rows)
   const size_t blocks = (size_t)std::min<int64_t>(
-      std::max<int64_t>((L.tiles + kHistRows - 1) / kHistRows * kHistRows, kTileRows), kMaxBlocks);
+      (L.tiles + kHistRows - 1) / kHistRows * kHistRows, kMaxBlocks);
   size_t off = kHeaderBytes;
   auto take = [&](size_t bytes) {
     const size_t at = off;
@@ -99,6 +99,24 @@ int no_tiles() {
 bool takes_tiles(int64_t n) {
   return needs_global(n) && n <= kTileMaxItems && !no_tiles() && !force_wide() && !no_compact() &&
          d0_bits() == 10;
+}
+
+// The one-tile-per-workgroup path has more rows than the big-tile path, whose
+// workspace it works in: they lie in what it leaves unused, so that a workspace
+// of the size that path needs holds either. Count rows (2 KB a tile, at most
+// 512 KB) in sub_start, the final digit's (8 KB) behind them for tiles of 1024
+// requests (at most 64) and else in the id arrays (8 bytes per request, and
+// tiles of 2048 and more), the ranges (16 bytes) in the digit totals.
+void place_tile_rows(char* base, const Layout& L, int64_t n, GArgs& g) {
+  constexpr size_t kCountBytes = 2 * (size_t)kMaxBins * kTileRows;
+  static_assert(kCountBytes + 8 * (size_t)kMaxBins * 64 <=
+                    sizeof(uint32_t) * (size_t)kMaxChunks * kMaxBins, "rows fit sub_start");
+  static_assert(16 * (size_t)kTileRows <= sizeof(uint32_t) * kMaxScatter * kMaxBins,
+                "ranges fit the digit totals");
+  g.block_hist = reinterpret_cast<uint32_t*>(base + L.sub_start);
+  g.block_histw = reinterpret_cast<uint64_t*>(
+      base + (tile_rounds(n) == 1 ? L.sub_start + kCountBytes : L.ids0));
+  g.block_ranges = reinterpret_cast<uint32_t*>(base + L.hist_cnt);
 }
 
 // SEMSCHED_SPLIT_MID=1 runs the middle passes as separate launches per phase
@@ -308,7 +326,10 @@ int enqueue_queue(const uint8_t* p, const int32_t* l, int64_t n, int32_t num_cla
     }
   }
   const bool tiled = takes_tiles(n);
-  if (tiled) g.chunked = 0;
+  if (tiled) {
+    g.chunked = 0;
+    place_tile_rows(base, L, n, g);
+  }
   return (tiled ? launch_tile_schedule(g, st, armed ? &ev : nullptr)
                 : launch_global_schedule(g, st, armed ? &ev : nullptr)) == hipSuccess
              ? SEM_OK
@@ -628,7 +649,7 @@ BLayout batched_layout(int64_t S, uint64_t long_cap) {
   L.grab = take(sizeof(GrabLine) * kLists * kSubLists);
   // the medium and wide lists' segments, then the long list
   L.lists = take(4 * (2 * kSubLists * (size_t)list_segment_cap(S) + (size_t)S));
-  if (long_cap > 0) {
+  if (long_cap > kSegLargeCap) {  // (fewer requests are no long queue)
     const uint64_t queues = std::min<uint64_t>((uint64_t)S, long_cap / (kSegLargeCap + 1));
     L.max_tiles = long_max_tiles(long_cap, S);
     const size_t rows = (size_t)kMaxBins * (size_t)L.max_tiles;
@@ -653,11 +674,11 @@ BLayout batched_layout(int64_t S, uint64_t long_cap) {
   return L;
 }
 
-// Largest long-queue capacity whose batched layout fits ws_bytes (0 if only
-// the fixed part does).
+// Largest long-queue capacity whose batched layout fits ws_bytes (0 if that
+// takes no long queue).
 uint64_t long_capacity(int64_t S, size_t ws_bytes) {
-  if (batched_layout(S, 1).total > ws_bytes) return 0;
-  uint64_t lo = 1, hi = ws_bytes / 24 + 1;  // more than 24 bytes per request
+  if (batched_layout(S, kSegLargeCap + 1).total > ws_bytes) return 0;
+  uint64_t lo = kSegLargeCap + 1, hi = ws_bytes / 24 + 1;  // more than 24 bytes per request
   while (hi - lo > 1) {
     const uint64_t mid = lo + (hi - lo) / 2;
     if (batched_layout(S, mid).total <= ws_bytes) lo = mid;

@@ -805,11 +805,9 @@ hipError_t launch_batched(const BArgs& a, hipStream_t st) {
                      st, a, (int)chunk);
   hipLaunchKernelGGL(b_medium, dim3(grid_for(r_medium, S)), dim3(256), 0, st, a);
   hipLaunchKernelGGL(b_wide, dim3(grid_for(r_wide, S)), dim3(kWideThreads), 0, st, a);
-  // Room for fewer requests than the shortest long queue has takes none: there
-  // is then nothing to launch (a long queue all the same is an error that
-  // long_layout raises). 64 queues of 256 with room for all 16,384 requests:
-  // 57 us with nine launches that return at once, 18 without.
-  if (a.long_cap > (uint64_t)kSegLargeCap) {
+  // (no room for a long queue: nothing to launch, and one all the same is an
+  // error that the planner raises)
+  if (a.long_cap > 0) {
     const hipError_t e = launch_long_queues(a, st);
     if (e != hipSuccess) return e;
   }

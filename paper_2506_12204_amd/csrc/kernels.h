@@ -278,6 +278,15 @@ void mark_stage(const StageEvents* ev, int stage, bool after, hipStream_t st);
 // kTileMaxItems requests (tile_sort.hip). Packed keys only (force_wide == 0).
 constexpr int kTileRows = 256;  // most tiles of such a queue
 constexpr int64_t kTileMaxItems = (int64_t)kTileRows * 8192;
+// Its tiles hold 1024 requests times this. Small tiles make more workgroups and
+// shorter chains in each, but every workgroup reads every tile's count rows: 64
+// tiles are best up to 2^18 requests (262,144: 36.8 us in 64 tiles, 37.9 in
+// 128, 44.7 in 256), 128 above (524,288: 45.0 us in 64, 42.8 in 128, 48.0 in
+// 256), and from 2^20 as many of 8192 as it takes, up to one per CU (2^21: 65 us
+// in 256, 79 in the big-tile path; 2,500,000: 114 in 306, 79).
+constexpr int tile_rounds(int64_t n) {
+  return n <= 64ll * 1024 ? 1 : n <= 64ll * 2048 ? 2 : n <= 128ll * 4096 ? 4 : 8;
+}
 // Workgroups of its middle-pass kernel, which wait for one another and so must
 // all be resident: at most `resident`, what the device holds at once of that
 // kernel alone (a smaller or partitioned device: 32 compute units hold 32 to

@@ -594,16 +594,12 @@ hipError_t launch_tiles(const GArgs& a, hipStream_t st, const StageEvents* ev) {
 }  // namespace
 
 hipError_t launch_tile_schedule(const GArgs& a, hipStream_t st, const StageEvents* ev) {
-  // Small tiles make more workgroups and shorter chains in each, but every
-  // workgroup reads every tile's count rows: 64 tiles are best up to 2^18
-  // requests (262,144: 36.8 us in 64 tiles, 37.9 in 128, 44.7 in 256), 128
-  // above (524,288: 45.0 us in 64, 42.8 in 128, 48.0 in 256), and from 2^20 as
-  // many of 8192 as it takes, up to one per CU (2^21: 65 us in 256, 79 in the
-  // big-tile path; 2,500,000: 114 in 306, 79).
-  if (a.n <= 64ll * TT) return launch_tiles<1>(a, st, ev);
-  if (a.n <= 64ll * TT * 2) return launch_tiles<2>(a, st, ev);
-  if (a.n <= 128ll * TT * 4) return launch_tiles<4>(a, st, ev);
-  return launch_tiles<8>(a, st, ev);
+  switch (tile_rounds(a.n)) {
+    case 1: return launch_tiles<1>(a, st, ev);
+    case 2: return launch_tiles<2>(a, st, ev);
+    case 4: return launch_tiles<4>(a, st, ev);
+    default: return launch_tiles<8>(a, st, ev);
+  }
 }
 
 }  // namespace semsched

@@ -98,6 +98,40 @@ def test_batched_workspace_sizes(ss):
     assert ss.lib.sem_check(ctypes.c_void_p(0), ctypes.c_void_p(0)) == ss.SEM_EINVAL
 
 
+# Workspace sizes that callers may have kept from an earlier build of the library
+# (its functions' results there): a workspace of such a size is still enough.
+KEPT_QUEUE = {16385: 2582272, 17000: 2596608, 50003: 3486976, 65536: 3896064, 65537: 3909632,
+              131073: 5679360, 262145: 9218816, 524289: 16297728, 1048576: 30441984,
+              2097152: 58757632, 10000019: 272173824, 67108864: 1663136256}
+KEPT_COST = {16385: 2648320, 50003: 3687424, 65537: 4172288, 262145: 10267904,
+             1048576: 34636544, 2097152: 67146496, 67108864: 1931571968}
+KEPT_INSERT = {(100000, 500): 15616, (100000, 17000): 2876160, (1048576, 70000): 5163264,
+               (67108864, 1048576): 47749888}
+KEPT_BATCHED = {(0, 1): 20992, (300, 1): 42496, (16384, 1): 432128, (17, 126490): 1553664,
+                (16384, 64): 432640, (131072, 512): 3278080, (20000, 1): 2668288,
+                (1048576, 16): 25811712, (16777216, 16): 411516672, (20000000, 1000): 494720256}
+
+
+def test_kept_workspace_sizes_are_enough(ss):
+    for n, kept in KEPT_QUEUE.items():
+        assert ss.workspace_bytes(n, 1) <= kept, n
+    for n, kept in KEPT_COST.items():
+        assert ss.lib.sem_cost_workspace_bytes(n) <= kept, n
+    for (n_old, m), kept in KEPT_INSERT.items():
+        assert ss.lib.sem_insert_workspace_bytes(n_old, m) <= kept, (n_old, m)
+    for (n, s), kept in KEPT_BATCHED.items():
+        assert ss.workspace_bytes(n, s) <= kept, (n, s)
+
+
+def test_workspace_sizes_never_shrink(ss):
+    # a workspace for n requests holds every smaller queue
+    sizes = sorted(set(list(KEPT_QUEUE) + [1, 1000, 16384, 16385, (1 << 21) + 1, 1 << 22]))
+    for f in (lambda n: ss.workspace_bytes(n, 1), lambda n: ss.workspace_bytes(n, 7),
+              ss.lib.sem_cost_workspace_bytes):
+        need = [f(n) for n in sizes]
+        assert need == sorted(need)
+
+
 def test_binding_type_checks(ss):
     import torch
     p = torch.zeros(4, dtype=torch.uint8)

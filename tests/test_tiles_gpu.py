@@ -132,3 +132,28 @@ def test_replayed_graph_equals_eager():
         torch.cuda.synchronize()
         got = (s.order.cpu().numpy(), s.wait.cpu().numpy(), ss.totals_to_ints(s.totals))
         assert_same(got, c_oracle_queue(p, l), f"replay {seed}")
+
+
+# The tiles' rows lie in parts of the workspace that this path leaves unused: the
+# most rows of every tile size, and nothing written past the workspace's end
+@pytest.mark.parametrize("n", [16385, 65535, 65537, 1 << 17, (1 << 17) + 1, 1 << 19,
+                               (1 << 19) + 1, 1 << 21])
+@pytest.mark.parametrize("classes,max_len", [(5, 4096), (256, 2**31 - 1)])
+def test_rows_inside_the_workspace(n, classes, max_len):
+    import torch
+    import paper_2506_12204_amd as ss
+    p, l = fuzz_queue(n, seed=n, classes=classes, max_len=max_len)
+    tp, tl = to_gpu(p, l)
+    size = ss.workspace_bytes(n, 1)
+    ws = torch.full((size + 65536,), 0xA5, dtype=torch.uint8, device="cuda")
+    order = torch.empty(n, dtype=torch.int32, device="cuda")
+    wait = torch.empty(n, dtype=torch.int64, device="cuda")
+    totals = torch.empty((257, 2), dtype=torch.int64, device="cuda")
+    stream = ss._stream_handle(ws.device)
+    print(f"[gpu] rows n={n} {classes}x{max_len}", flush=True)
+    rc = ss.lib.sem_schedule_async(ss._ptr(tp), ss._ptr(tl), n, ss._ptr(order), ss._ptr(wait),
+                                   ss._ptr(totals), ss._ptr(ws), size, stream)
+    assert rc == ss.SEM_OK and ss.lib.sem_check(ss._ptr(ws), stream) == ss.SEM_OK
+    assert bool((ws[size:] == 0xA5).all())
+    assert_same((order.cpu().numpy(), wait.cpu().numpy(), ss.totals_to_ints(totals)),
+                c_oracle_queue(p, l), "rows")
