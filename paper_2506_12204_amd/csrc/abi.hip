@@ -422,9 +422,9 @@ int enqueue_insert(const uint8_t* p, const int32_t* l, int64_t n_old, int64_t m,
   return launch_insert(a, st, before, after) == hipSuccess ? SEM_OK : SEM_EDEVICE;
 }
 
-// Workspace of a comparison-policy schedule. SJF runs the queue kernels on a
-// zeroed rank array first, so its layout starts with the queue workspace
-// (error flags at offset 0) and that array; FCFS and HPJF use the header's
+// Workspace of a comparison-policy schedule. SJF runs the queue kernels first,
+// up to the LDS size on a zeroed rank array, so its layout starts with the
+// queue workspace (error flags at offset 0) and that array; FCFS and HPJF use the header's
 // flag word. Then the policy kernels' tables.
 struct PolLayout {
   size_t zeros = 0, pmax = 0, rsum = 0, tab_cnt = 0, tab_len = 0, ctot_cnt = 0, ctot_len = 0,
@@ -441,7 +441,7 @@ PolLayout policy_layout(int policy, int64_t n) {
   };
   const size_t ranges = (size_t)std::max<int64_t>(policy_ranges(n), 1);
   const size_t blocks = (size_t)std::max<int64_t>(policy_blocks(n), 1);
-  if (policy == SEM_POLICY_SJF) L.zeros = take(((size_t)n + 3) / 4 * 4);
+  if (policy == SEM_POLICY_SJF && !needs_global(n)) L.zeros = take(((size_t)n + 3) / 4 * 4);
   L.pmax = take(4);
   if (policy == SEM_POLICY_FCFS) L.rsum = take(8 * ranges);
   if (policy == SEM_POLICY_HPJF) {

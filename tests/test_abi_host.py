@@ -123,6 +123,15 @@ def test_kept_workspace_sizes_are_enough(ss):
         assert ss.workspace_bytes(n, s) <= kept, (n, s)
 
 
+def test_sjf_workspace_holds_no_rank_array(ss):
+    # above the LDS size the sort itself leaves the ranks out of the order: beside
+    # the queue's workspace only the class sums (16 * 256 bytes per workgroup of
+    # four 4096-position waves) and a few words
+    for n in (1 << 24, 1 << 26):
+        extra = ss.lib.sem_policy_workspace_bytes(ss.POLICY_SJF, n) - ss.workspace_bytes(n, 1)
+        assert extra <= 4096 * (n // 16384 + 1) + 4096
+
+
 def test_workspace_sizes_never_shrink(ss):
     # a workspace for n requests holds every smaller queue
     sizes = sorted(set(list(KEPT_QUEUE) + [1, 1000, 16384, 16385, (1 << 21) + 1, 1 << 22]))
