@@ -227,7 +227,9 @@ int sem_schedule_policy(int policy, const uint8_t *priority, const int32_t *leng
                         sem_i128 *totals_out);
 
 /* Workspace size in bytes of sem_schedule_policy_async (0 for an unknown
- * policy or n < 0). */
+ * policy or n < 0). The call also takes a smaller one, with fewer and longer
+ * ranges of positions (slower below 8 million requests), as long as it holds
+ * their tables: the size this function gave when all ranges were 4096. */
 size_t sem_policy_workspace_bytes(int policy, int64_t n);
 
 /* Asynchronous sem_schedule_policy: a caller-owned DEVICE workspace of at

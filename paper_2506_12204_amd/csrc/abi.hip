@@ -431,7 +431,9 @@ struct PolLayout {
          part = 0, sink = 0, total = 0;
 };
 
-PolLayout policy_layout(int policy, int64_t n) {
+// `least`: with the fewest ranges, which every workspace has room for; a kept
+// size of an earlier build, whose ranges were all of that length, is enough.
+PolLayout policy_layout(int policy, int64_t n, bool least = false) {
   PolLayout L;
   size_t off = policy == SEM_POLICY_SJF ? align_up(layout_for(n).total) : kHeaderBytes;
   auto take = [&](size_t bytes) {
@@ -439,8 +441,9 @@ PolLayout policy_layout(int policy, int64_t n) {
     off = align_up(off + bytes);
     return at;
   };
-  const size_t ranges = (size_t)std::max<int64_t>(policy_ranges(n), 1);
-  const size_t blocks = (size_t)std::max<int64_t>(policy_blocks(n), 1);
+  const int64_t r = least ? policy_ranges_least(n) : policy_ranges(n);
+  const size_t ranges = (size_t)std::max<int64_t>(r, 1);
+  const size_t blocks = (size_t)std::max<int64_t>(policy_blocks(r), 1);
   if (policy == SEM_POLICY_SJF && !needs_global(n)) L.zeros = take(((size_t)n + 3) / 4 * 4);
   L.pmax = take(4);
   if (policy == SEM_POLICY_FCFS) L.rsum = take(8 * ranges);
@@ -539,7 +542,7 @@ hipError_t no_class_totals(hipStream_t st, hipEvent_t before, hipEvent_t after) 
 }
 
 int enqueue_policy(int policy, const uint8_t* p, const int32_t* l, int64_t n, int32_t* order,
-                   int64_t* wait, sem_i128* totals, void* ws, hipStream_t st) {
+                   int64_t* wait, sem_i128* totals, void* ws, size_t ws_bytes, hipStream_t st) {
   if (policy == SEM_POLICY_SEMANTIC)
     return enqueue_queue(p, l, n, SEM_MAX_CLASSES, order, wait, totals, ws, st);
   char* base = static_cast<char*>(ws);
@@ -552,9 +555,10 @@ int enqueue_policy(int policy, const uint8_t* p, const int32_t* l, int64_t n, in
       return SEM_EDEVICE;
     return SEM_OK;
   }
-  const PolLayout L = policy_layout(policy, n);
+  const bool least = ws_bytes < policy_layout(policy, n).total;
+  const PolLayout L = policy_layout(policy, n, least);
   PolArgs a = {};
-  a.range = policy_range(n);
+  a.range = least ? kPolRangeMax : policy_range(n);
   a.priority = p;
   a.length = l;
   a.n = n;
@@ -894,11 +898,12 @@ int sem_schedule_policy_async(int policy, const uint8_t* priority, const int32_t
   if (!known_policy(policy)) return SEM_EINVAL;
   const int rc = check_queue_args(priority, length, n, order_out, wait_out, totals_out);
   if (rc != SEM_OK) return rc;
-  if (!workspace || ws_bytes < sem_policy_workspace_bytes(policy, n) ||
-      (reinterpret_cast<uintptr_t>(workspace) % kAlign) != 0)
+  const size_t least = policy == SEM_POLICY_SEMANTIC ? sem_workspace_bytes(n, 1)
+                                                     : policy_layout(policy, n, true).total;
+  if (!workspace || ws_bytes < least || (reinterpret_cast<uintptr_t>(workspace) % kAlign) != 0)
     return SEM_EINVAL;
   return enqueue_policy(policy, priority, length, n, order_out, wait_out, totals_out, workspace,
-                        static_cast<hipStream_t>(stream));
+                        ws_bytes, static_cast<hipStream_t>(stream));
 }
 
 int sem_schedule_policy(int policy, const uint8_t* priority, const int32_t* length, int64_t n,
@@ -908,11 +913,13 @@ int sem_schedule_policy(int policy, const uint8_t* priority, const int32_t* leng
   if (rc != SEM_OK) return rc;
   std::lock_guard<std::mutex> g(state().mu);
   void* ws = nullptr;
-  rc = cached_workspace(sem_policy_workspace_bytes(policy, n), &ws);
+  const size_t need = sem_policy_workspace_bytes(policy, n);
+  rc = cached_workspace(need, &ws);
   if (rc != SEM_OK) return rc;
   const hipStream_t st = state().stream;
   return run_blocking(ws, st, [&] {
-    return enqueue_policy(policy, priority, length, n, order_out, wait_out, totals_out, ws, st);
+    return enqueue_policy(policy, priority, length, n, order_out, wait_out, totals_out, ws, need,
+                          st);
   });
 }
 

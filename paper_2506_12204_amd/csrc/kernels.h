@@ -345,6 +345,7 @@ hipError_t launch_insert(const InsArgs& a, hipStream_t st, hipEvent_t before, hi
 // 8,192 ranges; 2.1 million take 2048: HPJF 110 -> 71 us, FCFS 43 -> 38).
 constexpr int kPolRangeMin = 512;
 constexpr int64_t kPolRangeEdges[] = {1ll << 19, 1ll << 21, 1ll << 23};
+constexpr int kPolRangeMax = kPolRangeMin << 3;
 inline int policy_range(int64_t n) {
   int len = kPolRangeMin;
   for (int64_t edge : kPolRangeEdges)
@@ -352,7 +353,8 @@ inline int policy_range(int64_t n) {
   return len;
 }
 struct PolArgs {
-  int32_t range;            // policy_range(n)
+  int32_t range;            // positions per wave: policy_range(n), or kPolRangeMax where the
+                            // workspace holds no more ranges than that needs
   const uint8_t* priority;  // [n]
   const int32_t* length;    // [n]
   int64_t n;
@@ -372,8 +374,12 @@ struct PolArgs {
                             // (the plan's flag; null when the sort has no plan)
 };
 
+// Ranges and workgroups that a workspace for n requests has room for: with the
+// ranges of policy_range (never fewer than for a smaller queue), and with
+// kPolRangeMax, the fewest.
 int64_t policy_ranges(int64_t n);
-int64_t policy_blocks(int64_t n);
+int64_t policy_ranges_least(int64_t n);
+int64_t policy_blocks(int64_t ranges);
 // `before` / `after` (may be null) are recorded around the pass that writes
 // the schedule (FCFS, HPJF) or sums the classes (SJF).
 hipError_t launch_fcfs(const PolArgs& a, hipStream_t st, hipEvent_t before, hipEvent_t after);

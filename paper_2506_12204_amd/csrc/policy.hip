@@ -851,8 +851,7 @@ __global__ __launch_bounds__(PT) void p_total(PolArgs a, int64_t blocks) {
   }
 }
 
-int64_t ranges_of(int64_t n) { return (n + policy_range(n) - 1) / policy_range(n); }
-int64_t blocks_of(int64_t n) { return (ranges_of(n) + kWaves - 1) / kWaves; }
+int64_t ranges_of(int64_t n, int range) { return (n + range - 1) / range; }
 
 hipError_t launch_p_range(const PolArgs& a, hipStream_t st) {
   const int64_t g = std::min<int64_t>((a.n + PT * 64 - 1) / (PT * 64), 1024);
@@ -866,18 +865,17 @@ void mark(hipEvent_t e, hipStream_t st) {
 
 }  // namespace
 
-// Ranges a workspace for n requests has room for: never fewer than a smaller
-// queue has, so that a workspace holds every queue up to the size it is for.
 int64_t policy_ranges(int64_t n) {
-  int64_t r = ranges_of(n);
+  int64_t r = ranges_of(n, policy_range(n));
   for (int64_t edge : kPolRangeEdges)
-    if (n >= edge) r = std::max(r, ranges_of(edge - 1));
+    if (n >= edge) r = std::max(r, ranges_of(edge - 1, policy_range(edge - 1)));
   return r;
 }
-int64_t policy_blocks(int64_t n) { return (policy_ranges(n) + kWaves - 1) / kWaves; }
+int64_t policy_ranges_least(int64_t n) { return ranges_of(n, kPolRangeMax); }
+int64_t policy_blocks(int64_t ranges) { return (ranges + kWaves - 1) / kWaves; }
 
 hipError_t launch_fcfs(const PolArgs& a, hipStream_t st, hipEvent_t before, hipEvent_t after) {
-  const int64_t ranges = ranges_of(a.n), blocks = blocks_of(a.n);
+  const int64_t ranges = ranges_of(a.n, a.range), blocks = policy_blocks(ranges);
   hipLaunchKernelGGL(f_sums, dim3((unsigned)blocks), dim3(PT), 0, st, a, ranges);
   hipLaunchKernelGGL(f_scan, dim3(1), dim3(ST), 0, st, a, ranges);
   mark(before, st);
@@ -889,7 +887,7 @@ hipError_t launch_fcfs(const PolArgs& a, hipStream_t st, hipEvent_t before, hipE
 }
 
 hipError_t launch_hpjf(const PolArgs& a, hipStream_t st, hipEvent_t before, hipEvent_t after) {
-  const int64_t ranges = ranges_of(a.n), blocks = blocks_of(a.n);
+  const int64_t ranges = ranges_of(a.n, a.range), blocks = policy_blocks(ranges);
   if (launch_p_range(a, st) != hipSuccess) return hipGetLastError();
   hipLaunchKernelGGL(h_count<true>, dim3((unsigned)blocks), dim3(PT), 0, st, a, ranges);
   hipLaunchKernelGGL(h_count<false>, dim3((unsigned)blocks), dim3(PT), 0, st, a, ranges);
@@ -906,7 +904,7 @@ hipError_t launch_policy_range(const PolArgs& a, hipStream_t st) { return launch
 
 hipError_t launch_class_totals(const PolArgs& a, hipStream_t st, hipEvent_t before,
                                hipEvent_t after) {
-  const int64_t ranges = ranges_of(a.n), blocks = blocks_of(a.n);
+  const int64_t ranges = ranges_of(a.n, a.range), blocks = policy_blocks(ranges);
   mark(before, st);
   hipLaunchKernelGGL(s_classes<true>, dim3((unsigned)blocks), dim3(PT), 0, st, a, ranges);
   hipLaunchKernelGGL(s_classes<false>, dim3((unsigned)blocks), dim3(PT), 0, st, a, ranges);
