@@ -305,7 +305,7 @@ __device__ __forceinline__ void select_place(const SelArgs& a, const uint64_t* c
 
 constexpr int kPickBits = 11;
 constexpr int kPickBins = 1 << kPickBits;
-constexpr uint32_t kKept = BT;         // most entries kept without another look at the lists
+constexpr uint32_t kKept = BT;         // most entries kept (one per thread)
 // Entries of the small sort (a wave per run of 64, every run searched by every
 // other): its LDS reads grow with the square; 1,000 entries in 16 runs took
 // 14 us, the radix sort of 1024 8 us. Narrowing goes on above this many.
@@ -441,11 +441,12 @@ struct SelectShared {
 // ongoing requests sorted, the stage filter and the merged places. What
 // bounds it is its chain of dependent steps: two gathers (ids, then their
 // ranks and lengths), about ten barriers per narrowing round and sort, one
-// gather of stages. Sorting all 4,352 candidates of the benchmark iteration
-// in six radix passes took 47 us; narrowing them to about 260 first, 17 us.
+// gather of stages. Sorting all 4,352 candidates of an iteration over 2^20
+// requests in six radix passes took 45 us; narrowing them to about 260 first,
+// 16 us (over 2^26, where the gathers miss the caches, 57 and 23).
 __global__ __launch_bounds__(BT) void b_select(SelArgs a) {
   __shared__ SelectShared sh;
-  constexpr int EC = kCandCap / BT, EO = kSelectCap / BT;
+  constexpr int EC = kCandCap / BT;
   const uint32_t t = threadIdx.x;
   const int w = __builtin_amdgcn_readfirstlane((int)(t / kWave));
   const uint32_t nh = (uint32_t)min(a.b, a.n_heap);
@@ -457,182 +458,183 @@ __global__ __launch_bounds__(BT) void b_select(SelArgs a) {
     a.flags[0] = 0;
     wait_stores();  // before any other thread's error bit
   }
-  // the ids of both lists, then their ranks and lengths, each in one go
-  int32_t ci[EC], oi[EO];
-#pragma unroll
-  for (int r = 0; r < EC; ++r) {
-    const uint32_t i = r * BT + t;
-    ci[r] = 0;
-    if (i < nc_in) ci[r] = i < nh ? a.heap_order[i] : a.buffer[i - nh];
-  }
-#pragma unroll
-  for (int r = 0; r < EO; ++r) {
-    const uint32_t i = r * BT + t;
-    oi[r] = i < no ? a.ongoing[i] : 0;
-  }
-  bool bad = false;
-  uint32_t cp[EC], cl[EC], op[EO], ol[EO];
-#pragma unroll
-  for (int r = 0; r < EC; ++r) {
-    const bool in = (uint32_t)(r * BT + t) < nc_in, ok = in && ci[r] >= 0 && ci[r] < a.n_ids;
-    bad |= in && !ok;
-    cp[r] = ok ? a.priority[ci[r]] : 0u;
-    cl[r] = ok ? (uint32_t)a.length[ci[r]] : 0u;
-  }
-#pragma unroll
-  for (int r = 0; r < EO; ++r) {
-    const bool in = (uint32_t)(r * BT + t) < no, ok = in && oi[r] >= 0 && oi[r] < a.n_ids;
-    bad |= in && !ok;
-    op[r] = ok ? a.priority[oi[r]] : 0u;
-    ol[r] = ok ? (uint32_t)a.length[oi[r]] : 0u;
-  }
-  uint32_t pmax = 0, lmax = 0;
-#pragma unroll
-  for (int r = 0; r < EC; ++r) {
-    pmax = max(pmax, cp[r]);
-    lmax = max(lmax, cl[r]);
-  }
-#pragma unroll
-  for (int r = 0; r < EO; ++r) {
-    pmax = max(pmax, op[r]);
-    lmax = max(lmax, ol[r]);
-  }
-  block_sync();
-  if (bad) sh.bad = 1u;
-  const Packer pk = make_packer(a.n_ids, pmax, lmax, sh.red);  // (holds barriers)
-  uint64_t cv[EC];  // the candidates, packed (meaningless beyond 63 bits, then not used)
-#pragma unroll
-  for (int r = 0; r < EC; ++r) cv[r] = pk.pack(cp[r], cl[r], (uint32_t)ci[r]);
-  const uint64_t mine_o = pk.pack(op[0], ol[0], (uint32_t)oi[0]);
-  if (sh.bad) {
-    if (t == 0) {
-      atomicOr(a.flags, kFlagInval);
-      a.counts[0] = a.counts[1] = 0;
-    }
-    return;
-  }
   const uint32_t need = min((uint32_t)min(a.b, (int64_t)kCandCap), nc_in);
-  uint32_t m = nc_in;  // candidates kept for the sort
-  uint32_t top_shift = pk.bits;  // kept: (v >> top_shift) <= bound
-  uint64_t bound = 0;
-  bool kept = pk.bits <= 63 && no <= kKept && need <= kKept;
-  if (need == 0) m = 0;
-  // (between 513 and 1024 of at most 2048, narrowing costs what it saves)
-  if (kept && need > 0 && nc_in > kSmall && (need <= kSmall || nc_in > 2 * kKept)) {
-    uint32_t below = 0;  // candidates below the bound's group
-    while (top_shift > 0) {
-      const uint32_t sh_ = top_shift > kPickBits ? top_shift - kPickBits : 0u;
-      const uint32_t mask = (1u << (top_shift - sh_)) - 1;
-      sh.hist[2 * t] = 0;
-      sh.hist[2 * t + 1] = 0;
-      block_sync();
-#pragma unroll
-      for (int r = 0; r < EC; ++r) {
-        if ((uint32_t)(r * BT + t) < nc_in && (cv[r] >> top_shift) == bound)
-          atomicAdd(&sh.hist[(uint32_t)(cv[r] >> sh_) & mask], 1u);
-      }
-      block_sync();
-      const uint32_t c0 = sh.hist[2 * t], c1 = sh.hist[2 * t + 1];
-      uint32_t all;
-      const uint32_t ex = below + block_excl_scan_u32<BT>(c0 + c1, sh.scan32, all);
-      if (ex < need && need <= ex + c0) sh.pick = {2 * t, ex, c0, 0, 1};
-      else if (ex + c0 < need && need <= ex + c0 + c1) sh.pick = {2 * t + 1, ex + c0, c1, 0, 1};
-      block_sync();
-      bound = (bound << (top_shift - sh_)) | sh.pick.bin;
-      below = sh.pick.before;
-      m = below + sh.pick.count;
-      top_shift = sh_;
-      if (m <= max(need, kSmall)) break;  // (uniform)
-      block_sync();  // the pick is read before the next round's
-    }
-  }
-  kept = kept && m <= kKept;
-  if (kept) {
-    // The kept candidates to the first runs of ckey, the ongoing ones to okey:
-    // lists of at most kSmall entries as packed values in runs of 64, waves
-    // 0 .. 7 the candidates and 8 .. 15 the ongoing ones, longer ones as the
-    // radix sort takes them.
-    const bool small_c = m <= kSmall, small_o = no <= kSmall;
-    sh.ckey[t] = ~0ull;
-    sh.okey[t] = t < no && small_o ? mine_o : ~0ull;
-    block_sync();
-    bool keep[EC];
-    uint32_t place[EC];
-#pragma unroll
-    for (int r = 0; r < EC; ++r)
-      keep[r] = m > 0 && (uint32_t)(r * BT + t) < nc_in && (cv[r] >> top_shift) <= bound;
-    append_places(keep, &sh.count, place);
+  // The lists are sorted whole where they are known to need it: more than kKept
+  // of either to order, or between 513 and 1024 of at most 2048 candidates,
+  // where narrowing costs what it saves.
+  const bool whole = need > kKept || no > kKept ||
+                     (need > kSmall && nc_in > kKept && nc_in <= 2 * kKept);
+  uint32_t m = nc_in;
+  bool kept = false;
+  if (!whole) {
+    // the ids of both lists, then their ranks and lengths, each in one go
+    int32_t ci[EC];
 #pragma unroll
     for (int r = 0; r < EC; ++r) {
-      if (keep[r] && place[r] < kKept) {
-        sh.ckey[place[r]] = small_c ? cv[r] : pk.key(cv[r]);
-        if (!small_c) sh.cid[place[r]] = pk.id(cv[r]);
+      const uint32_t i = r * BT + t;
+      ci[r] = 0;
+      if (i < nc_in) ci[r] = i < nh ? a.heap_order[i] : a.buffer[i - nh];
+    }
+    static_assert(kKept == BT, "an ongoing request per thread");
+    const int32_t oi = t < no ? a.ongoing[t] : 0;
+    const bool o_ok = t < no && oi >= 0 && oi < a.n_ids;
+    bool bad = t < no && !o_ok;
+    uint32_t cp[EC], cl[EC];
+#pragma unroll
+    for (int r = 0; r < EC; ++r) {
+      const bool in = (uint32_t)(r * BT + t) < nc_in, ok = in && ci[r] >= 0 && ci[r] < a.n_ids;
+      bad |= in && !ok;
+      cp[r] = ok ? a.priority[ci[r]] : 0u;
+      cl[r] = ok ? (uint32_t)a.length[ci[r]] : 0u;
+    }
+    const uint32_t op = o_ok ? a.priority[oi] : 0u;
+    const uint32_t ol = o_ok ? (uint32_t)a.length[oi] : 0u;
+    uint32_t pmax = op, lmax = ol;
+#pragma unroll
+    for (int r = 0; r < EC; ++r) {
+      pmax = max(pmax, cp[r]);
+      lmax = max(lmax, cl[r]);
+    }
+    block_sync();
+    if (bad) sh.bad = 1u;
+    const Packer pk = make_packer(a.n_ids, pmax, lmax, sh.red);  // (holds barriers)
+    uint64_t cv[EC];  // the candidates, packed (meaningless beyond 63 bits, then not used)
+#pragma unroll
+    for (int r = 0; r < EC; ++r) cv[r] = pk.pack(cp[r], cl[r], (uint32_t)ci[r]);
+    const uint64_t mine_o = pk.pack(op, ol, (uint32_t)oi);
+    if (sh.bad) {
+      if (t == 0) {
+        atomicOr(a.flags, kFlagInval);
+        a.counts[0] = a.counts[1] = 0;
+      }
+      return;
+    }
+    m = nc_in;  // candidates kept for the sort
+    uint32_t top_shift = pk.bits;  // kept: (v >> top_shift) <= bound
+    uint64_t bound = 0;
+    kept = pk.bits <= 63;
+    if (need == 0) m = 0;
+    if (kept && need > 0 && nc_in > (need <= kSmall ? kSmall : kKept)) {
+      uint32_t below = 0;  // candidates below the bound's group
+      while (top_shift > 0) {
+        const uint32_t sh_ = top_shift > kPickBits ? top_shift - kPickBits : 0u;
+        const uint32_t mask = (1u << (top_shift - sh_)) - 1;
+        sh.hist[2 * t] = 0;
+        sh.hist[2 * t + 1] = 0;
+        block_sync();
+#pragma unroll
+        for (int r = 0; r < EC; ++r) {
+          if ((uint32_t)(r * BT + t) < nc_in && (cv[r] >> top_shift) == bound)
+            atomicAdd(&sh.hist[(uint32_t)(cv[r] >> sh_) & mask], 1u);
+        }
+        block_sync();
+        const uint32_t c0 = sh.hist[2 * t], c1 = sh.hist[2 * t + 1];
+        uint32_t all;
+        const uint32_t ex = below + block_excl_scan_u32<BT>(c0 + c1, sh.scan32, all);
+        if (ex < need && need <= ex + c0) sh.pick = {2 * t, ex, c0, 0, 1};
+        else if (ex + c0 < need && need <= ex + c0 + c1) sh.pick = {2 * t + 1, ex + c0, c1, 0, 1};
+        block_sync();
+        bound = (bound << (top_shift - sh_)) | sh.pick.bin;
+        below = sh.pick.before;
+        m = below + sh.pick.count;
+        top_shift = sh_;
+        // (uniform) above kSmall the radix sort of one entry per thread takes any
+        // number up to kKept
+        if (m <= (need <= kSmall ? kSmall : kKept)) break;
+        block_sync();  // the pick is read before the next round's
       }
     }
-    if (!small_o && t < no) {
-      sh.okey[t] = pk.key(mine_o);
-      sh.oid[t] = pk.id(mine_o);
-    }
-    block_sync();
-    const bool of_c = w < kSortWaves / 2;
-    const int mine = of_c ? w : w - kSortWaves / 2;  // this wave's run
-    const uint32_t count = of_c ? m : no;
-    const int runs = (int)((count + kWave - 1) / kWave);
-    const bool used = (of_c ? small_c : small_o) && mine < runs;  // (uniform in the wave)
-    uint64_t* buf = of_c ? sh.ckey : sh.okey;
-    uint64_t v = 0;
-    if (used) {
-      v = buf[mine * kWave + lane_id()];
-      uint32_t none = 0;
-      wave_sort(v, none);
-      buf[mine * kWave + lane_id()] = v;
-    }
-    block_sync();
-    const uint32_t rank = used ? rank_in_runs(buf, 0, runs, mine, v) : ~0u;
-    block_sync();  // the runs are read before the sorted lists are written
-    if (rank < count) {
-      buf[rank] = pk.key(v);
-      (of_c ? sh.cid : sh.oid)[rank] = pk.id(v);
-    }
-    block_sync();
-    if (!small_c) {  // (the sort's padding: entries m .. 1023)
-      if (t >= m) sh.cid[t] = ~0u;
+    kept = kept && m <= kKept;
+    if (kept) {
+      // The kept candidates to the first runs of ckey, the ongoing ones to okey:
+      // lists of at most kSmall entries as packed values in runs of 64, waves
+      // 0 .. 7 the candidates and 8 .. 15 the ongoing ones, longer ones as the
+      // radix sort takes them.
+      const bool small_c = m <= kSmall, small_o = no <= kSmall;
+      sh.ckey[t] = ~0ull;
+      sh.okey[t] = t < no && small_o ? mine_o : ~0ull;
       block_sync();
-      block_sort<1, false>(sh.ckey, sh.cid, nullptr, m, sh.sort);
-    }
-    if (!small_o) {
-      if (t >= no) sh.oid[t] = ~0u;
-      block_sync();
-      block_sort<1, false>(sh.okey, sh.oid, nullptr, no, sh.sort);
-    }
-  } else {
-    // more than the kept lists take, or ids, lengths and ranks beyond 63
-    // bits: the lists are sorted whole
-    m = nc_in;
-    const uint32_t NC = sort_size<false>(nc_in), NO = sort_size<false>(no);
-    if (pk.bits <= 63) {
+      bool keep[EC];
+      uint32_t place[EC];
+#pragma unroll
+      for (int r = 0; r < EC; ++r)
+        keep[r] = m > 0 && (uint32_t)(r * BT + t) < nc_in && (cv[r] >> top_shift) <= bound;
+      append_places(keep, &sh.count, place);
 #pragma unroll
       for (int r = 0; r < EC; ++r) {
-        const uint32_t i = r * BT + t;
-        if (i < NC) {
-          sh.ckey[i] = i < nc_in ? pk.key(cv[r]) : ~0ull;
-          sh.cid[i] = i < nc_in ? pk.id(cv[r]) : ~0u;
+        if (keep[r] && place[r] < kKept) {
+          sh.ckey[place[r]] = small_c ? cv[r] : pk.key(cv[r]);
+          if (!small_c) sh.cid[place[r]] = pk.id(cv[r]);
         }
       }
-    } else {
-      for (uint32_t i = t; i < NC; i += BT) {
-        const uint32_t id =
-            i < nc_in ? (uint32_t)(i < nh ? a.heap_order[i] : a.buffer[i - nh]) : ~0u;
-        sh.ckey[i] = i < nc_in ? key_of(a, id) : ~0ull;
-        sh.cid[i] = id;
+      if (!small_o && t < no) {
+        sh.okey[t] = pk.key(mine_o);
+        sh.oid[t] = pk.id(mine_o);
+      }
+      block_sync();
+      const bool of_c = w < kSortWaves / 2;
+      const int mine = of_c ? w : w - kSortWaves / 2;  // this wave's run
+      const uint32_t count = of_c ? m : no;
+      const int runs = (int)((count + kWave - 1) / kWave);
+      const bool used = (of_c ? small_c : small_o) && mine < runs;  // (uniform in the wave)
+      uint64_t* buf = of_c ? sh.ckey : sh.okey;
+      uint64_t v = 0;
+      if (used) {
+        v = buf[mine * kWave + lane_id()];
+        uint32_t none = 0;
+        wave_sort(v, none);
+        buf[mine * kWave + lane_id()] = v;
+      }
+      block_sync();
+      const uint32_t rank = used ? rank_in_runs(buf, 0, runs, mine, v) : ~0u;
+      block_sync();  // the runs are read before the sorted lists are written
+      if (rank < count) {
+        buf[rank] = pk.key(v);
+        (of_c ? sh.cid : sh.oid)[rank] = pk.id(v);
+      }
+      block_sync();
+      if (!small_c) {  // (the sort's padding: entries m .. 1023)
+        if (t >= m) sh.cid[t] = ~0u;
+        block_sync();
+        block_sort<1, false>(sh.ckey, sh.cid, nullptr, m, sh.sort);
+      }
+      if (!small_o) {
+        if (t >= no) sh.oid[t] = ~0u;
+        block_sync();
+        block_sort<1, false>(sh.okey, sh.oid, nullptr, no, sh.sort);
       }
     }
-    for (uint32_t i = t; i < NO; i += BT) {
-      const uint32_t id = i < no ? (uint32_t)a.ongoing[i] : ~0u;
-      sh.okey[i] = i < no ? key_of(a, id) : ~0ull;
-      sh.oid[i] = id;
-    }
+  }
+  if (!kept) {
+    // (also when more candidates tie than the kept list takes, and ids, lengths
+    // and ranks beyond 63 bits)
+    m = nc_in;
+    const uint32_t NC = sort_size<false>(nc_in), NO = sort_size<false>(no);
     block_sync();
+    bool bad = false;
+    for (uint32_t i = t; i < NC; i += BT) {
+      const int32_t v = i >= nc_in ? 0 : i < nh ? a.heap_order[i] : a.buffer[i - nh];
+      const bool ok = i < nc_in && v >= 0 && v < a.n_ids;
+      bad |= i < nc_in && !ok;
+      sh.ckey[i] = ok ? key_of(a, (uint32_t)v) : ~0ull;
+      sh.cid[i] = ok ? (uint32_t)v : ~0u;
+    }
+    for (uint32_t i = t; i < NO; i += BT) {
+      const int32_t v = i < no ? a.ongoing[i] : 0;
+      const bool ok = i < no && v >= 0 && v < a.n_ids;
+      bad |= i < no && !ok;
+      sh.okey[i] = ok ? key_of(a, (uint32_t)v) : ~0ull;
+      sh.oid[i] = ok ? (uint32_t)v : ~0u;
+    }
+    if (bad) sh.bad = 1u;
+    block_sync();
+    if (sh.bad) {
+      if (t == 0) {
+        atomicOr(a.flags, kFlagInval);
+        a.counts[0] = a.counts[1] = 0;
+      }
+      return;
+    }
     sort_pairs<false>(sh.ckey, sh.cid, nullptr, nc_in, sh.sort);
     sort_pairs<false>(sh.okey, sh.oid, nullptr, no, sh.sort);
   }
@@ -729,8 +731,9 @@ struct EvictShared {
 // KV sizes cover the last demand's need: a radix select weighted by KV finds
 // a bound that keeps those and few others, and only they are sorted (all of
 // them, as before, when the need takes everything or more than fit the small
-// sort). Sorting the 8,192 cached requests of the benchmark iteration took
-// 55 us, this 21 us.
+// sort). Sorting the 8,192 cached requests of an iteration over 2^20 requests
+// took 53 us, this 21 us (over 2^26, where the gathers miss the caches, 71 and
+// 32).
 __global__ __launch_bounds__(BT) void b_evict(EvictArgs a) {
   __shared__ EvictShared sh;
   constexpr int E = kEvictCap / BT;
@@ -743,162 +746,183 @@ __global__ __launch_bounds__(BT) void b_evict(EvictArgs a) {
     a.flags[0] = 0;
     wait_stores();  // before any other thread's error bit
   }
-  // ids and KV sizes, the demands' sum, then ranks and lengths
-  int32_t ci[E];
-  int64_t kv[E];
+  // Up to kKept entries the radix sort takes 8 us; narrowing pays there only when
+  // few victims are likely, about one per demand.
+  const bool whole = nr > kSmall && nr <= kKept && 2 * a.n_demands > nr;
+  uint32_t m = nr;
+  bool packed = false;
+  if (!whole) {
+    // ids and KV sizes, the demands' sum, then ranks and lengths
+    int32_t ci[E];
+    int64_t kv[E];
 #pragma unroll
-  for (int r = 0; r < E; ++r) {
-    const uint32_t i = r * BT + t;
-    ci[r] = i < nr ? a.cached[i] : 0;
-    kv[r] = i < nr ? a.kv[i] : 0;
-  }
-  uint64_t want = 0;  // (negative demands end in an error, whatever they select)
-  for (int64_t j = t; j < a.n_demands; j += BT) want += (uint64_t)max(a.demands[j], (int64_t)0);
-  uint32_t bad = 0, cp[E], cl[E], pmax = 0, lmax = 0;
+    for (int r = 0; r < E; ++r) {
+      const uint32_t i = r * BT + t;
+      ci[r] = i < nr ? a.cached[i] : 0;
+      kv[r] = i < nr ? a.kv[i] : 0;
+    }
+    uint64_t want = 0;  // (negative demands end in an error, whatever they select)
+    for (int64_t j = t; j < a.n_demands; j += BT) want += (uint64_t)max(a.demands[j], (int64_t)0);
+    uint32_t bad = 0, cp[E], cl[E], pmax = 0, lmax = 0;
 #pragma unroll
-  for (int r = 0; r < E; ++r) {
-    const bool in = (uint32_t)(r * BT + t) < nr, ok = in && ci[r] >= 0 && ci[r] < a.n_ids;
-    if (in && !ok) bad |= 1u;
-    else if (kv[r] < 0) bad |= 2u;  // 2: negative KV size
-    cp[r] = ok ? a.priority[ci[r]] : 0u;
-    cl[r] = ok ? (uint32_t)a.length[ci[r]] : 0u;
-  }
+    for (int r = 0; r < E; ++r) {
+      const bool in = (uint32_t)(r * BT + t) < nr, ok = in && ci[r] >= 0 && ci[r] < a.n_ids;
+      if (in && !ok) bad |= 1u;
+      else if (kv[r] < 0) bad |= 2u;  // 2: negative KV size
+      cp[r] = ok ? a.priority[ci[r]] : 0u;
+      cl[r] = ok ? (uint32_t)a.length[ci[r]] : 0u;
+    }
 #pragma unroll
-  for (int r = 0; r < E; ++r) {
-    pmax = max(pmax, cp[r]);
-    lmax = max(lmax, cl[r]);
-  }
-  block_sync();
-  if (bad) atomicOr(&sh.bad, bad);
-  uint64_t total;
-  (void)block_excl_scan_u64<BT>(want, sh.scan64, total);
-  const Packer pk = make_packer(a.n_ids, pmax, lmax, sh.red);  // (holds barriers)
-  uint64_t cv[E];  // packed (meaningless beyond 63 bits, then not used)
+    for (int r = 0; r < E; ++r) {
+      pmax = max(pmax, cp[r]);
+      lmax = max(lmax, cl[r]);
+    }
+    block_sync();
+    if (bad) atomicOr(&sh.bad, bad);
+    uint64_t total;
+    (void)block_excl_scan_u64<BT>(want, sh.scan64, total);
+    const Packer pk = make_packer(a.n_ids, pmax, lmax, sh.red);  // (holds barriers)
+    uint64_t cv[E];  // packed (meaningless beyond 63 bits, then not used)
 #pragma unroll
-  for (int r = 0; r < E; ++r) cv[r] = pk.pack(cp[r], cl[r], (uint32_t)ci[r]);
-  if (sh.bad) {
-    if (t == 0) atomicOr(a.flags, (sh.bad & 1u) ? kFlagInval : kFlagRange);
-    return;
-  }
-  const int64_t need = a.usage + (int64_t)total - a.capacity;
-  // kept: (v >> low_shift) >= bound, the entries that leave first
-  uint32_t m = nr, low_shift = min(pk.bits, 63u);
-  uint64_t bound = 0;
-  if (need <= 0) {
-    m = 0;
-    bound = ~0ull;  // (none)
-  } else if (pk.bits <= 63 && (nr > kKept || (nr > kSmall && 2 * a.n_demands <= nr))) {
-    // (up to kKept the radix sort takes 8 us: there only when few victims are
-    // likely, about one per demand)
-    uint64_t freed = 0;  // KV of the entries above the bound's group
-    uint32_t above = 0;  // their number
-    while (low_shift > 0) {
-      const uint32_t sh_ = low_shift > kPickBits ? low_shift - kPickBits : 0u;
-      const uint32_t mask = (1u << (low_shift - sh_)) - 1;
+    for (int r = 0; r < E; ++r) cv[r] = pk.pack(cp[r], cl[r], (uint32_t)ci[r]);
+    if (sh.bad) {
+      if (t == 0) atomicOr(a.flags, (sh.bad & 1u) ? kFlagInval : kFlagRange);
+      return;
+    }
+    const int64_t need = a.usage + (int64_t)total - a.capacity;
+    // kept: (v >> low_shift) >= bound, the entries that leave first
+    m = nr;
+    uint32_t low_shift = min(pk.bits, 63u);
+    uint64_t bound = 0;
+    if (need <= 0) {
+      m = 0;
+      bound = ~0ull;  // (none)
+    } else if (pk.bits <= 63 && nr > kSmall) {
+      uint64_t freed = 0;  // KV of the entries above the bound's group
+      uint32_t above = 0;  // their number
+      while (low_shift > 0) {
+        const uint32_t sh_ = low_shift > kPickBits ? low_shift - kPickBits : 0u;
+        const uint32_t mask = (1u << (low_shift - sh_)) - 1;
 #pragma unroll
-      for (int k = 0; k < 2; ++k) {
-        sh.hist.kv[2 * t + k] = 0;
-        sh.hist.n[2 * t + k] = 0;
+        for (int k = 0; k < 2; ++k) {
+          sh.hist.kv[2 * t + k] = 0;
+          sh.hist.n[2 * t + k] = 0;
+        }
+        if (t == 0) sh.pick.found = 0;
+        block_sync();
+#pragma unroll
+        for (int r = 0; r < E; ++r) {
+          if ((uint32_t)(r * BT + t) < nr && (cv[r] >> low_shift) == bound) {
+            const uint32_t d = (uint32_t)(cv[r] >> sh_) & mask;
+            atomicAdd(reinterpret_cast<unsigned long long*>(&sh.hist.kv[d]),
+                      (unsigned long long)kv[r]);
+            atomicAdd(&sh.hist.n[d], 1u);
+          }
+        }
+        block_sync();
+        // bins from the top: thread t takes bins 2047 - 2t and 2046 - 2t
+        const uint32_t b0 = kPickBins - 1 - 2 * t, b1 = b0 - 1;
+        const uint64_t k0 = sh.hist.kv[b0], k1 = sh.hist.kv[b1];
+        const uint32_t n0 = sh.hist.n[b0], n1 = sh.hist.n[b1];
+        uint64_t all;
+        uint32_t alln;
+        const uint64_t ex = freed + block_excl_scan_u64<BT>(k0 + k1, sh.scan64, all);
+        const uint32_t en = above + block_excl_scan_u32<BT>(n0 + n1, sh.scan32, alln);
+        const uint64_t nd = (uint64_t)need;
+        if (ex < nd && nd <= ex + k0) sh.pick = {b0, en, n0, ex, 1};
+        else if (ex + k0 < nd && nd <= ex + k0 + k1) sh.pick = {b1, en + n0, n1, ex + k0, 1};
+        block_sync();
+        if (!sh.pick.found) break;  // (uniform; first round only) everything leaves
+        bound = (bound << (low_shift - sh_)) | sh.pick.bin;
+        freed = sh.pick.weight_before;
+        above = sh.pick.before;
+        m = above + sh.pick.count;
+        low_shift = sh_;
+        // (uniform) done, or more leave for certain than the small sort takes and
+        // the radix sort of those would be as wide as of all kept
+        if (m <= kSmall || (above >= kSmall && sort_size<true>(above + 1) == sort_size<true>(m)))
+          break;
+        block_sync();  // the pick is read before the next round's
       }
-      if (t == 0) sh.pick.found = 0;
+    }
+    bool keep[E];
+    uint32_t place[E];
+#pragma unroll
+    for (int r = 0; r < E; ++r)
+      keep[r] = (uint32_t)(r * BT + t) < nr && (cv[r] >> low_shift) >= bound;
+    const bool small = pk.bits <= 63 && m <= kSmall;
+    if (small) {
+      // runs of 64 at the start of key, the kept entries' KV sizes after them,
+      // then the sizes in eviction order
+      uint64_t* kept_kv = sh.key + BT;
+      uint64_t* order_kv = sh.key + 2 * BT;
+      sh.key[t] = ~0ull;
       block_sync();
+      append_places(keep, &sh.count, place);
 #pragma unroll
       for (int r = 0; r < E; ++r) {
-        if ((uint32_t)(r * BT + t) < nr && (cv[r] >> low_shift) == bound) {
-          const uint32_t d = (uint32_t)(cv[r] >> sh_) & mask;
-          atomicAdd(reinterpret_cast<unsigned long long*>(&sh.hist.kv[d]),
-                    (unsigned long long)kv[r]);
-          atomicAdd(&sh.hist.n[d], 1u);
+        if (keep[r] && place[r] < kSmall) {
+          sh.key[place[r]] = cv[r];
+          kept_kv[place[r]] = (uint64_t)kv[r];
         }
       }
       block_sync();
-      // bins from the top: thread t takes bins 2047 - 2t and 2046 - 2t
-      const uint32_t b0 = kPickBins - 1 - 2 * t, b1 = b0 - 1;
-      const uint64_t k0 = sh.hist.kv[b0], k1 = sh.hist.kv[b1];
-      const uint32_t n0 = sh.hist.n[b0], n1 = sh.hist.n[b1];
-      uint64_t all;
-      uint32_t alln;
-      const uint64_t ex = freed + block_excl_scan_u64<BT>(k0 + k1, sh.scan64, all);
-      const uint32_t en = above + block_excl_scan_u32<BT>(n0 + n1, sh.scan32, alln);
-      const uint64_t nd = (uint64_t)need;
-      if (ex < nd && nd <= ex + k0) sh.pick = {b0, en, n0, ex, 1};
-      else if (ex + k0 < nd && nd <= ex + k0 + k1) sh.pick = {b1, en + n0, n1, ex + k0, 1};
+      const int runs = (int)((m + kWave - 1) / kWave);
+      uint64_t v = sh.key[t];
+      uint32_t from = t;
+      if (w < runs) {
+        wave_sort(v, from);
+        sh.key[t] = v;
+      }
       block_sync();
-      if (!sh.pick.found) break;  // (uniform; first round only) everything leaves
-      bound = (bound << (low_shift - sh_)) | sh.pick.bin;
-      freed = sh.pick.weight_before;
-      above = sh.pick.before;
-      m = above + sh.pick.count;
-      low_shift = sh_;
-      if (m <= kSmall) break;  // (uniform)
-      block_sync();  // the pick is read before the next round's
+      if (w < runs) {
+        const uint32_t rank = rank_in_runs(sh.key, 0, runs, w, v);
+        if (rank < m) {
+          order_kv[m - 1 - rank] = kept_kv[from];
+          sh.id[m - 1 - rank] = pk.id(v);
+        }
+      }
+      block_sync();
+      const uint64_t x = t < m ? order_kv[t] : 0;
+      uint64_t all;
+      const uint64_t ex = block_excl_scan_u64<BT>(x, sh.scan64, all);
+      sh.key[t] = ex + x;  // KV evicted by the first t + 1 victims
+      block_sync();
+      evict_demands(a, sh.key, sh.id, m, sh.scan64, &sh.bad);
+      return;
+    }
+    // more victims than the small sort holds
+    packed = pk.bits <= 63;
+    if (packed) {
+      append_places(keep, &sh.count, place);
+#pragma unroll
+      for (int r = 0; r < E; ++r) {
+        if (keep[r]) {
+          sh.key[place[r]] = pk.key(cv[r]);
+          sh.id[place[r]] = pk.id(cv[r]);
+          sh.src[place[r]] = (uint32_t)(r * BT + t);
+        }
+      }
     }
   }
-  bool keep[E];
-  uint32_t place[E];
-#pragma unroll
-  for (int r = 0; r < E; ++r)
-    keep[r] = (uint32_t)(r * BT + t) < nr && (cv[r] >> low_shift) >= bound;
-  const bool small = pk.bits <= 63 && m <= kSmall;
-  if (small) {
-    // runs of 64 at the start of key, the kept entries' KV sizes after them,
-    // then the sizes in eviction order
-    uint64_t* kept_kv = sh.key + BT;
-    uint64_t* order_kv = sh.key + 2 * BT;
-    sh.key[t] = ~0ull;
-    block_sync();
-    append_places(keep, &sh.count, place);
-#pragma unroll
-    for (int r = 0; r < E; ++r) {
-      if (keep[r] && place[r] < kSmall) {
-        sh.key[place[r]] = cv[r];
-        kept_kv[place[r]] = (uint64_t)kv[r];
-      }
-    }
-    block_sync();
-    const int runs = (int)((m + kWave - 1) / kWave);
-    uint64_t v = sh.key[t];
-    uint32_t from = t;
-    if (w < runs) {
-      wave_sort(v, from);
-      sh.key[t] = v;
-    }
-    block_sync();
-    if (w < runs) {
-      const uint32_t rank = rank_in_runs(sh.key, 0, runs, w, v);
-      if (rank < m) {
-        order_kv[m - 1 - rank] = kept_kv[from];
-        sh.id[m - 1 - rank] = pk.id(v);
-      }
-    }
-    block_sync();
-    const uint64_t x = t < m ? order_kv[t] : 0;
-    uint64_t all;
-    const uint64_t ex = block_excl_scan_u64<BT>(x, sh.scan64, all);
-    sh.key[t] = ex + x;  // KV evicted by the first t + 1 victims
-    block_sync();
-    evict_demands(a, sh.key, sh.id, m, sh.scan64, &sh.bad);
-    return;
-  }
-  // more victims than the small sort holds: the kept entries, or all of them
-  // when they do not pack
-  if (pk.bits <= 63) {
-    append_places(keep, &sh.count, place);
-#pragma unroll
-    for (int r = 0; r < E; ++r) {
-      if (keep[r]) {
-        sh.key[place[r]] = pk.key(cv[r]);
-        sh.id[place[r]] = pk.id(cv[r]);
-        sh.src[place[r]] = (uint32_t)(r * BT + t);
-      }
-    }
-  } else {
+  if (!packed) {  // all of them (also when they do not pack)
     m = nr;
+    block_sync();
+    uint32_t bad = 0;
     for (uint32_t i = t; i < nr; i += BT) {
-      const uint32_t id = (uint32_t)a.cached[i];
-      sh.key[i] = (uint64_t)a.priority[id] << 32 | (uint32_t)a.length[id];
-      sh.id[i] = id;
+      const int32_t v = a.cached[i];
+      const bool ok = v >= 0 && v < a.n_ids;
+      if (!ok) bad |= 1u;
+      else if (a.kv[i] < 0) bad |= 2u;  // 2: negative KV size
+      sh.key[i] = ok ? (uint64_t)a.priority[v] << 32 | (uint32_t)a.length[v] : 0ull;
+      sh.id[i] = (uint32_t)v;
       sh.src[i] = i;
+    }
+    if (bad) atomicOr(&sh.bad, bad);
+    block_sync();
+    if (sh.bad) {
+      if (t == 0) atomicOr(a.flags, (sh.bad & 1u) ? kFlagInval : kFlagRange);
+      return;
     }
   }
   for (uint32_t i = m + t; i < sort_size<true>(m); i += BT) {

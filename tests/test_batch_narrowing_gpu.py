@@ -92,3 +92,49 @@ def test_keys_beyond_63_bits():
     want = evict(ps, ls, [small[i] for i in cached.tolist()], kv.tolist(), usage, usage, demands)
     got = run_evict(p, l, cached, kv, usage, usage, demands)
     assert got == ([back[k] for k in want[0]], want[1])
+
+
+# Sizes that are narrowed, and sizes whose lists are known to be sorted whole: a
+# bad id (and a negative KV size) is found in either form, and a good call after
+# it is right
+@pytest.mark.parametrize("b,buffer,ongoing", [(64, 600, 64), (800, 3000, 300), (800, 700, 300),
+                                              (1500, 700, 300), (64, 600, 1500)])
+@pytest.mark.parametrize("where", ["buffer", "ongoing"])
+def test_select_bad_id(b, buffer, ongoing, where):
+    import paper_2506_12204_amd as ss
+    n = 30000
+    p, l, stage, heap, buf, ong = instance(b, n, 3000, buffer, ongoing, 5, 4000)
+    bad = {"buffer": buf, "ongoing": ong}[where].copy()
+    for value in (n, -1):
+        bad[-1] = value
+        print(f"[gpu] select b={b} buffer={buffer} ongoing={ongoing}: {where} {value}", flush=True)
+        with pytest.raises(ss.SemschedError):
+            run_select(p, l, stage, heap, bad if where == "buffer" else buf,
+                       bad if where == "ongoing" else ong, b)
+    want = select_batch(p.tolist(), l.tolist(), stage.tolist(), heap.tolist(), buf.tolist(),
+                        ong.tolist(), b)
+    assert run_select(p, l, stage, heap, buf, ong, b) == want
+
+
+@pytest.mark.parametrize("cached,nd", [(300, 5), (700, 5), (700, 600), (1024, 1024), (3000, 5)])
+@pytest.mark.parametrize("share", [0.0, 0.3, 0.95])
+def test_evict_forms(cached, nd, share):
+    import paper_2506_12204_amd as ss
+    rng = np.random.default_rng(cached + nd)
+    n = 30000
+    p = rng.integers(0, 5, n).astype(np.uint8)
+    l = rng.integers(0, 4000, n).astype(np.int32)
+    ids = rng.permutation(n)[:cached]
+    kv = rng.integers(1, 5000, cached)
+    demands = rng.multinomial(int(share * kv.sum()), np.full(nd, 1 / nd))
+    usage = int(kv.sum())
+    print(f"[gpu] evict cached={cached} demands={nd} share={share}", flush=True)
+    for change, error in ((lambda i, k: i.__setitem__(-1, n), ss.SemschedError),
+                          (lambda i, k: k.__setitem__(-1, -1), ss.SemschedRangeError)):
+        bad_ids, bad_kv = ids.copy(), kv.copy()
+        change(bad_ids, bad_kv)
+        with pytest.raises(error):
+            run_evict(p, l, bad_ids, bad_kv, usage, usage, demands)
+    want = evict(p.tolist(), l.tolist(), ids.tolist(), kv.tolist(), usage, usage,
+                 demands.tolist())
+    assert run_evict(p, l, ids, kv, usage, usage, demands) == (want[0], want[1])
