@@ -167,11 +167,14 @@ def test_one_class_and_zero_lengths(n):
     (2, 1 << 26, (1 << 26) + (1 << 19), "two passes, lengths past 2^26"),
     (5, 0, 1 << 31, "34-bit keys: generic final pass"),
 ])
-def test_wide_keys_with_few_final_digits(classes, lo, hi, label):
+@pytest.mark.parametrize("no_tiles", ["0", "1"])
+def test_wide_keys_with_few_final_digits(classes, lo, hi, label, no_tiles, monkeypatch):
+    monkeypatch.setenv("SEMSCHED_NO_TILES", no_tiles)
     # Keys of at most 32 bits (in the high word) with at most 256 final
     # digits but more than two passes or lengths of 2^26 and more: the wide
     # form of the big-tile final pass, reading the buffer of the pass before
-    # it (either of the two)
+    # it (either of the two). Queues of this size take one tile per workgroup
+    # unless the knob says otherwise.
     rng = np.random.default_rng(len(label))
     n = 300_000
     p = rng.integers(0, classes, n).astype(np.uint8)

@@ -105,14 +105,18 @@ def test_semantic_policy_is_sem_schedule():
 
 @pytest.mark.parametrize("classes,max_len", [(4, 2**18 - 1), (5, 2**18 - 1), (8, 2**17 - 1),
                                              (9, 2**17 - 1), (256, 4095), (256, 4096)])
-def test_sjf_carried_ranks_either_side_of_the_fit(classes, max_len):
-    # A long SJF queue in the compact layout carries the ranks through the
+@pytest.mark.parametrize("no_tiles", ["0", "1"])
+def test_sjf_carried_ranks_either_side_of_the_fit(classes, max_len, no_tiles, monkeypatch):
+    # Up to 2^21 requests the one-tile-per-workgroup path always carries the
+    # ranks; the knob sends the queue to the big-tile path.
+    # There a long SJF queue in the compact layout carries the ranks through the
     # sort when final-digit bits + rank bits fit above the 22 id bits
     # (4 ranks with 256 final digits fit, 5 do not; 8 ranks with 128 digits
     # fit, 9 do not; 256 ranks fit with 4 digits, lengths below 4096, not
     # with 5); otherwise
     # the class sums gather every position's rank. Both sides must agree
     # with the oracle.
+    monkeypatch.setenv("SEMSCHED_NO_TILES", no_tiles)
     rng = np.random.default_rng(classes * 7 + max_len % 97)
     n = 70000
     p = rng.integers(0, classes, n).astype(np.uint8)
@@ -120,6 +124,34 @@ def test_sjf_carried_ranks_either_side_of_the_fit(classes, max_len):
     l = rng.integers(0, max_len + 1, n).astype(np.int32)
     l[1], l[2] = 0, max_len  # the full length range is present
     check(p, l, POLICY_SJF, f"classes={classes} max_len={max_len}")
+
+
+# The big-tile path where the ranks are not carried: wide keys (one and two middle
+# passes, lengths past 2^26), and forced layouts; the ordering ranks are 0 there
+# though the caller's are not
+@pytest.mark.parametrize("classes,max_len", [(7, 2**21), (200, 2**27), (5, 2**31 - 1),
+                                             (256, 2**31 - 1)])
+@pytest.mark.parametrize("knob", [None, "SEMSCHED_FORCE_WIDE", "SEMSCHED_NO_COMPACT",
+                                  "SEMSCHED_SPLIT_MID"])
+def test_sjf_big_tiles_without_carried_ranks(classes, max_len, knob, monkeypatch):
+    monkeypatch.setenv("SEMSCHED_NO_TILES", "1")
+    if knob:
+        monkeypatch.setenv(knob, "1")
+    rng = np.random.default_rng(classes)
+    n = 200_003
+    p = rng.integers(0, classes, n).astype(np.uint8)
+    l = rng.integers(0, max_len, n, endpoint=True).astype(np.int32)
+    l[:1000] = l[1000:2000]  # ties on the length
+    l[-2:] = [0, max_len]
+    check(p, l, POLICY_SJF, f"classes={classes} max_len={max_len} {knob}")
+
+
+def test_sjf_above_the_tile_path_ranks_do_not_fit():
+    rng = np.random.default_rng(77)
+    n = (1 << 21) + 4097
+    p = rng.integers(0, 200, n).astype(np.uint8)
+    l = rng.integers(0, 32768, n).astype(np.int32)
+    check(p, l, POLICY_SJF, "above 2^21, 200 ranks")
 
 
 def test_sjf_carried_ranks_window_in_global_memory():
