@@ -74,7 +74,9 @@ int d0_bits() {
 
 // SEMSCHED_FORCE_WIDE=1 makes the global path keep ids in their own array
 // even when key and id would share one u64 (the layout very wide key ranges
-// need); it lets that layout be exercised on small queues.
+// need), and the batched call's long queues leave the first digit out of their
+// elements (what they do then); it lets those layouts be exercised on small
+// queues.
 int force_wide() {
   const char* e = std::getenv("SEMSCHED_FORCE_WIDE");
   return (e && e[0] == '1') ? 1 : 0;
@@ -734,6 +736,7 @@ int enqueue_batched(const uint8_t* p, const int32_t* l, const int64_t* offsets,
     a.lfinal = reinterpret_cast<uint64_t*>(base + L.lfinal);
     a.lwait = reinterpret_cast<uint64_t*>(base + L.lwait);
     a.claim_polls = claim_polls();
+    a.force_wide = force_wide();
   }
   return launch_batched(a, st) == hipSuccess ? SEM_OK : SEM_EDEVICE;
 }

@@ -114,6 +114,7 @@ struct BArgs {
   uint32_t* hist;           // [max_tiles][1024] their prefixes over the queue's tiles
   uint64_t* lfinal;         // [max_tiles][1024] final-digit counts and length sums
   uint64_t* lwait;          // [max_tiles][1024] prefixes of the length sums
+  int32_t force_wide;       // elements as for keys and ids beyond 64 bits together
   uint32_t claim_polls;     // next_work: polls before a further share is taken (> 0)
 };
 

@@ -49,18 +49,20 @@ constexpr int kFirstBits = 10;
 // one queue of 2^20 90, 87, with wide keys 102, 106.
 constexpr uint32_t kFoldTiles = 256, kFoldRows = 96;
 
-// Runs f with the element form of the plan's keys.
-template <typename F>
+// Runs f with the element form of the plan's keys. SMALL: the batch's queues have
+// at most kFoldTiles tiles, so that their ids (21 bits) always fit above a key.
+template <bool SMALL = false, typename F>
 __device__ __forceinline__ void with_codec(const Plan* pl, F&& f) {
+  static_assert((uint64_t)kFoldTiles * kLongTile <= 1ull << (64 - 39), "39 bits of key at most");
   if (pl->W == 32) {
     KeyCodec32 kc;
     kc.init(kFirstBits, pl);
     f(kc);
-  } else if (pl->packed) {
+  } else if (SMALL || pl->packed) {
     KeyCodec64 kc;
     kc.init(kFirstBits, pl);
     f(kc);
-  } else {
+  } else if constexpr (!SMALL) {
     KeyCodecGather kc;
     kc.init(kFirstBits, pl);
     f(kc);
@@ -252,7 +254,7 @@ __device__ void long_plan(const BArgs& a, uint32_t tiles, uint32_t (*red)[TWV]) 
   if (all.y >> 31) {
     atomicOr(a.flags, kFlagRange);
   } else {
-    make_plan(kFirstBits, longest - 1, false, false, all.x, all.y, all.z, all.w, &p);
+    make_plan(kFirstBits, longest - 1, a.force_wide != 0, false, all.x, all.y, all.z, all.w, &p);
     p.ok = 1;
     // a wave's 512 waits, each below longest * 2^bits, in 64 bits
     p.sum64 = bit_width32(longest) + bit_width32(all.w) + 9 <= 64 ? 1u : 0u;
@@ -545,7 +547,7 @@ __device__ void mid_count(const BArgs& a, int s, uint32_t lo, uint32_t hi, uint3
   const int t = threadIdx.x;
   const uint32_t copy = (uint32_t)lane_id() & (kCountCopies - 1);
   const uint32_t dshift = a.plan->shift[s];
-  with_codec(a.plan, [&](auto kc) {
+  with_codec<FOLD>(a.plan, [&](auto kc) {
     for (uint32_t tt = lo; tt < hi; ++tt) {
       const LongTileDesc x = a.tdesc[tt];
       uint64_t e[LR];
@@ -619,7 +621,7 @@ __global__ __launch_bounds__(TT) void l_mid(BArgs a) {
     if ((phase & 1) == 0)
       mid_count<true>(a, s, lo, hi, sh.cnt);
     else
-      with_codec(a.plan, [&](auto kc) { long_scatter<false, true>(a, kc, s, lo, hi, sh.scatter); });
+      with_codec<true>(a.plan, [&](auto kc) { long_scatter<false, true>(a, kc, s, lo, hi, sh.scatter); });
   }
 }
 
@@ -774,7 +776,7 @@ __global__ __launch_bounds__(TT) void l_final(BArgs a) {
     kc.init(kFirstBits, a.plan);
     long_final<false, FOLD>(a, kc, lo, hi, sh);
   } else {
-    with_codec(a.plan, [&](auto kc) { long_final<true, FOLD>(a, kc, lo, hi, sh); });
+    with_codec<FOLD>(a.plan, [&](auto kc) { long_final<true, FOLD>(a, kc, lo, hi, sh); });
   }
 }
 
@@ -792,7 +794,8 @@ hipError_t launch_long_queues(const BArgs& a, hipStream_t st) {
   const int most = (int)kMaxShares;
   launch(l_count, std::min(r_count, most));
   launch(l_first, r_first);
-  if (a.max_tiles <= kFoldTiles && a.max_tiles <= kFoldRows * (uint64_t)a.num_segments) {
+  if (!a.force_wide && a.max_tiles <= kFoldTiles &&
+      a.max_tiles <= kFoldRows * (uint64_t)a.num_segments) {
     static const int r_mid = resident_groups(l_mid), r_final = resident_groups(l_final<true>);
     launch(l_mid, std::min(r_mid, most));
     launch(l_histF, r_histF);

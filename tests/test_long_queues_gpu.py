@@ -50,6 +50,18 @@ def test_key_widths(classes, max_len):
     check([50001, 17000, 35 * TILE], f"widths {classes}x{max_len}", classes, max_len)
 
 
+# Elements without the first digit, whose lengths are read through the id (keys and
+# ids beyond 64 bits together, here forced): several queues, tiles of two queues
+# in one workgroup's run, tile edges
+@pytest.mark.parametrize("sizes", [[16385], [50001, 17000, 35 * TILE], [3 * TILE + 1, 40 * TILE - 1],
+                                   [16385 + 13 * i for i in range(300)]])
+@pytest.mark.parametrize("classes,max_len", [(1, 1000), (5, 32768), (9, 2_000_000),
+                                             (256, 2**31 - 1)])
+def test_lengths_read_through_the_id(sizes, classes, max_len, monkeypatch):
+    monkeypatch.setenv("SEMSCHED_FORCE_WIDE", "1")
+    check(sizes, f"gather {classes}x{max_len}", classes, max_len)
+
+
 def test_workgroups_that_span_queues():
     # more tiles than workgroups, so that one takes tiles of several queues
     check([16385 + 13 * i for i in range(400)], "span")
@@ -65,11 +77,25 @@ def test_largest_sums():
     assert_same(got, c_oracle_batched(p, l, off, 4), "largest sums")
 
 
+def folds(room, queues):
+    """Whether the passes sum the count rows themselves: the library's tiles for
+    that room (a partial one per queue, and one) against its limits."""
+    tiles = -(-room // TILE) + min(queues, room // 16385) + 1
+    return tiles <= min(256, 96 * queues)
+
+
 # The same queues with their exact room (the passes sum the count rows
-# themselves) and with room for 300 tiles more (the rows' prefixes are launched)
-@pytest.mark.parametrize("sizes", [[16385], [96 * TILE - 1], [30 * TILE, 17000, 65 * TILE + 1]])
+# themselves, up to the last size that does) and with room for 300 tiles more
+# (the rows' prefixes are launched)
+@pytest.mark.parametrize("sizes,exact_folds", [
+    ([16385], True), ([94 * TILE - 1], True), ([94 * TILE], True), ([94 * TILE + 1], False),
+    ([96 * TILE - 1], False), ([30 * TILE, 17000, 65 * TILE + 1], True),
+    ([84 * TILE] * 2 + [84 * TILE], True), ([84 * TILE] * 2 + [84 * TILE + 1], False),
+    ([3 * TILE] * 60 + [4 * TILE] * 3, True), ([3 * TILE] * 60 + [4 * TILE] * 2 + [4 * TILE + 1], False)])
 @pytest.mark.parametrize("classes,max_len", [(5, 32768), (9, 2_000_000), (256, 2**31 - 1)])
-def test_both_sides_of_the_fold_rule(sizes, classes, max_len):
+def test_both_sides_of_the_fold_rule(sizes, exact_folds, classes, max_len):
+    assert folds(sum(sizes), len(sizes)) == exact_folds
+    assert not folds(sum(sizes) + 300 * TILE, len(sizes))
     p, l, off = fuzz_segments(sizes, seed=len(sizes), classes=classes, max_len=max_len)
     want = c_oracle_batched(p, l, off, classes)
     for more in (0, 300 * TILE):
