@@ -40,12 +40,6 @@ constexpr int MR = kInsUnit / kWave;  // rounds of 64 entries in a unit
 constexpr int kClassSlots = 257;  // class starts (classes 0..255 and the end)
 constexpr int kTotalWords = 2 * (1 + 256);  // u64 words of the totals
 constexpr int kMaxMergeBlocks = 4096;
-// Classes of a wave's 64 arrivals up to which class_starts pays, which takes them
-// one after another (2 us each in 2^20 earlier entries, 4 in 2^26); with more
-// every lane searches by keys. 64 arrivals of 10 classes into 100,000: 47 us by
-// class starts, 28 by keys; of one class 25 and 29; of 64 classes into 2^20:
-// 186 and 38.
-constexpr int kSearchClasses = 2;
 static_assert(MT == 256, "the merge kernel's final reduction keeps one class per thread");
 
 // Global memory that no kernel writes while the merge kernel runs, read
@@ -140,11 +134,15 @@ __device__ __forceinline__ void class_starts(const InsArgs& a, uint32_t c0, uint
 //
 // What bounds it is the chain of dependent cache misses of a search. An
 // earlier entry's key is two loads away (its id, then its rank and length) on
-// three lines. An arrival of a wave of at most kSearchClasses classes (nearly
-// every wave of a large insertion: the arrivals are sorted) is therefore
-// searched among its class's entries only, whose lengths are the differences
-// of neighbouring waits: one load on one line, three probes side by side; the
-// class's first and last entry come from class_starts. 2^16 arrivals in 2^26 entries: 58 us by keys, one probe
+// three lines. An arrival is therefore searched among its class's entries only,
+// whose lengths are the differences of neighbouring waits: one load on one
+// line, three probes side by side; the class's first and last entry come from
+// class_starts. That takes the wave's classes one after another (2 us each in
+// 2^20 earlier entries, 4 in 2^26), so it pays for one or two, which nearly
+// every wave of a large insertion has (the arrivals are sorted); with more
+// every lane searches by keys. 64 arrivals of 10 classes into 100,000: 47 us by
+// class starts, 28 by keys; of one class 25 and 29; of 64 classes into 2^20:
+// 186 and 38. 2^16 arrivals in 2^26 entries: 58 us by keys, one probe
 // per step; 45 us, some of it the write-back of the previous call's outputs.
 __global__ __launch_bounds__(IT) void i_search(InsArgs a, int64_t units) {
   int64_t wv = (int64_t)blockIdx.x * (IT / kWave) +
@@ -154,11 +152,10 @@ __global__ __launch_bounds__(IT) void i_search(InsArgs a, int64_t units) {
   if (wv < wa) {
     const int64_t i = wv * kWave + lane;
     const KeyPL kj = new_key(a, min(i, a.m - 1));
-    // (the arrivals are sorted: their classes change from lane to lane)
-    const uint32_t before = (uint32_t)__shfl_up((int)kj.p, 1, kWave);
-    const int changes = __popcll(__ballot(lane > 0 && kj.p != before));
+    const uint32_t p0 = (uint32_t)__builtin_amdgcn_readlane((int)kj.p, 0);
+    const uint32_t p1 = (uint32_t)__builtin_amdgcn_readlane((int)kj.p, kWave - 1);
     int64_t at;
-    if (changes < kSearchClasses) {  // (uniform)
+    if (__ballot(kj.p != p0 && kj.p != p1) == 0) {  // (uniform) at most two classes
       int64_t lo = 0, hi = 0;
       uint64_t todo = ~0ull;
       while (todo) {  // (uniform) a class of the wave's arrivals at a time
