@@ -450,7 +450,8 @@ const char *sem_strerror(int code);
  *                           moves the earlier entries and places the arrivals),
  *          SEM_STAGE_POLICY (sem_schedule_policy*: for FCFS and HPJF the pass
  *                           that writes order and waits, for SJF the pass
- *                           that sums the waits per class),
+ *                           that sums the waits per class; no kernel up to
+ *                           2^21 requests, where the schedule sums them),
  *          SEM_STAGE_COST  (sem_schedule_cost*: the service-time pass),
  *          SEM_STAGE_MID   (multi-pass path: the middle scatter passes that keys
  *                           wider than two digits need; for narrower keys one
