@@ -434,7 +434,7 @@ struct PolLayout {
 };
 
 // `least`: with the fewest ranges, which every workspace has room for; a kept
-// size of an earlier build, whose ranges were all of that length, is enough.
+// size of an earlier version, whose ranges were all of that length, is enough.
 PolLayout policy_layout(int policy, int64_t n, bool least = false) {
   PolLayout L;
   size_t off = policy == SEM_POLICY_SJF ? align_up(layout_for(n).total) : kHeaderBytes;

@@ -27,8 +27,8 @@
 // of 256 with room for long ones take 35 us with five launches here, 49 with
 // nine; 4096 of 1024 take 80 us with nine, 91 with twelve.
 // Launches instead of one cooperative kernel with grid syncs: 16 queues of
-// 2^20 requests took 760 us there (its launch alone 24 us), 317 us here; 1000 of
-// 20,000 923 us, 462 us here.
+// 2^20 requests took 764 us there (its launch alone 24 us), 319 us here; 1000 of
+// 20,000 923 us, 435 us here.
 #include <algorithm>
 #include <type_traits>
 

@@ -16,8 +16,8 @@
 //   t_histF   final-digit counts and length sums of every tile
 //   t_final   offsets, order, waits; the last workgroup adds up the totals
 // Measured: a queue of 50,003 requests 156 us in the big-tile path's nine
-// launches (16K-item tiles: 4 workgroups), 28 us here; one of 2^20 76 us (64
-// workgroups), 51 us here.
+// launches (16K-item tiles: 4 workgroups), 26 us here; one of 2^20 76 us (64
+// workgroups), 49 us here.
 #include "tile_common.h"
 
 namespace semsched {

@@ -98,7 +98,7 @@ def test_batched_workspace_sizes(ss):
     assert ss.lib.sem_check(ctypes.c_void_p(0), ctypes.c_void_p(0)) == ss.SEM_EINVAL
 
 
-# Workspace sizes that callers may have kept from an earlier build of the library
+# Workspace sizes that callers may have kept from an earlier version of the library
 # (its functions' results there): a workspace of such a size is still enough.
 KEPT_QUEUE = {16385: 2582272, 17000: 2596608, 50003: 3486976, 65536: 3896064, 65537: 3909632,
               131073: 5679360, 262145: 9218816, 524289: 16297728, 1048576: 30441984,
