@@ -364,6 +364,27 @@ def test_batched_long_queue_key_and_index_beyond_64_bits():
     check_batched(p, l, off, 256, "long-keys-65-bits")
 
 
+# Keys of exactly the bits that a 32-bit element leaves beside the id, and one more
+# or fewer: 24 bits in queues of up to 256 requests, 20 in queues of up to 4096;
+# one class (no bits of the key above the length), two and five
+@pytest.mark.parametrize("size,bits", [(1, 24), (2, 24), (3, 24), (64, 24), (256, 24), (257, 20),
+                                       (1000, 20), (4096, 20)])
+@pytest.mark.parametrize("classes", [1, 2, 5])
+def test_batched_keys_that_fill_the_element(size, bits, classes):
+    rng = np.random.default_rng(size + classes)
+    queues = []
+    for span in (bits - 4, bits - 3, bits - 2, bits - 1, bits, bits + 1):
+        for low in (0, 12345):
+            l = rng.integers(low, low + (1 << span), size)
+            l[0], l[-1] = low + (1 << span) - 1, low  # the whole span
+            queues.append((rng.integers(0, classes, size), l))
+            queues.append((np.full(size, classes - 1), l))  # one class in the queue
+    p = np.concatenate([q[0] for q in queues]).astype(np.uint8)
+    l = np.concatenate([q[1] for q in queues]).astype(np.int32)
+    off = np.arange(len(queues) + 1, dtype=np.int64) * size
+    check_batched(p, l, off, classes, f"full-element-{size}-{classes}")
+
+
 def test_batched_wide_keys_in_short_queues():
     # lengths over the whole int32 range: short queues whose key does not fit
     # a 32-bit element go to the 64-bit kernel, long ones to the segmented sort
