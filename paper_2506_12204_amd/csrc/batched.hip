@@ -359,7 +359,10 @@ __device__ bool schedule_loaded(const BArgs& a, int64_t s, int64_t base, int m,
   }
   const uint32_t wl = bit_width32(lmax - lmin);
   const uint32_t kb = wl + bit_width32(pmax - pmin);
-  if (kb + IDB > EBITS) return false;
+  // (one class: no key bits above the length, but the class is taken by a shift
+  // of all below it, which must stay below the element's width: a shift of 32
+  // is one of 0)
+  if (max(kb, wl + 1) + IDB > EBITS) return false;
   const uint32_t P = pmax - pmin + 1;
   // class sums in kClsCopies copies (lane % kClsCopies) when they fit, so that
   // the lanes of a round that change class together spread over that many
@@ -453,14 +456,7 @@ __device__ bool schedule_loaded(const BArgs& a, int64_t s, int64_t base, int m,
   const uint64_t lane_part = (uint64_t)lmin * (uint32_t)j0;
   const uint64_t round_part = (uint64_t)lmin * kWave;
   const uint32_t idmask = (1u << IDB) - 1;
-  // The class above the length. With one class and a length of all the bits a
-  // u32 element has left, there is nothing above it (cshift is 32, which a
-  // plain shift would take as 0): a field of no bits then.
-  const uint32_t cshift = IDB + wl, cbits = kb - wl;
-  auto class_of = [&](ET x) {
-    if constexpr (WIDE) return (int)(uint32_t)(x >> cshift);
-    else return (int)__builtin_amdgcn_ubfe(x, cshift, cbits);
-  };
+  const uint32_t cshift = IDB + wl;  // below EBITS
   const __amdgpu_buffer_rsrc_t ro = buffer_over(a.order + base, 4u * (uint32_t)m);
   const __amdgpu_buffer_rsrc_t rw = buffer_over(a.wait + base, 8u * (uint32_t)m);
   int cur = -1;
@@ -486,7 +482,7 @@ __device__ bool schedule_loaded(const BArgs& a, int64_t s, int64_t base, int m,
       __builtin_amdgcn_raw_buffer_store_b64(u32x2{(uint32_t)wt, (uint32_t)(wt >> 32)}, rw, 8 * j,
                                             0, 0);
       if (j < m) {
-        const int cls = class_of(e[r]);  // class - pmin
+        const int cls = (int)(uint32_t)(e[r] >> cshift);  // class - pmin
         if (cls != cur) {  // a lane's positions increase, so its classes do not decrease
           if (cur >= 0)
             atomicAdd(reinterpret_cast<unsigned long long*>(&sh.cls[cur * K + (lane & (K - 1))]),
