@@ -362,7 +362,7 @@ __device__ bool schedule_loaded(const BArgs& a, int64_t s, int64_t base, int m,
   // (one class: no key bits above the length, but the class is taken by a shift
   // of all below it, which must stay below the element's width: a shift of 32
   // is one of 0)
-  if (max(kb, wl + 1) + IDB > EBITS) return false;
+  if ((WIDE ? kb : max(kb, wl + 1)) + IDB > EBITS) return false;
   const uint32_t P = pmax - pmin + 1;
   // class sums in kClsCopies copies (lane % kClsCopies) when they fit, so that
   // the lanes of a round that change class together spread over that many
